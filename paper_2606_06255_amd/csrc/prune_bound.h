@@ -76,4 +76,43 @@ RFPS_HOST_DEVICE inline float prune_threshold(float R, float dv)
     return prune_threshold_with(R, dv, kPruneInner, kPruneOuter);
 }
 
+// Distance filter on the matrix cores.  The samplers test many points s
+// against many points p with one matrix product: with both shifted by a
+// common origin, fl(x - o),
+//   D = col(|s|^2) - 2 p.s - row(limit, |p|^2)
+// (a 4-long dot product and its addend, FP32), and the pair is kept for the
+// exact FP32 work iff !(D >= 0).  A kept pair costs work; a dropped one must
+// be one whose formula distance ((dx*dx + dy*dy) + dz*dz) is not below
+// `limit`.  Why that is so (u = 2^-24, a = |p|, b = |s| of the shifted
+// points, r the true distance):
+//   - the shift moves each point by at most u a and u b, so the squared
+//     distance of the shifted points is at most r^2 + 2.01 u (a + b)^2, and
+//     the formula distance is at least r^2 (1 - 5.1 u);
+//   - |s|^2 and col() round four times (4 u b^2), row() errs by at most
+//     6 u a^2 + 3 u limit, and the product's nine operations err by at most
+//     2 u each, truncation included, of partial sums below
+//     b^2 + 2 a b + a^2 + limit (18 u times that);
+//   - with (a + b)^2 <= 2 (a^2 + b^2) and 2 a b <= a^2 + b^2 these add up to
+//     less than 63 u (a^2 + b^2) + 27 u limit, and the two sides give
+//     2^-17 (a^2 + b^2) = 128 u (a^2 + b^2) and 2^-19 limit = 32 u limit away.
+// A limit or square beyond 1e36 (overflow, or NaN: "never skip") keeps every
+// pair; 1e-36 keeps the comparison clear of subnormals.
+constexpr float kFilterNorm = 1.0f - 0x1p-17f;
+constexpr float kFilterLimit = 1.0f + 0x1p-19f;
+
+RFPS_HOST_DEVICE inline float filter_col(float n2)
+{
+    return n2 <= 1e36f ? n2 * kFilterNorm : -INFINITY;
+}
+
+RFPS_HOST_DEVICE inline float filter_row(float limit, float n2)
+{
+    if (!(limit <= 1e36f) || !(n2 <= 1e36f))
+        return INFINITY;
+    const float a = limit * kFilterLimit;
+    const float b = n2 * kFilterNorm;
+    const float t = a - b;
+    return t + 1e-36f;
+}
+
 }  // namespace rfps

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "rfps_internal.h"
+#include "round_layout.h"
 
 using namespace rfps;
 
@@ -228,6 +229,21 @@ int resolve_tile(const rfps_params *p) { return (p && p->tile) ? p->tile : kWave
 
 bool aligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) % kAlign) == 0; }
 
+// On-chip bytes a workgroup's share may take.
+bool sampler_budget(const DeviceInfo &d, SampleLaunch &L)
+{
+    L.max_lds = d.max_lds;
+    if (L.R > 0) {
+        L.lds_budget = rounds_budget((uint32_t)d.max_lds);
+        return L.lds_budget != 0;
+    }
+    const size_t stat = rfps_sampler_static_lds();
+    if (stat == 0 || (size_t)d.max_lds <= stat + 1024)
+        return false;
+    L.lds_budget = (uint32_t)((d.max_lds - stat - 256) & ~(size_t)255);
+    return true;
+}
+
 // Plain-FPS workspace: status word, exchange board, distance array.
 struct PlainLayout {
     size_t status, board, dist, total;
@@ -340,21 +356,21 @@ rfps_status rfps_sample(const rfps_index *index, int32_t m, int32_t start, const
         return RFPS_ERR_UNSUPPORTED;
     SampleLaunch L;
     L.flags = params ? params->flags : 0u;
-    // default workgroups: every compute unit; clouds below 64k points take
-    // half of them for the multi-pick sampler (a round then exchanges and
-    // merges half the candidates, and each workgroup still owns a few hundred
-    // points: measured 5-10 % faster on 4k-30k point clouds)
-    const int all = std::min(d->cus, kMaxGroups);
-    const bool small = index->n < (1 << 16) && !(L.flags & (RFPS_F_SINGLE_PICK | RFPS_F_NO_PRUNE));
-    L.G = (params && params->groups) ? params->groups : (small ? std::max(1, all / 2) : all);
-    // the multi-pick sampler is the default; plain (unpruned) sampling and an
-    // explicit request use one selection per exchange
+    // The multi-pick sampler is the default; plain (unpruned) sampling and an
+    // explicit request use one selection per exchange.  Default workgroups:
+    // every compute unit; the multi-pick sampler's plan then picks the team
+    // that samples among them (the capacity limit counts all of them, or half
+    // on clouds below 65,536 points).
     const bool single = (L.flags & (RFPS_F_SINGLE_PICK | RFPS_F_NO_PRUNE)) != 0;
-    L.R = single ? 0 : ((params && params->lookahead) ? params->lookahead : kDefaultLookahead);
-    const size_t stat = rfps_sampler_static_lds(L.R);
-    if (stat == 0 || (size_t)d->max_lds <= stat + 1024)
+    const int all = std::min(d->cus, kMaxGroups);
+    L.fixed_g = params && params->groups;
+    L.G = L.fixed_g ? params->groups : all;
+    L.Gcap = (!L.fixed_g && !single && index->n < (1 << 16)) ? std::max(1, all / 2) : L.G;
+    L.K = (params && params->lookahead) ? params->lookahead : 0;
+    L.R = single ? 0 : (L.K ? L.K : kDefaultLookahead);
+    L.steps = 0;
+    if (!sampler_budget(*d, L))
         return RFPS_ERR_UNSUPPORTED;
-    L.lds_budget = (uint32_t)((d->max_lds - stat - 256) & ~(size_t)255);
     if (L.G > d->cus)
         return RFPS_ERR_UNSUPPORTED;
     const IndexView v = make_view(index->ws, index->n, index->n_vox, index->tile, index->shells);
@@ -581,11 +597,13 @@ rfps_status rfps_sample_batched(const float *xyz, int32_t n, const int32_t *offs
     SampleLaunch L;
     L.G = d->cus;
     L.flags = flags;
-    L.R = (params && params->lookahead) ? params->lookahead : kDefaultLookahead;
-    const size_t stat = rfps_sampler_static_lds(L.R);
-    if (stat == 0 || (size_t)d->max_lds <= stat + 1024)
+    L.Gcap = L.G;
+    L.fixed_g = true;
+    L.K = (params && params->lookahead) ? params->lookahead : 0;
+    L.R = L.K ? L.K : kDefaultLookahead;
+    L.steps = 2;
+    if (!sampler_budget(*d, L))
         return RFPS_ERR_UNSUPPORTED;
-    L.lds_budget = (uint32_t)((d->max_lds - stat - 256) & ~(size_t)255);
 
     IndexView v = make_view_l(ws, BL, n, fixed_n_vox, resolve_tile(params));
     v.bc.batch = batch;

@@ -60,7 +60,8 @@ struct IndexHeader {
     double origin[3];    // centre of the range shells (bounding-box centre)
     double shell_inv;    // 1 / shell spacing, 0 without shells
     uint32_t shell_cap;  // shells in use (the last one is open-ended); 1 without shells
-    uint32_t pad_;
+    // shape of the team that samples a single cloud (k_rounds_plan)
+    int32_t team_g, team_k, team_steps;
     unsigned long long tele[kTeleFields];  // rfps_telemetry, in its field order
 };
 
@@ -232,24 +233,26 @@ constexpr int kDppBcast31 = 0x143;
 // a ballot of a compound condition first turns it into a value per lane.
 __device__ __forceinline__ unsigned long long ballot64(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 
+// (the first operand, kept by lanes without a source, is the identity of the
+// operation: the move then folds into it, one instruction a step)
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
 {
-    v = max(v, dpp_u32<kDppQuadSwap1>(v, v));
-    v = max(v, dpp_u32<kDppQuadSwap2>(v, v));
-    v = max(v, dpp_u32<kDppHalfMirror>(v, v));
-    v = max(v, dpp_u32<kDppRowMirror>(v, v));
-    v = max(v, dpp_u32<kDppBcast15, 0xa>(v, v));
-    v = max(v, dpp_u32<kDppBcast31, 0xc>(v, v));
+    v = max(v, dpp_u32<kDppQuadSwap1>(0u, v));
+    v = max(v, dpp_u32<kDppQuadSwap2>(0u, v));
+    v = max(v, dpp_u32<kDppHalfMirror>(0u, v));
+    v = max(v, dpp_u32<kDppRowMirror>(0u, v));
+    v = max(v, dpp_u32<kDppBcast15, 0xa>(0u, v));
+    v = max(v, dpp_u32<kDppBcast31, 0xc>(0u, v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)
 {
-    v = min(v, dpp_u32<kDppQuadSwap1>(v, v));
-    v = min(v, dpp_u32<kDppQuadSwap2>(v, v));
-    v = min(v, dpp_u32<kDppHalfMirror>(v, v));
-    v = min(v, dpp_u32<kDppRowMirror>(v, v));
-    v = min(v, dpp_u32<kDppBcast15, 0xa>(v, v));
-    v = min(v, dpp_u32<kDppBcast31, 0xc>(v, v));
+    v = min(v, dpp_u32<kDppQuadSwap1>(~0u, v));
+    v = min(v, dpp_u32<kDppQuadSwap2>(~0u, v));
+    v = min(v, dpp_u32<kDppHalfMirror>(~0u, v));
+    v = min(v, dpp_u32<kDppRowMirror>(~0u, v));
+    v = min(v, dpp_u32<kDppBcast15, 0xa>(~0u, v));
+    v = min(v, dpp_u32<kDppBcast31, 0xc>(~0u, v));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
@@ -423,20 +426,24 @@ hipError_t launch_scan(const uint32_t *in, uint32_t *out, int n, uint32_t *parti
                        hipStream_t s);
 
 struct SampleLaunch {
-    int G;
-    int R;                // lookahead depth of the multi-pick sampler; 0 = one selection per exchange
+    int G;                // workgroups launched
+    int Gcap;             // workgroups whose shares the capacity limit counts
+    bool fixed_g;         // the caller asked for G workgroups
+    int R;                // candidates per workgroup the limit counts; 0 = one selection per exchange
     uint32_t flags;
-    uint32_t lds_budget;  // dynamic LDS bytes per workgroup
+    uint32_t lds_budget;  // on-chip bytes a workgroup's share may take (the capacity limit)
+    int max_lds;          // bytes of LDS a workgroup may use
+    int K;                // multi-pick sampler: candidates a workgroup publishes as asked for; 0 = by rule
+    int steps;            // lookahead steps of a wavefront (batched sampler)
 };
-// Static LDS of the sampler kernel chosen by R (bytes); 0 if R is not supported.
-size_t rfps_sampler_static_lds(int R);
+// Static LDS of the one-pick sampler kernel (bytes).
+size_t rfps_sampler_static_lds();
 hipError_t launch_rfps_sample(const IndexView &v, int m, int start, const SampleLaunch &L, int32_t *out_idx,
                               float *out_d2, hipStream_t s);
 // The unfused sampler (sample_unfused.hip): two launches per selection.
 hipError_t launch_rfps_unfused(const IndexView &v, int m, int start, uint32_t flags, int32_t *out_idx,
                                float *out_d2, hipStream_t s);
 // The multi-pick sampler (sample_rounds.hip); called by launch_rfps_sample.
-size_t rfps_rounds_static_lds(int R);
 hipError_t launch_rfps_rounds(const IndexView &v, int m, int start, const SampleLaunch &L, int32_t *out_idx,
                               float *out_d2, hipStream_t s);
 // Exchange floor probe (sample_rounds.hip): `rounds` bare exchanges of W
@@ -452,22 +459,23 @@ hipError_t launch_sample_finalize(const IndexHeader *hdr, int m, int32_t *out_id
 // cannot be recorded into a graph) it is an ordinary launch after the same
 // residency check from the occupancy calculator; every wait in the
 // persistent kernels is bounded, so even a shared device cannot hang them.
-inline hipError_t launch_persistent(const void *fn, int G, void **args, size_t lds, hipStream_t s)
+inline hipError_t launch_persistent(const void *fn, int G, void **args, size_t lds, hipStream_t s,
+                                    int block = kBlock)
 {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(s, &cs);
     if (e != hipSuccess)
         return e;
     if (cs == hipStreamCaptureStatusNone)
-        return hipLaunchCooperativeKernel(fn, dim3(G), dim3(kBlock), args, (unsigned)lds, s);
+        return hipLaunchCooperativeKernel(fn, dim3(G), dim3(block), args, (unsigned)lds, s);
     int dev = 0, cus = 0, per_cu = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess ||
         (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess ||
-        (e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlock, lds)) != hipSuccess)
+        (e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, lds)) != hipSuccess)
         return e;
     if ((long long)per_cu * cus < G)
         return hipErrorCooperativeLaunchTooLarge;
-    return hipLaunchKernel(fn, dim3(G), dim3(kBlock), args, lds, s);
+    return hipLaunchKernel(fn, dim3(G), dim3(block), args, lds, s);
 }
 
 // Batched index build (index_build.hip) and batched sampling (sample_rounds.hip).

@@ -1,0 +1,108 @@
+// Layout and capacity rules of the multi-pick sampler, shared by its kernels,
+// the launchers and the host tests.
+#pragma once
+
+#include <cstdint>
+
+#include "prune_bound.h"
+
+namespace rfps {
+
+// Threads and wavefronts of a sampler workgroup.
+constexpr int kRBlock = 512;
+constexpr int kRLanes = 64;
+constexpr int kRWaves = kRBlock / kRLanes;
+// Lookahead steps of a wavefront, and so candidates of a workgroup, at most.
+constexpr int kMaxSteps = 8;
+constexpr int kMaxRec = kRWaves * kMaxSteps;
+// Candidates one merge lists, and so the selections one round may settle
+// (the merge stops there; a shorter round is always valid).
+constexpr int kList = 256;
+constexpr int kListWords = kList / kRLanes;
+// Side of the 16 x 16 blocks the matrix cores filter.
+constexpr int kBlk = 16;
+// Static LDS of a sampler workgroup, at most; the rest of the compute unit's
+// is its tiles and points.
+constexpr uint32_t kRoundsStatic = 27712;
+
+// A published slot: K + 1 units of four 64-bit words, one unit per candidate
+// and one for the bound.  A word is tag << 48 | 48 payload bits.
+constexpr int kUnit = 4;
+RFPS_HOST_DEVICE inline uint32_t slot_units(uint32_t K) { return K + 1u; }
+
+// Tile slots of a workgroup: its tiles are dealt to the wavefronts in turn,
+// and every wavefront's share is padded to whole filter blocks.
+RFPS_HOST_DEVICE inline uint32_t wave_slots(uint32_t tiles)
+{
+    return ((tiles + kRWaves - 1) / kRWaves + kBlk - 1) / kBlk * kBlk;
+}
+
+RFPS_HOST_DEVICE inline uint32_t rounds_lds_need(uint32_t tiles, uint32_t pts)
+{
+    return wave_slots(tiles) * kRWaves * 36u + pts * 20u;
+}
+
+// The share a workgroup may take: R candidates with whole coordinates per
+// slot, a private copy of the distances and the sort buffers of one list, as
+// counted here, against the budget the caller passes.  This is the sampler's
+// documented capacity (RFPS_ERR_CAPACITY beyond it); the layout above needs
+// less for every share it admits (4 bytes less per point, and more than the
+// padding of the tile slots costs).
+RFPS_HOST_DEVICE inline uint32_t share_bytes(uint32_t tiles, uint32_t pts, uint32_t G, uint32_t R)
+{
+    uint32_t sort = 2 * kRLanes;
+    while (sort < G * R)
+        sort <<= 1;
+    const uint32_t keys = 2u * sort, picks = 6u * kRLanes;
+    const uint32_t padded = tiles ? (tiles + 31u) / 32u * 32u : 32u;
+    return tiles * 40u + padded * 16u + pts * 24u + G * (6u * R + 2u) * 4u + (2u * kRLanes + 2u) * 4u + sort * 4u +
+           (keys > picks ? keys : picks) * 4u + 128u;
+}
+RFPS_HOST_DEVICE inline bool share_granted(uint32_t tiles, uint32_t pts, uint32_t G, uint32_t R,
+                                                       uint32_t budget)
+{
+    return pts <= 65535u && share_bytes(tiles, pts, G, R) <= budget;
+}
+
+// Shape of a team: its workgroups, the candidates each publishes per round
+// and the lookahead steps of each wavefront.  A cloud most of whose tiles
+// hold many of its picks (few, full tiles: a spinning sweep sampled to a
+// quarter) needs depth, one with several tiles per pick breadth.  Measured
+// sampling times in ms for (workgroups, candidates, steps):
+//   sweep 114,624 -> 28,656 (12.7 picks per tile): (64, 6, 4) 5.0, (64, 4, 2)
+//   6.9, (256, 3, 2) 6.9; sweep 28,656 -> 7,164: (32, 6, 4) 1.77, (128, 3, 2) 2.3
+//   room 80,000 -> 20,000 (2.1 picks per tile): (256, 3, 2) 2.87, (64, 6, 4) 4.3
+constexpr int kDeepPicks = 6;  // picks per tile from which depth pays
+struct TeamShape {
+    int G, K, steps;
+};
+RFPS_HOST_DEVICE inline TeamShape team_shape(uint32_t tiles, uint32_t m)
+{
+    TeamShape t;
+    const bool deep = m > (uint32_t)kDeepPicks * tiles;
+    // enough workgroups that the exchange, whose cost grows with the team,
+    // still replaces more local work than it adds; the best team of each
+    // range is within 5 % of its neighbours' at the limits
+    if (deep)
+        t.G = tiles < 400 ? 16 : tiles < 1500 ? 32 : 64;
+    else
+        t.G = tiles < 500 ? 32 : tiles < 2500 ? 64 : tiles < 12000 ? 128 : 256;
+    t.K = deep ? 6 : 3;
+    t.steps = deep ? 4 : 2;
+    return t;
+}
+
+// Bytes a workgroup's share may take by that rule: what a compute unit has
+// beside 6,496 bytes.
+constexpr uint32_t kRoundsReserve = 6496;
+RFPS_HOST_DEVICE inline uint32_t rounds_budget(uint32_t max_lds)
+{
+    return max_lds <= kRoundsReserve + 1024u ? 0u : (max_lds - kRoundsReserve - 256u) & ~255u;
+}
+// Dynamic LDS the sampler is launched with.
+RFPS_HOST_DEVICE inline uint32_t rounds_dynamic(uint32_t max_lds)
+{
+    return max_lds > kRoundsStatic + 1024u ? (max_lds - kRoundsStatic) & ~63u : 0u;
+}
+
+}  // namespace rfps

@@ -380,10 +380,8 @@ __global__ __launch_bounds__(kBlock) void k_rfps(SampleArgs a)
 
 namespace rfps {
 
-size_t rfps_sampler_static_lds(int R)
+size_t rfps_sampler_static_lds()
 {
-    if (R > 0)
-        return rfps_rounds_static_lds(R);
     hipFuncAttributes attr;
     if (hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(k_rfps)) != hipSuccess)
         return 0;

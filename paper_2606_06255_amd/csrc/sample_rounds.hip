@@ -1,58 +1,64 @@
 // RadiusFPS-G with certified multi-pick rounds (the default sampler), for a
 // single cloud and for batches of clouds.
 //
-// A cloud is sampled by a team of G workgroups.  Rank r of the team owns the
-// cloud's tiles t with (t - first tile) % G == r (tiles of neighbouring voxels
-// land on different workgroups, so the unpruned work near a new sample
-// spreads over the team) and keeps their points (x, y, z, Dist_p, a private
-// lookahead copy of Dist_p, original index) and per-tile state (sphere, packed
-// Dist_v key, pruning threshold) in LDS for the whole cloud.  One exchange
-// settles a whole round of selections:
+// A cloud is sampled by a team of G workgroups of eight wavefronts.  Rank r of
+// the team owns the cloud's tiles t with (t - first tile) % G == r, and deals
+// them to its wavefronts in turn (tiles of neighbouring voxels land on
+// different workgroups, and there on different wavefronts, so the unpruned
+// work near a new sample spreads).  Points (x, y, z, Dist_p, original index)
+// and per-tile state (centre, radius, packed Dist_v key, filter row) stay in
+// LDS for the whole cloud.  One exchange settles a whole round of selections:
 //
-//   L  lookahead: every workgroup runs R steps of FPS on its own points only
-//      (on the private copy, with the same spherical pruning), giving local
-//      candidates l_1..l_R with local keys k_1 > .. > k_R, and for every step
-//      h the runner-up u_h, the largest local key of the group's other points
-//      when l_h was chosen.  The group's bound k_{R+1} = max(u_R, (0, l_R))
-//      is at least every local key once l_R is applied too (applying it only
-//      lowers the others, and its own distance becomes 0), so that last
-//      update is never run;
-//   X  exchange: each workgroup publishes its candidates (coordinates, local
-//      distance, original index, runner-up distance) and k_{R+1};
-//   M  merge: every workgroup replays the same deterministic merge.  Group g
-//      keeps a head h_g (how many of its candidates were taken).  Its bound
-//      B_g = k_{h_g+1} is an upper bound on the true key of every point of g
-//      not taken: the true distances include every pick of the round so far,
-//      among them l_1..l_{h_g}, so they are at most the local ones.  Hence the largest
-//      true key anywhere is at most max_g B_g, and if the head candidate of
-//      the group with the largest bound still has its true key equal to its
-//      local key (no other pick of the round lowered it), that candidate is
-//      exactly the next FPS selection (the Sec. 3.1 rule; keys are unique).
-//      The local distance already includes the group's own earlier picks
-//      (those it skipped are at least as far), so the true distance is the
-//      local one lowered by the other groups' earlier picks.  When the head
-//      l_h of g fails this test, its true key t is known exactly, and the
-//      other points of g are bounded by u_h (their local keys at step h
-//      assumed only l_1..l_{h-1}, which are picks); the later candidates of g
-//      are dropped, l_h is listed again with key t, and the merge goes on
-//      under the larger bound.  The merge lists the candidates above the
-//      largest bound, finds with all threads of the workgroup their order and,
-//      for each, the listed candidates that would lower it, and then walks the
-//      order in one wavefront, re-listing at every failure;
-//   A  apply: all picks of the round update the true state (spherical test
-//      per tile and pick, point skip, strict update, tile-key resync).
+//   L  lookahead: every wavefront proposes `steps` candidates of its own
+//      tiles: it takes the largest tile key, notes the point and the
+//      runner-up (the largest distance among its other points), applies the
+//      candidate to its own tile only, in registers, and takes the largest
+//      key again.  Its bound is the largest key left.  Applying a candidate
+//      only lowers keys, so tiles it was not applied to keep keys that bound
+//      their points from above;
+//   X  exchange: a workgroup publishes its K largest candidates and a bound
+//      that is at least every other key it holds;
+//   M  merge: every workgroup runs the same deterministic merge.  S* is the
+//      largest bound of the team: every point that was not published has its
+//      key at or below it.  The candidates above S* are listed, and for each
+//      the listed ones of no smaller distance that could lower it.  A
+//      candidate none of those lowers keeps its distance until it is the
+//      largest of all, so it is exactly one of the next selections of plain
+//      FPS (the Sec. 3.1 rule; keys are unique).  One that is lowered fails:
+//      its true key is at most its new distance and the other points of its
+//      wavefront are bounded by its runner-up, so the bound rises to the
+//      larger of the two and candidates at or below it leave;
+//   A  apply: every wavefront applies the round's picks to its own tiles
+//      (spherical test of 16 tiles by 16 picks at a time on the matrix cores,
+//      strict update, tile-key resync), and starts its next lookahead without
+//      a barrier.
 //
-// Every round certifies at least one selection (at round start the largest
-// bound is attained by its own head), so the loop always terminates; the
-// output equals plain FPS bit for bit.
+// The largest candidate of a round always survives, so the loop terminates,
+// and the output equals plain FPS bit for bit.  A candidate's order among the
+// picks is its key order, which rank 0 of the team works out while the next
+// exchange is in flight.
 //
-// Exchange scopes: a team spread over the device exchanges through
-// agent-scope atomics (coherent across XCDs); a team whose workgroups all
-// sit on one XCD exchanges through that XCD's L2 (plain stores, L1
-// invalidate before every poll), which halves the exchange latency.
+// What bounds a round (1,048,576 points -> 65,536 picks, 256 workgroups, 879
+// rounds of 10.3 us, 74 picks each): lookahead 1.6 us (a serial chain of wave
+// maxima), exchange 3.7 us (2.7 of them are the bare exchange of the team's
+// 32 KB, measured with nothing else in a round), list 1.0, conflicts 1.4,
+// certification 1.7, apply 1.0.  One lookahead per wavefront instead of one
+// per workgroup removes the serial steps over all tiles of a workgroup (the
+// largest term before: 16 steps on one list of tile keys), and the matrix
+// cores take the pair tests, which were the next.  Sampling times before and
+// after: 1,048,576 -> 65,536 14.9 -> 9.0 ms, 114,623 -> 28,655 Euclidean 9.9
+// -> 5.9 ms, 80,000 -> 20,000 4.4 -> 2.9 ms, 32 clouds of 8k to 120k points
+// 34 -> 15.6 ms.
+//
+// Exchange scopes: a team spread over the device stores through agent-scope
+// atomics (coherent across XCDs); a team whose workgroups all sit on one XCD
+// exchanges through that XCD's L2.  Both read past the L1 (sc1): every word
+// carries the tag of its exchange, so a thread keeps reading its own 32-byte
+// units until the words are there.
 #include <type_traits>
 
 #include "rfps_internal.h"
+#include "round_layout.h"
 
 namespace rfps {
 
@@ -66,29 +72,17 @@ struct RoundArgs {
     unsigned long long *trace;
     int32_t *out_idx;
     float *out_d2;
-    int32_t n, m, start, G;
+    int32_t n, m, start;
     uint32_t flags;
     uint32_t lds_budget;
+    int32_t K, steps;  // candidates a workgroup publishes per round, lookahead steps of a wavefront
     // batched mode
     BatchCtl bc;
     BatchState *bstate;
     const uint32_t *tile_first;  // [batch+1]
     const int32_t *order;        // [batch] clouds by decreasing cost
+    const uint32_t *cl_bb;       // [batch][6] boxes
 };
-
-// Candidates one merge lists, and so the selections one round may settle
-// (the merge stops there; a shorter round is always valid).
-constexpr int kList = 2 * kWave;
-constexpr int kMaxRoundPicks = kList;
-// Words of the order of a cut list (kList + 1, rounded to whole 8-byte words).
-constexpr uint32_t kOrdWords = kList + 2;
-
-// Tiles a wavefront tests per pass of the apply phase (their sphere loads are
-// in flight together; 8 measured faster than 4 or 16).
-constexpr int kApplyTiles = 8;
-// Listed candidates a wavefront ranks per pass of the merge's ranking loop.
-constexpr int kRankPerPass = 2;
-
 
 // Value of lane l of v (l uniform).
 __device__ __forceinline__ float lane_f32(float v, int l)
@@ -99,42 +93,16 @@ __device__ __forceinline__ uint32_t lane_u32(uint32_t v, int l)
 {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
 }
-// Failed candidates a round re-lists before it ends (each failure lowers a
-// listed key, so the loop ends anyway; this caps the work of one round).
-constexpr uint32_t kMaxFailures = 64;
-
-// Entries of the merge's sort buffers: the next power of two of G * R, at
-// least 128 (the smallest network the merge runs).
-__host__ __device__ __forceinline__ uint32_t sort_cap(uint32_t G, uint32_t R)
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int l)
 {
-    uint32_t s = 2 * kWave;
-    while (s < G * R)
-        s <<= 1;
-    return s;
+    return ((unsigned long long)lane_u32((uint32_t)(v >> 32), l) << 32) | lane_u32((uint32_t)v, l);
+}
+__device__ __forceinline__ uint32_t uniform_u32(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
-// 4-byte words of the region the merge uses first for its sorted keys and
-// then for the pick coordinates.
-__host__ __device__ __forceinline__ uint32_t merge_words(uint32_t G, uint32_t R)
-{
-    const uint32_t keys = 2u * sort_cap(G, R), picks = 3u * kMaxRoundPicks;
-    return keys > picks ? keys : picks;
-}
-
-// Tile spheres a workgroup keeps: its tile count rounded up to whole passes
-// of the apply phase (kApplyTiles per wavefront), at least one pass; the
-// padding never passes a test.
-__host__ __device__ __forceinline__ uint32_t padded_tiles(uint32_t tiles)
-{
-    constexpr uint32_t q = (uint32_t)(kApplyTiles * kWavesPerBlock);
-    return tiles ? (tiles + q - 1) / q * q : q;
-}
-
-__host__ __device__ __forceinline__ uint32_t rounds_lds_need(uint32_t tiles, uint32_t pts, uint32_t G, uint32_t R)
-{
-    return tiles * 40u + padded_tiles(tiles) * 16u + pts * 24u + G * (6u * R + 2u) * 4u + kOrdWords * 4u +
-           sort_cap(G, R) * 4u + merge_words(G, R) * 4u + 128u;
-}
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Capacity plan of one team of G workgroups over the tiles [tb, te).
 __device__ __forceinline__ bool team_fits(const uint32_t *tcnt, uint32_t tb, uint32_t te, int G, int R,
@@ -145,40 +113,74 @@ __device__ __forceinline__ bool team_fits(const uint32_t *tcnt, uint32_t tb, uin
         ++tiles;
         pts += tcnt[t];
     }
-    return pts <= 65535u && rounds_lds_need(tiles, pts, G, R) <= budget;
+    return share_granted(tiles, pts, G, R, budget);
 }
 
-__global__ __launch_bounds__(kBlock) void k_rounds_plan(IndexHeader *hdr, const uint32_t *__restrict__ tcnt,
-                                                        int G, int R, uint32_t budget)
+// Plan of a single cloud: checks the capacity of the team of Gcap workgroups
+// (R candidates) the caller's parameters stand for, then settles the shape
+// the sampler runs with, in the header: G0 workgroups when the caller asked
+// for a team, else by team_shape, enlarged until every share fits the
+// sampler's LDS.  K0 as asked for, or 0.  One workgroup.
+constexpr int kPlanBlock = 1024;
+__global__ __launch_bounds__(kPlanBlock) void k_rounds_plan(IndexHeader *hdr, const uint32_t *__restrict__ tcnt,
+                                                            int m, int Gall, int Gcap, int G0, int K0, int R,
+                                                            uint32_t budget, uint32_t lds)
 {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= G || hdr->build_status)
+    __shared__ uint32_t s_tiles[kMaxGroups], s_pts[kMaxGroups];
+    __shared__ uint32_t s_bad, s_big;
+    if (hdr->build_status)
         return;
-    if (!team_fits(tcnt, 0, hdr->n_tiles, G, R, budget, g))
+    const int tid = threadIdx.x;
+    const uint32_t NT = hdr->n_tiles;
+    TeamShape shape = team_shape(NT, (uint32_t)m);
+    // shares of a team of G workgroups (tile t belongs to rank t % G)
+    auto shares = [&](int G) {
+        __syncthreads();
+        if (tid < kMaxGroups)
+            s_tiles[tid] = s_pts[tid] = 0u;
+        if (tid == 0)
+            s_bad = s_big = 0u;
+        __syncthreads();
+        for (uint32_t t = tid; t < NT; t += kPlanBlock) {
+            const uint32_t r = t % (uint32_t)G;
+            atomicAdd(&s_tiles[r], 1u);
+            atomicAdd(&s_pts[r], tcnt[t]);
+        }
+        __syncthreads();
+    };
+    shares(Gcap);
+    if (tid < Gcap && !share_granted(s_tiles[tid], s_pts[tid], Gcap, R, budget))
         set_status(&hdr->sample_status, RFPS_ERR_CAPACITY);
-}
-
-// One wavefront recomputes the key, best point and threshold of tile lt
-// (points ls .. ls + cnt - 1) from each lane's distance d and original index
-// o of its point, held in registers (all lanes of the wave must call it).
-// The threshold goes to tthr[lt * TS].
-template <int TS>
-__device__ __forceinline__ void tile_rekey(int lane, uint32_t lt, uint32_t ls, uint32_t cnt, float d, uint32_t o,
-                                           const float *trad, unsigned long long *tkey, uint32_t *tbest, float *tthr)
-{
-    const bool valid = (uint32_t)lane < cnt;
-    const unsigned long long key = valid ? pack_key(d, o) : 0ull;
-    const unsigned long long kmax = wave_max_u64(key);
-    const unsigned long long hit = ballot64(key == kmax) & ballot64(valid);
-    if (lane == 0) {
-        tkey[lt] = kmax;
-        tbest[lt] = ls + (uint32_t)(__ffsll((long long)hit) - 1);
-        tthr[lt * TS] = prune_threshold(trad[lt], key_d2(kmax));
+    int G = G0;
+    if (!G) {
+        G = min(shape.G, Gall);
+        for (;;) {
+            shares(G);
+            if (tid < G && rounds_lds_need(s_tiles[tid], s_pts[tid]) > lds)
+                s_big = 1u;
+            __syncthreads();
+            if (!s_big || G >= Gcap)
+                break;
+            G = min(2 * G, Gcap);
+        }
+    }
+    // a thread reads at most two units of an exchange unless the caller
+    // asked for more candidates
+    int K = K0;
+    if (!K) {
+        K = shape.K;
+        while (K > 3 && G * (int)slot_units((uint32_t)K) > 2 * kRBlock)
+            --K;
+    }
+    if (tid == 0) {
+        hdr->team_g = G;
+        hdr->team_k = K;
+        hdr->team_steps = shape.steps;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Exchange primitives for the two scopes.
+// Exchange primitives for the scopes of a team.
 // ---------------------------------------------------------------------------
 enum class Scope { Agent, Xcd };
 
@@ -205,30 +207,119 @@ __device__ __forceinline__ unsigned long long bload(const unsigned long long *p)
         return *reinterpret_cast<const volatile unsigned long long *>(p);
 }
 
-// Scalars every workgroup keeps in LDS (static shared memory of the kernels).
-struct RoundShared {
-    unsigned long long red[kWavesPerBlock];
-    uint32_t scan[kWavesPerBlock];
-    unsigned long long red2[kWavesPerBlock];
-    uint32_t abort, npick, mcount, pfront, mtotal, msel;
-    float4 lq[kList];                   // merge: listed candidates' coordinates and listed distance
-    uint32_t lkl[kList];                // merge: low halves of their keys (~ original index)
-    // merge: listed candidates with larger keys that would lower each one
-    // (positions below 64, and 64 and up)
-    unsigned long long lset0[kList], lset1[kList];
-    uint32_t lrank[kList];              // merge: rank of each listed candidate in key order
-    uint32_t repw[kWavesPerBlock];      // merge: a wavefront's groups repeat a candidate (equal keys)
-    uint32_t hist[256];    // merge: candidates per key bucket
-    uint32_t my[6 * 8 + 2];  // this workgroup's slot payload (R <= 8)
+// Tags run through 1..65534 with the exchange counter: 0 is a cleared board,
+// 65535 the abort tag, and a slot is rewritten every second exchange, so a
+// stale word never carries the current tag.
+constexpr uint32_t kAbortTag = 0xffffu;
+__device__ __forceinline__ uint32_t tag_of(uint32_t epoch) { return epoch % 65534u + 1u; }
+
+template <Scope S>
+__device__ void publish_abort_tags(unsigned long long *board, int G, int rank, int K)
+{
+    const size_t words = slot_units(K) * kUnit;
+    for (int par = 0; par < 2; ++par)
+        for (size_t w = 0; w < words; ++w)
+            bstore<S>(board + ((size_t)par * G + rank) * words + w, (unsigned long long)kAbortTag << 48);
+}
+
+// Reads one or two units (32 bytes each) past the L1, all loads in flight;
+// each aligned 64-bit word is read whole.  Words come as (low, high) pairs.
+__device__ __forceinline__ void load_unit(const unsigned long long *p, u32x4 &a, u32x4 &b)
+{
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\t"
+                 "global_load_dwordx4 %1, %2, off offset:16 sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(a), "=&v"(b)
+                 : "v"(p)
+                 : "memory");
+}
+__device__ __forceinline__ void load_unit2(const unsigned long long *p, const unsigned long long *q, u32x4 &a,
+                                           u32x4 &b, u32x4 &c, u32x4 &d)
+{
+    asm volatile("global_load_dwordx4 %0, %4, off sc1\n\t"
+                 "global_load_dwordx4 %1, %4, off offset:16 sc1\n\t"
+                 "global_load_dwordx4 %2, %5, off sc1\n\t"
+                 "global_load_dwordx4 %3, %5, off offset:16 sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
+                 : "v"(p), "v"(q)
+                 : "memory");
+}
+
+// Payload of a candidate's unit: x, y, z, distance bits, ~original index and
+// the runner-up's distance bits, 192 bits in four words of 48.
+struct Cand {
+    float x, y, z;
+    uint32_t d, o, u;  // distance bits, ~original index, runner-up distance bits
 };
+__device__ __forceinline__ Cand unpack_cand(const u32x4 &a, const u32x4 &b)
+{
+    // a = words 0, 1 and b = words 2, 3 as (low, high) halves
+    Cand c;
+    c.x = __uint_as_float(a.x);
+    c.y = __uint_as_float((a.y & 0xffffu) | (a.z << 16));
+    c.z = __uint_as_float((a.z >> 16) | (a.w << 16));
+    c.d = b.x;
+    c.o = (b.y & 0xffffu) | (b.z << 16);
+    c.u = (b.z >> 16) | (b.w << 16);
+    return c;
+}
+
+// What every workgroup keeps in LDS besides its tiles and points.
+struct __align__(16) RoundShared {
+    u32x4 rec[kMaxRec][2];              // this workgroup's candidates of the round, packed
+    float4 lq[kList];                   // listed candidates: coordinates, runner-up distance (bits)
+    float4 lb[kList];                   // shifted coordinates and column term of the distance filter
+    float ld[kList], lT[kList];         // distance, minus the row term of the filter
+    unsigned long long lkey[kList];     // keys (0 in the padding of the last block)
+    // conflict rows of the listed candidates (see conflict_pos), then, in the
+    // same memory, the round's picks: coordinates, and shifted ones with the
+    // column term
+    union {
+        unsigned long long adj[kList * kListWords];
+        float4 pk[2 * kList];
+    };
+    unsigned long long pkey[kList];     // the picks' keys
+    uint32_t prank[kList];              // and their ranks (0 between uses)
+    unsigned long long rkey[kMaxRec];   // keys of rec
+    // by parity of the round (cleared for the next one): the largest bound of
+    // this workgroup's wavefronts, and of the whole team
+    unsigned long long gb[2], sx[2];
+    unsigned long long red2[kRWaves];
+    unsigned long long wf[4], wo[4], wscur;  // certification of long lists: masks and bound
+    uint32_t wmet[4];
+    uint32_t scan[kRWaves];
+    uint32_t cnt[kRWaves];              // candidates a wavefront lists
+    uint32_t abort, npick, cut_bin, cut_have;
+    uint32_t hist[256];
+};
+
+// (and the few words the kernels add)
+static_assert(sizeof(RoundShared) + 256 <= kRoundsStatic, "static LDS of the sampler");
+
+// Bit b of word w of a conflict row stands for list position
+// conflict_pos<NW>(w, b), NW words in use (64 NW positions): the layout the
+// matrix cores' result registers give without any exchange between lanes.
+// For more than 128 positions each quarter of a word holds qs row blocks, 3
+// (up to 192 positions; 4 bits of the quarter stay unused) or 4.
+template <int NW>
+__device__ __forceinline__ int conflict_pos(int w, int b, int qs)
+{
+    if constexpr (NW == 1)
+        return 16 * ((b >> 2) & 3) + 4 * (b >> 4) + (b & 3);
+    else if constexpr (NW == 2)
+        return 16 * ((b >> 2) & 7) + 4 * (2 * w + (b >> 5)) + (b & 3);
+    else
+        return ((b >> 2) & 3) < qs ? 16 * ((b >> 4) * qs + ((b >> 2) & 3)) + 4 * w + (b & 3) : kList;
+}
 
 // Per-thread telemetry accumulators.
 struct RoundTele {
     unsigned long long tests = 0, pruned = 0, visited = 0, skipped = 0, updated = 0, resync = 0;
     unsigned long long ph[5] = {0, 0, 0, 0, 0};  // lookahead, exchange, merge, apply, exchange wait
-    // finer clocks: merge list / rank / walk / picks, lookahead copy / steps,
-    // exchange poll / keys; and the merge's list lengths and failures
-    unsigned long long sub[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};  // + apply loop, lookahead selects, apply updates
+    // finer clocks: merge list / conflicts / walk / picks, lookahead first / later
+    // steps, exchange poll / keys, apply, lookahead selects, apply updates
+    unsigned long long sub[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     unsigned long long apairs = 0, arekeys = 0;  // wavefront 0's apply: tile-pick pairs updated, tiles re-keyed
     unsigned long long above = 0, listed = 0, fails = 0;
     unsigned long long rounds = 0;
@@ -236,74 +327,83 @@ struct RoundTele {
 
 // What one team samples: tiles [tb, te) of the index, whose original indices
 // start at point_base (subtracted from the output), m selections from the
-// local start index, outputs at out_idx / out_d2 (already offset).
+// local start index, outputs at out_idx / out_d2 (already offset), and the
+// origin the distance filter shifts to.
 struct CloudJob {
     uint32_t tb, te, point_base;
     int32_t m, start;
     int32_t *out_idx;
     float *out_d2;
+    float ox, oy, oz;
 };
+
+__device__ __forceinline__ float norm2(float x, float y, float z)
+{
+    const float xx = x * x, yy = y * y, zz = z * z;
+    const float s = xx + yy;
+    return s + zz;
+}
+
+// Largest key of the wave and the lowest lane that holds it (all lanes active).
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v, int &at)
+{
+    const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v;
+    const uint32_t mhi = wave_max_u32(hi);
+    unsigned long long tie = ballot64(hi == mhi);
+    if (tie & (tie - 1)) {  // several lanes hold the largest high half
+        const uint32_t mlo = wave_max_u32(hi == mhi ? lo : 0u);
+        tie &= ballot64(lo == mlo);
+    }
+    at = __builtin_ctzll(tie);
+    return ((unsigned long long)mhi << 32) | lane_u32(lo, at);
+}
 
 // Samples one cloud.  Every thread of every workgroup of the team calls it.
 // `epoch` is the team's exchange counter: it only grows, so slots never need
-// clearing between clouds.  Returns false when an exchange failed (abort).
-template <int R, Scope S, bool E, bool T>
-__device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, int rank, int G, unsigned long long *board,
-                             uint32_t &epoch, unsigned char *smem, RoundShared &sh, RoundTele &tl,
-                             bool record_trace, bool clocks)
+// clearing between clouds.  NU: units a thread reads per exchange (the team's
+// G (K + 1) units are dealt to kRBlock threads).  Returns false when an
+// exchange failed (abort).
+template <Scope S, int NU, bool E, bool T>
+__device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int rank, const int G, const int K,
+                             const int steps, unsigned long long *board, uint32_t &epoch, unsigned char *smem,
+                             RoundShared &sh, RoundTele &tl, bool record_trace, bool clocks)
 {
-    constexpr int W = 6 * R + 2;  // words per slot
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     // the wavefront index is uniform: as a scalar it keeps wave-strided loops
     // and their addressing off the exec mask
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint32_t span = job.te - job.tb;
     const int ntl = (span > (uint32_t)rank) ? (int)((span - 1 - rank) / G) + 1 : 0;
-    const bool use_skip = !(a.flags & RFPS_F_NO_POINT_SKIP);
     constexpr bool euclid = E;  // Euclidean distances (RFPS_F_SQRT), a separate instantiation
     // counters, phase clocks and the exchange trace exist only in the
     // instrumented instantiation (T): the default kernels carry none of
     // their code
     const bool tele = T && (a.flags & RFPS_F_TELEMETRY) != 0;
+    const bool count_skip = T && !(a.flags & RFPS_F_NO_POINT_SKIP);
     const bool trace = T && record_trace && tid == 0;
     clocks = T && clocks;
+    const bool solo = G == 1;
+    const int li = lane & (kBlk - 1), lg = lane / kBlk;  // column (or row) and group of a filter block's operands
 
     // ---- LDS layout (the plan checked that it fits) ----
-    unsigned long long *tkey = reinterpret_cast<unsigned long long *>(smem);
-    unsigned long long *tkeyl = tkey + ntl;
-    unsigned long long *obuf = tkeyl + ntl;  // order of a cut list
-    // merge: the keys in sort order, then (same memory) the pick coordinates
-    unsigned long long *skey = obuf + kOrdWords / 2;
-    float *pkx = reinterpret_cast<float *>(skey);
-    float *pky = pkx + kMaxRoundPicks;
-    float *pkz = pky + kMaxRoundPicks;
-    // tile spheres with their pruning thresholds: (centre, threshold), one
-    // 16-byte load per tile test
-    // (aligned by offset from the LDS base, so that the compiler still sees
-    // an LDS pointer)
-    const size_t tsph_off =
-        ((size_t)(reinterpret_cast<unsigned char *>(reinterpret_cast<float *>(skey) + merge_words(G, R)) - smem) + 15) &
-        ~(size_t)15;
-    float4 *tsph = reinterpret_cast<float4 *>(smem + tsph_off);
-    float *tthr = reinterpret_cast<float *>(tsph) + 3;  // with stride 4
-    const int ntlp = (int)padded_tiles((uint32_t)ntl);
-    float *trad = reinterpret_cast<float *>(tsph + ntlp);
-    float *tthrl = trad + ntl;
-    uint32_t *tmeta = reinterpret_cast<uint32_t *>(tthrl + ntl);
-    uint32_t *tbest = tmeta + ntl;
-    uint32_t *tbestl = tbest + ntl;
-    uint32_t *tflag = tbestl + ntl;
-    // the round's slots as published, one W-word image per group: candidate
-    // s of group g is x, y, z, local d2, original index and runner-up d2 at
-    // words 6 s .. 6 s + 5, the bound key's high and low halves follow
-    uint32_t *simg = reinterpret_cast<uint32_t *>(tflag + ntl);
-    // field f of candidate c = g * R + s
-    auto cword = [&](uint32_t c, int f) -> uint32_t { return simg[(c / R) * W + 6 * (c % R) + f]; };
-    uint32_t *sidx = simg + G * W;  // merge order; its first P entries are the round's picks
-    float *px = reinterpret_cast<float *>(sidx + sort_cap(G, R));
+    const int nws = (int)wave_slots((uint32_t)ntl);  // tile slots per wavefront
+    const int nts = nws * kRWaves;
+    float4 *tsph = reinterpret_cast<float4 *>(smem);                              // tile centres
+    unsigned long long *tkey = reinterpret_cast<unsigned long long *>(tsph + nts);
+    float *trow = reinterpret_cast<float *>(tkey + nts);  // the tile's filter: minus its row term
+    float *trad = trow + nts;
+    uint32_t *tmeta = reinterpret_cast<uint32_t *>(trad + nts);  // LDS offset | count << 16
+    float4 *pq = reinterpret_cast<float4 *>(tmeta + nts);        // points: coordinates, ~original index (bits)
 
     // ---- prologue: tile metadata and LDS offsets (block prefix sum) ----
-    const int per = (ntl + kBlock - 1) / kBlock;
+    for (int s = tid; s < nts; s += kRBlock) {
+        tsph[s] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        tkey[s] = 0ull;
+        trow[s] = INFINITY;  // a padding slot passes no filter
+        trad[s] = 0.0f;
+        tmeta[s] = 0u;
+    }
+    const int per = (ntl + kRBlock - 1) / kRBlock;
     const int l0 = tid * per, l1 = min(l0 + per, ntl);
     uint32_t cnt_sum = 0;
     for (int lt = l0; lt < l1; ++lt)
@@ -319,343 +419,494 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, int rank, 
         sh.scan[wave] = incl;
     __syncthreads();
     uint32_t off = incl - cnt_sum, npl = 0;
-    for (int q = 0; q < kWavesPerBlock; ++q) {
+    for (int q = 0; q < kRWaves; ++q) {
         off += q < wave ? sh.scan[q] : 0u;
         npl += sh.scan[q];
     }
+    // tile lt belongs to wavefront lt % kRWaves: tiles of neighbouring voxels
+    // go to different wavefronts as they go to different workgroups
     for (int lt = l0; lt < l1; ++lt) {
         const size_t t = job.tb + rank + (size_t)lt * G;
         const uint32_t c = a.tcnt[t];
-        tmeta[lt] = off | (c << 16);
-        tsph[lt] = make_float4(a.tcx[t], a.tcy[t], a.tcz[t], 0.0f);
-        trad[lt] = a.trad[t];
+        const int s = (lt % kRWaves) * nws + lt / kRWaves;
+        tmeta[s] = off | (c << 16);
+        tsph[s] = make_float4(a.tcx[t], a.tcy[t], a.tcz[t], 0.0f);
+        trad[s] = a.trad[t];
         off += c;
     }
-    // padding spheres: no squared distance is below a threshold of -inf
-    for (int lt = ntl + tid; lt < ntlp; lt += kBlock)
-        tsph[lt] = make_float4(0.0f, 0.0f, 0.0f, -INFINITY);
-    float *py = px + npl;
-    float *pz = py + npl;
-    float *pd = pz + npl;
-    float *pdl = pd + npl;
-    uint32_t *po = reinterpret_cast<uint32_t *>(pdl + npl);
+    float *pd = reinterpret_cast<float *>(pq + npl);
     // the carving must end inside the dynamic LDS the plan sized
-    if (reinterpret_cast<unsigned char *>(po + npl) - smem > (ptrdiff_t)a.lds_budget) {
+    if (reinterpret_cast<unsigned char *>(pd + npl) - smem > (ptrdiff_t)a.lds_budget) {
         if (tid == 0) {
             set_status(&a.hdr->sample_status, RFPS_ERR_INTERNAL);
             // the rest of the team must not wait for this workgroup
-            for (int par = 0; par < 2; ++par)
-                for (int w = 0; w < W; ++w)
-                    bstore<S>(board + ((size_t)par * G + rank) * kMaxSlotWords + w,
-                              (unsigned long long)kAbortEpoch << 32);
+            if (!solo)
+                publish_abort_tags<S>(board, G, rank, K);
         }
         return false;
     }
+    const int wb = wave * nws;  // this wavefront's tile slots: wb .. wb + ntw - 1
+    const int ntw = ntl > wave ? (ntl - 1 - wave) / kRWaves + 1 : 0;
+
+    // Key, threshold and filter row of tile slot s from each lane's distance d
+    // and key low half o of its point (all lanes of the wave must call it).
+    auto rekey = [&](int s, bool valid, float d, uint32_t o) {
+        const float4 c = tsph[s];
+        const float r = trad[s];
+        int at;
+        const unsigned long long kmax = wave_max_key(
+            valid ? ((unsigned long long)__float_as_uint(d) << 32) | o : 0ull, at);
+        const float thr = prune_threshold(r, key_d2(kmax));
+        const float row = thr == 0.0f ? INFINITY
+                                      : -filter_row(thr, norm2(c.x - job.ox, c.y - job.oy, c.z - job.oz));
+        if (lane == 0) {
+            tkey[s] = kmax;
+            trow[s] = row;
+        }
+    };
 
     // Seed and initial update (Sec. 3.3)
     {
         const uint32_t p0 = a.inv[job.point_base + (uint32_t)job.start];
         const float sx = a.xs[p0], sy = a.ys[p0], sz = a.zs[p0];
         __syncthreads();
-        for (int lt = wave; lt < ntl; lt += kWavesPerBlock) {
-            const uint32_t meta = tmeta[lt];
+        for (int i = 0; i < ntw; ++i) {
+            const uint32_t meta = tmeta[wb + i];
             const uint32_t ls = meta & 0xffffu, c = meta >> 16;
-            const uint32_t gs = a.tstart[job.tb + rank + (size_t)lt * G];
+            const uint32_t gs = a.tstart[job.tb + rank + (size_t)(i * kRWaves + wave) * G];
             float dp = 0.0f;
             uint32_t op = 0;
             if ((uint32_t)lane < c) {
-                const uint32_t i = gs + lane, p = ls + lane;
-                const float x = a.xs[i], y = a.ys[i], z = a.zs[i];
-                px[p] = x;
-                py[p] = y;
-                pz[p] = z;
+                const uint32_t q = gs + lane, p = ls + lane;
+                const float x = a.xs[q], y = a.ys[q], z = a.zs[q];
                 const float d0 = sqdist(x, y, z, sx, sy, sz);
                 dp = euclid ? sqrt_class_top(d0) : d0;
-                op = a.orig[i] - job.point_base;
+                op = ~(a.orig[q] - job.point_base);
+                pq[p] = make_float4(x, y, z, __uint_as_float(op));
                 pd[p] = dp;
-                po[p] = op;
             }
-            tile_rekey<4>(lane, lt, ls, c, dp, op, trad, tkey, tbest, tthr);
+            rekey(wb + i, (uint32_t)lane < c, dp, op);
         }
         if (tid == 0)
             sh.abort = 0;
+        if (tid < kList)
+            sh.prank[tid] = 0u;
+        if (tid < 2)
+            sh.gb[tid] = sh.sx[tid] = 0ull;
         __syncthreads();
     }
+
+    // ---- this thread's units of every exchange ----
+    const int units = (int)slot_units(K);
+    const int total = solo ? kRWaves * steps : G * units;
+    uint32_t upos[NU];            // word offset of its units on the board
+    bool uin[NU], ubound[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        const int e = tid + u * kRBlock;
+        const int g = e / units, s = e - g * units;
+        uin[u] = e < total;
+        ubound[u] = !solo && s == K;
+        upos[u] = uin[u] ? (uint32_t)(e * kUnit) : 0u;
+    }
+    const size_t par_words = (size_t)G * units * kUnit;
+    const unsigned long long below = lane ? (~0ull >> (kWave - lane)) : 0ull;
 
     unsigned long long t_mark = 0;
     int j = 1;
     uint32_t round = 0;
+    int j_out = 1, n_out = 0, p_out = 0;  // the last round's outputs, written during the next exchange (rank 0)
+
+    // Outputs of the last round (rank 0): a pick's position is its rank in key
+    // order among the picks, of which only the first n_out count.  Every
+    // wavefront counts the larger keys among its share of the picks, for all
+    // of them; after a barrier the threads of write_out store the results.
+    auto rank_out = [&]() {
+        for (int i0 = 0; i0 < p_out; i0 += kWave) {
+            const int i = i0 + lane;
+            const unsigned long long ki = sh.pkey[i < p_out ? i : 0];
+            uint32_t r = 0;
+            // (positions past the picks hold older keys: masked)
+            for (int q = wave; q < p_out; q += 4 * kRWaves)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int qv = q + v * kRWaves;
+                    r += (sh.pkey[qv & (kList - 1)] > ki && qv < p_out) ? 1u : 0u;
+                }
+            if (i < p_out && r)
+                atomicAdd(&sh.prank[i], r);
+        }
+    };
+    auto write_out = [&](int t) {
+        for (int i = t; i < p_out; i += kWave) {
+            const int r = (int)sh.prank[i];
+            sh.prank[i] = 0u;
+            if (r < n_out) {
+                const unsigned long long k = sh.pkey[i];
+                job.out_idx[j_out + r] = (int32_t)key_orig(k);
+                if (job.out_d2)
+                    job.out_d2[j_out + r] = key_d2(k);
+            }
+        }
+    };
+
     while (j < job.m) {
         ++round;
         ++epoch;
         if (clocks)
             t_mark = wall_clock64();
-        // =============== L: local lookahead on a private copy ===============
-        // One wavefront runs the lookahead: the per-step reductions stay
-        // inside it and its LDS operations complete in order, so the steps
-        // need no workgroup barrier.  Lanes take tiles for the arg max and the
-        // sphere tests; a tile that the test keeps is updated by all lanes.
-        // The first step reads the true tile state, while the other
-        // wavefronts copy it to the private state the later steps use.
+        // =============== L: lookahead of every wavefront on its own tiles ===============
+        // A candidate is the largest key of the wavefront's tiles; it is then
+        // applied to its own tile only, on a copy in registers (other tiles
+        // keep their keys, which bound their points from above), and the next
+        // step takes the largest key again.  A tile whose key was lowered by
+        // its own candidate holds the lowered key in LDS until the lookahead
+        // ends, when the true key is put back.
         {
-            unsigned long long lk = 0, lk2 = 0;  // the lane's two largest tile keys
-            uint32_t lt_best = 0;
-            float lx = 0.0f, ly = 0.0f, lz = 0.0f;  // the last candidate
-            bool more = false;                     // the lookahead goes on after step 0
-            // candidate s from the lane maxima (lk, lk2, lt_best): its
-            // coordinates, local key, runner-up and, for the last, the bound;
-            // false for a workgroup without points
-            auto select = [&](int s, bool first) -> bool {
-                if (clocks)
-                    tl.sub[9] -= wall_clock64();
-                const unsigned long long bk = wave_max_u64(lk);
-                if (bk == 0) {
-                    // no points: bound 0, no candidates (every point's key is
-                    // above 0, so this is step 0)
-                    if (lane == 0)
-                        for (int w = 0; w < W; ++w)
-                            sh.my[w] = 0;
-                    if (clocks)
-                        tl.sub[9] += wall_clock64();
-                    return false;
+            const int rb = wave * steps;
+            unsigned long long bound = 0;
+            // candidate s: lane p of the loaded tile (coordinates q, distance
+            // bits db), with the largest distance of its wavefront's others u
+            auto record = [&](int s, bool own, const float4 &q, uint32_t db, uint32_t u) {
+                if (own) {
+                    const uint32_t x = __float_as_uint(q.x), y = __float_as_uint(q.y), z = __float_as_uint(q.z),
+                                   o = __float_as_uint(q.w);
+                    sh.rec[rb + s][0] = u32x4{x, y & 0xffffu, (y >> 16) | (z << 16), z >> 16};
+                    sh.rec[rb + s][1] = u32x4{db, o & 0xffffu, (o >> 16) | (u << 16), u >> 16};
+                    sh.rkey[rb + s] = ((unsigned long long)db << 32) | o;
                 }
-                const unsigned long long hit = ballot64(lk == bk);
-                const uint32_t bt = (uint32_t)__builtin_amdgcn_readlane((int)lt_best, __ffsll((long long)hit) - 1);
-                const uint32_t p = first ? tbest[bt] : tbestl[bt];
-                lx = px[p];
-                ly = py[p];
-                lz = pz[p];
-                // runner-up: the largest local key of any other point of this
-                // workgroup (other tiles, and the rest of the best tile); it
-                // bounds them if this candidate is not taken at its turn.  One
-                // reduction takes both parts.
-                unsigned long long ru;
-                {
-                    const uint32_t meta = tmeta[bt];
-                    const uint32_t ls = meta & 0xffffu, cnt = meta >> 16;
-                    const bool valid = (uint32_t)lane < cnt;
-                    const uint32_t pp = ls + (valid ? lane : 0);
-                    const float dpl = pdl[pp], dpt = pd[pp];
-                    const float dl = (!first && tflag[bt]) ? dpl : dpt;
-                    const unsigned long long k = valid ? pack_key(dl, po[pp]) : 0ull;
-                    ru = wave_max_u64(umax64(lk == bk ? lk2 : lk, k == bk ? 0ull : k));
-                }
-                if (lane == 0) {
-                    sh.my[6 * s + 0] = __float_as_uint(lx);
-                    sh.my[6 * s + 1] = __float_as_uint(ly);
-                    sh.my[6 * s + 2] = __float_as_uint(lz);
-                    sh.my[6 * s + 3] = (uint32_t)(bk >> 32);  // local d2
-                    sh.my[6 * s + 4] = po[p];
-                    sh.my[6 * s + 5] = (uint32_t)(ru >> 32);  // runner-up d2
-                    if (s == R - 1) {
-                        // the bound: the runner-up, or l_R itself at distance
-                        // 0 (l_R is never applied to the private copy)
-                        const unsigned long long b = umax64(ru, pack_key(0.0f, po[p]));
-                        sh.my[6 * R] = (uint32_t)(b >> 32);
-                        sh.my[6 * R + 1] = (uint32_t)b;
-                    }
-                }
-                if (clocks)
-                    tl.sub[9] += wall_clock64();
-                return true;
             };
-            if (wave == 0) {
-                // same trip count on every lane, loads clamped: no branches
-                for (int lt0 = 0; lt0 < ntl; lt0 += kWave) {
-                    const int lt = lt0 + lane;
-                    const unsigned long long kr = tkey[lt < ntl ? lt : 0];
-                    const unsigned long long k = lt < ntl ? kr : 0ull;
-                    const bool top = k > lk;
-                    lk2 = top ? lk : umax64(lk2, k);
-                    lt_best = top ? (uint32_t)lt : lt_best;
-                    lk = top ? k : lk;
+            // One step on a loaded tile (points q, distances d) whose largest
+            // key is bk: lane p of it, the largest distance of the others, and
+            // the tile's key once p is applied to it (d follows).
+            auto step = [&](const float4 &q, float &d, bool valid, unsigned long long bk, int &p, uint32_t &rest,
+                            unsigned long long &nk) {
+                // key low halves are unique to their points
+                const uint32_t o = __float_as_uint(q.w);
+                p = __builtin_ctzll(ballot64(o == (uint32_t)bk) & ballot64(valid));
+                const float cx = lane_f32(q.x, p), cy = lane_f32(q.y, p), cz = lane_f32(q.z, p);
+                const uint32_t db = valid && lane != p ? __float_as_uint(d) : 0u;
+                d = min_dist(d, sqdist(q.x, q.y, q.z, cx, cy, cz), euclid);
+                const uint32_t nb = valid ? __float_as_uint(d) : 0u;
+                rest = wave_max_u32(db);
+                const uint32_t mh = wave_max_u32(nb);
+                unsigned long long tie = ballot64(nb == mh) & ballot64(valid);
+                if (tie & (tie - 1)) {
+                    const uint32_t ml = wave_max_u32(((tie >> lane) & 1ull) ? o : 0u);
+                    tie &= ballot64(o == ml);
                 }
-                more = select(0, true) && R > 1;
-            } else {
-                for (int lt = tid - kWave; lt < ntl; lt += kBlock - kWave) {
-                    tkeyl[lt] = tkey[lt];
-                    tthrl[lt] = tsph[lt].w;
-                    tbestl[lt] = tbest[lt];
-                    tflag[lt] = 0;
-                }
-            }
-            __syncthreads();
-            if (clocks) {
-                const unsigned long long t = wall_clock64();
-                tl.sub[4] += t - t_mark;
-                tl.sub[5] -= t;  // the steps end at the phase mark below
-            }
-            if (wave == 0 && more) {
-                for (int s = 1; s < R; ++s) {
-                    // local update with l_{s-1} (pruned against the local thresholds)
-                    for (int lt0 = 0; lt0 < ntl; lt0 += kWave) {
-                        const int lt = lt0 + lane;
-                        const int li = lt < ntl ? lt : 0;
-                        unsigned long long m =
-                            ballot64(!(sqdist(tsph[li].x, tsph[li].y, tsph[li].z, lx, ly, lz) >= tthrl[li])) &
-                            ballot64(lt < ntl);
-                        while (m) {
-                            const int t = lt0 + (__ffsll((long long)m) - 1);
-                            m &= m - 1;
-                            const uint32_t meta = tmeta[t];
-                            const uint32_t ls = meta & 0xffffu, cnt = meta >> 16;
-                            const bool valid = (uint32_t)lane < cnt;
-                            const uint32_t pp = ls + (valid ? lane : 0);
-                            // the private copy starts from the true state the
-                            // first time a step of this round touches the tile
-                            const float dpl = pdl[pp], dpt = pd[pp];
-                            float d = tflag[t] ? dpl : dpt;
-                            bool upd = false;
-                            if (valid) {
-                                const float dx = px[pp] - lx, dy = py[pp] - ly, dz = pz[pp] - lz;
-                                const float xx = dx * dx, yy = dy * dy, zz = dz * dz;
-                                const bool skip = use_skip && (xx >= d || yy >= d || zz >= d);
-                                const float s2 = xx + yy;
-                                float tt = s2 + zz;
-                                if (euclid && !skip && tt < d)
-                                    tt = sqrt_class_top(tt);
-                                upd = !skip && tt < d;
-                                d = upd ? tt : d;
-                                pdl[pp] = d;
+                nk = ((unsigned long long)mh << 32) | lane_u32(o, __builtin_ctzll(tie));
+            };
+            auto load = [&](uint32_t meta, float4 &q, float &d, bool &valid) {
+                const uint32_t ls = meta & 0xffffu, cnt = meta >> 16;
+                valid = (uint32_t)lane < cnt;
+                const uint32_t pp = ls + (valid ? lane : 0);
+                q = pq[pp];
+                d = pd[pp];
+            };
+            if (ntw <= kWave) {
+                // The usual case, a tile per lane: the keys the lookahead
+                // lowers stay in registers.
+                unsigned long long k1 = lane < ntw ? tkey[wb + lane] : 0ull, oth = 0;
+                const uint32_t m1 = lane < ntw ? tmeta[wb + lane] : 0u;
+                int h, ho = 0;
+                unsigned long long bk = wave_max_key(k1, h);
+                if (bk == 0) {
+                    // a wavefront without points: no candidates, bound 0
+                    if (lane < steps) {
+                        sh.rkey[rb + lane] = 0ull;
+                        sh.rec[rb + lane][0] = u32x4{0u, 0u, 0u, 0u};
+                        sh.rec[rb + lane][1] = u32x4{0u, 0u, 0u, 0u};
+                    }
+                } else {
+                    float4 q;
+                    float d;
+                    bool valid;
+                    load(lane_u32(m1, h), q, d, valid);
+                    oth = wave_max_key(lane == h ? 0ull : k1, ho);
+                    float4 qn;  // the tile that comes next if another one does
+                    float dn;
+                    bool vn;
+                    load(lane_u32(m1, ho), qn, dn, vn);
+                    int ctile = -1;  // lane s: the tile of candidate s
+                    for (int s = 0;;) {
+                        int p;
+                        uint32_t rest;
+                        unsigned long long nk;
+                        const uint32_t db = __float_as_uint(d);
+                        step(q, d, valid, bk, p, rest, nk);
+                        record(s, lane == p, q, db, max(rest, (uint32_t)(oth >> 32)));
+                        bound = umax64(nk, oth);
+                        if (lane == s)
+                            ctile = h;
+                        if (++s == steps)
+                            break;
+                        bk = bound;
+                        if (nk < oth) {
+                            // the next candidate comes from another tile
+                            if (lane == h)
+                                k1 = nk;
+                            h = ho;
+                            q = qn;
+                            d = dn;
+                            valid = vn;
+                            oth = wave_max_key(lane == h ? 0ull : k1, ho);
+                            if (s + 1 < steps)
+                                load(lane_u32(m1, ho), qn, dn, vn);
+                            unsigned long long mine = ballot64(ctile == h);
+                            while (mine) {
+                                const int c = __builtin_ctzll(mine);
+                                mine &= mine - 1;
+                                const Cand l = unpack_cand(sh.rec[rb + c][0], sh.rec[rb + c][1]);
+                                d = min_dist(d, sqdist(q.x, q.y, q.z, l.x, l.y, l.z), euclid);
                             }
-                            if (lane == 0)
-                                tflag[t] = 1;
-                            if (__ballot(upd))
-                                tile_rekey<1>(lane, t, ls, cnt, d, po[pp], trad, tkeyl, tbestl, tthrl);
                         }
                     }
-                    // arg max over the private tile keys (key and tile travel together)
-                    lk = 0;
-                    lk2 = 0;
-                    lt_best = 0;
-                    for (int lt0 = 0; lt0 < ntl; lt0 += kWave) {
-                        const int lt = lt0 + lane;
-                        const unsigned long long kr = tkeyl[lt < ntl ? lt : 0];
-                        const unsigned long long k = lt < ntl ? kr : 0ull;
-                        const bool top = k > lk;
-                        lk2 = top ? lk : umax64(lk2, k);
-                        lt_best = top ? (uint32_t)lt : lt_best;
-                        lk = top ? k : lk;
+                }
+            } else {
+                unsigned long long bk, oth;  // the largest key, and the largest of the other tiles
+                int bt;                      // the tile of bk
+                uint32_t meta;               // and its points
+                auto scan = [&]() {
+                    unsigned long long k1 = 0, k2 = 0;
+                    int i1 = 0;
+                    uint32_t m1 = 0;
+                    for (int i = lane; i < ntw; i += kWave) {
+                        const unsigned long long k = tkey[wb + i];
+                        const uint32_t m = tmeta[wb + i];
+                        const bool top = k > k1;
+                        k2 = top ? k1 : umax64(k, k2);
+                        k1 = top ? k : k1;
+                        i1 = top ? i : i1;
+                        m1 = top ? m : m1;
                     }
-                    select(s, false);
+                    int hl, ol;
+                    bk = wave_max_key(k1, hl);
+                    bt = __builtin_amdgcn_readlane(i1, hl);
+                    meta = lane_u32(m1, hl);
+                    oth = wave_max_key(lane == hl ? k2 : k1, ol);
+                };
+                scan();
+                if (bk == 0) {
+                    // a wavefront without points: no candidates, bound 0
+                    if (lane < steps) {
+                        sh.rkey[rb + lane] = 0ull;
+                        sh.rec[rb + lane][0] = u32x4{0u, 0u, 0u, 0u};
+                        sh.rec[rb + lane][1] = u32x4{0u, 0u, 0u, 0u};
+                    }
+                } else {
+                    float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    float d = 0.0f;
+                    bool valid = false;
+                    int cur = -1;
+                    int ctile = -1;               // lane q: the tile of candidate q
+                    int svt = -1, nsv = 0;        // lane q: the q-th tile whose key was lowered,
+                    unsigned long long svk = 0;   // and its true key
+                    unsigned long long curk = 0;  // key of the loaded tile when it was taken
+                    for (int s = 0;;) {
+                        if (cur != bt) {
+                            cur = bt;
+                            curk = bk;
+                            load(meta, q, d, valid);
+                            unsigned long long mine = ballot64(ctile == bt);
+                            while (mine) {
+                                const int c = __builtin_ctzll(mine);
+                                mine &= mine - 1;
+                                const Cand l = unpack_cand(sh.rec[rb + c][0], sh.rec[rb + c][1]);
+                                d = min_dist(d, sqdist(q.x, q.y, q.z, l.x, l.y, l.z), euclid);
+                            }
+                        }
+                        int p;
+                        uint32_t rest;
+                        unsigned long long nk;
+                        const uint32_t db = __float_as_uint(d);
+                        step(q, d, valid, bk, p, rest, nk);
+                        record(s, lane == p, q, db, max(rest, (uint32_t)(oth >> 32)));
+                        if (lane == s)
+                            ctile = bt;
+                        bound = umax64(nk, oth);
+                        if (++s == steps)
+                            break;
+                        if (nk >= oth) {
+                            bk = nk;
+                        } else {
+                            if (!ballot64(svt == cur)) {
+                                if (lane == nsv) {
+                                    svt = cur;
+                                    svk = curk;
+                                }
+                                ++nsv;
+                            }
+                            if (lane == 0)
+                                tkey[wb + cur] = nk;
+                            scan();
+                        }
+                    }
+                    if (lane < nsv)
+                        tkey[wb + svt] = svk;
                 }
             }
+            if (lane == 0)
+                atomicMax(&sh.gb[round & 1u], bound);
         }
         __syncthreads();
+        if (tid == 0)
+            sh.gb[(round + 1u) & 1u] = 0ull;  // last read before this barrier
         if (clocks) {
             const unsigned long long t = wall_clock64();
             tl.ph[0] += t - t_mark;
-            tl.sub[5] += t;
             t_mark = t;
         }
 
         // =============== X: publish and read every slot ===============
-        // Every word carries the round's epoch.  The readers go over all words
-        // of all slots word-major (neighbouring threads, neighbouring words)
-        // until each word shows the epoch, keeping all of a thread's missing
-        // words in flight in every pass: reading the slots that are ready
-        // overlaps waiting for the rest, and words of one slot need not
-        // become visible in the order they were written.
-        unsigned long long t_pub = trace ? wall_clock64() : 0ull;
-        if (wave == 0) {
-            unsigned long long *slot = board + ((size_t)(epoch & 1u) * G + rank) * kMaxSlotWords;
-            for (int w = lane; w < W; w += kWave)
-                bstore<S>(slot + w, ((unsigned long long)epoch << 32) | sh.my[w]);
-        }
-        {
-            const int total = G * W;
-            const unsigned long long *sbase = board + (size_t)(epoch & 1u) * G * kMaxSlotWords;
-            // Word r of this thread, e = tid + kBlock * r, is word e % W of
-            // group e / W's slot; it goes to word e of the slot image, so the
-            // lanes of a wavefront store to neighbouring LDS words.
-            unsigned long long pend = 0;
-            uint32_t off[W];
+        // A workgroup publishes its K largest candidates and a bound on every
+        // other point's key: the largest of its wavefronts' bounds and of its
+        // next candidate.  Every wavefront finds the ranks of its own
+        // candidates and publishes those below K at their rank; the one that
+        // owns the next candidate publishes the bound.  Every thread then
+        // reads its own units of the whole team's slots into registers.
+        const unsigned long long t_pub = trace ? wall_clock64() : 0ull;
+        Cand cd[NU];
+        unsigned long long ck[NU];  // candidate keys (0: none)
+        unsigned long long smax;    // S*, the largest bound of the team
+        float4 cb[NU];              // candidates' shifted coordinates and column term
+        float ct[NU];               // and minus their row term
+        auto prepare = [&]() {
 #pragma unroll
-            for (int r = 0; r < W; ++r) {
-                const int e = tid + kBlock * r;
-                const bool in = e < total;
-                pend |= in ? (1ull << r) : 0ull;
-                off[r] = in ? (uint32_t)((e / W) * kMaxSlotWords + e % W) : 0u;
+            for (int u = 0; u < NU; ++u) {
+                const Cand &c = cd[u];
+                float sx = c.x - job.ox, sy = c.y - job.oy, sz = c.z - job.oz;
+                const float n2 = norm2(sx, sy, sz);
+                if (!(n2 <= 1e36f))
+                    sx = sy = sz = 0.0f;  // kept whatever the other point: no product may be NaN
+                cb[u] = make_float4(sx, sy, sz, filter_col(n2));
+                ct[u] = -filter_row(__uint_as_float(c.d), n2);
             }
-            bool ab = false;
-            constexpr int kFast = W < 32 ? W : 32;
-            unsigned long long t_first = 0;
-            for (uint32_t spin = 0; pend && !ab && spin < kSpinLimit; ++spin) {
-                if (clocks && spin == 1)
-                    t_first = wall_clock64();  // the passes after the first are waiting
-                binvalidate<S>();
-#pragma unroll
-                for (int r0 = 0; r0 < W; r0 += kFast) {
-                    unsigned long long x[kFast];
-#pragma unroll
-                    for (int q = 0; q < kFast; ++q) {
-                        const int r = r0 + q;
-                        x[q] = (r < W && ((pend >> r) & 1ull)) ? bload<S>(sbase + off[r]) : 0ull;
-                    }
-                    // a word is taken once it carries the round's epoch (a
-                    // word not read this pass is 0, and epochs start at 1)
-#pragma unroll
-                    for (int q = 0; q < kFast; ++q) {
-                        const int r = r0 + q;
-                        if (r >= W)
-                            break;
-                        const uint32_t ep = (uint32_t)(x[q] >> 32);
-                        ab |= ep == kAbortEpoch;
-                        const bool ok = ep == epoch;
-                        if (ok)
-                            simg[tid + kBlock * r] = (uint32_t)x[q];
-                        pend &= ok ? ~(1ull << r) : ~0ull;
+        };
+        bool solo_out = false;      // outputs of the last round wait for a barrier
+        if (!solo) {
+            const uint32_t tag = tag_of(epoch);
+            {
+                const int nr = kRWaves * steps, c0 = wave * steps;
+                const unsigned long long kq = lane < nr ? sh.rkey[lane] : 0ull;
+                const unsigned long long gb = sh.gb[round & 1u];
+                unsigned long long *slot = board + (epoch & 1u) * par_words + (size_t)rank * (units * kUnit);
+                const unsigned long long tag64 = (unsigned long long)tag << 48;
+                for (int s = 0; s < steps; ++s) {
+                    const int c = c0 + s;
+                    const unsigned long long w =
+                        reinterpret_cast<const unsigned long long *>(sh.rec[c])[lane & (kUnit - 1)];
+                    const unsigned long long kc = lane_u64(kq, c);
+                    // equal keys (empty wavefronts, or one point repeated): by position
+                    const int r = __popcll(ballot64(kq > kc) | (ballot64(kq == kc) & ((1ull << c) - 1ull)));
+                    if (r < K && lane < kUnit)
+                        bstore<S>(slot + r * kUnit + lane, tag64 | w);
+                    if ((r == K || (nr == K && c == 0)) && lane < kUnit) {
+                        const unsigned long long b = umax64(gb, r == K ? kc : 0ull);
+                        bstore<S>(slot + K * kUnit + lane, tag64 | (lane == 0 ? b >> 32 : b & 0xffffffffull));
                     }
                 }
             }
-            if (pend)
+            if (rank == 0 && n_out)
+                rank_out();
+            const unsigned long long *sbase = board + (epoch & 1u) * par_words;
+            unsigned long long b = 0;
+            unsigned long long t_first = 0;
+            bool lost = false;
+            const uint32_t tagw = tag << 16;
+            auto fresh = [&](const u32x4 &x, const u32x4 &y) {
+                return ((((x.y ^ tagw) | (x.w ^ tagw)) | ((y.y ^ tagw) | (y.w ^ tagw))) >> 16) == 0u;
+            };
+            auto aborted = [&](const u32x4 &x) { return (x.y >> 16) == kAbortTag; };
+            auto take = [&](int u, const u32x4 &x, const u32x4 &y) {
+                cd[u] = unpack_cand(x, y);
+                ck[u] = ubound[u] || !uin[u] ? 0ull : ((unsigned long long)cd[u].d << 32) | cd[u].o;
+                if (ubound[u])
+                    b = umax64(b, ((unsigned long long)x.x << 32) | x.z);
+            };
+            if constexpr (NU == 2) {
+                // both units' loads in flight together
+                bool p0 = uin[0], p1 = uin[1];
+                ck[0] = ck[1] = 0ull;
+                for (uint32_t spin = 0; p0 || p1; ++spin) {
+                    if (clocks && spin == 1 && !t_first)
+                        t_first = wall_clock64();  // the passes after the first are waiting
+                    u32x4 x0, y0, x1, y1;
+                    load_unit2(sbase + upos[0], sbase + upos[1], x0, y0, x1, y1);
+                    if (p0 && fresh(x0, y0)) {
+                        take(0, x0, y0);
+                        p0 = false;
+                    }
+                    if (p1 && fresh(x1, y1)) {
+                        take(1, x1, y1);
+                        p1 = false;
+                    }
+                    if ((p0 && aborted(x0)) || (p1 && aborted(x1)) || spin >= kSpinLimit) {
+                        lost = true;
+                        break;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    ck[u] = 0ull;
+                    bool p0 = uin[u];
+                    for (uint32_t spin = 0; p0; ++spin) {
+                        if (clocks && spin == 1 && !t_first)
+                            t_first = wall_clock64();
+                        u32x4 x0, y0;
+                        load_unit(sbase + upos[u], x0, y0);
+                        if (fresh(x0, y0)) {
+                            take(u, x0, y0);
+                            p0 = false;
+                        } else if (aborted(x0) || spin >= kSpinLimit) {
+                            lost = true;
+                            break;
+                        }
+                    }
+                }
+            }
+            if (lost)
                 sh.abort = 1;
+            // what the list needs of this thread's candidates, while the
+            // wavefront's bound is reduced
+            prepare();
+            int at;
+            b = wave_max_key(b, at);
+            if (lane == 0 && b)
+                atomicMax(&sh.sx[round & 1u], b);
             if (clocks && t_first)
                 tl.ph[4] += wall_clock64() - t_first;
             if (clocks)
                 tl.sub[6] += wall_clock64() - t_mark;
-        }
-        __syncthreads();
-        // Candidate keys, in registers: thread g (< G <= kBlock) holds group
-        // g's bound and candidate keys; a workgroup without tiles publishes the
-        // bound 0 and no candidates.  The merge's S* (largest bound) and
-        // largest head key are reduced on the way, and repeats of one point
-        // (equal keys, consecutive in a group) are flagged per wavefront.
-        unsigned long long gkey[R];
-        unsigned long long gbound = 0;
-        if (!sh.abort) {
-            const int g = tid < G ? tid : 0;
-            const uint32_t *gi = simg + g * W;
-            gbound = tid < G ? ((unsigned long long)gi[6 * R] << 32) | gi[6 * R + 1] : 0ull;
-            const bool empty = gbound == 0ull;
-            bool repeat = false;
+            __syncthreads();
+            if (sh.abort) {
+                if (tid == 0) {
+                    set_status(&a.hdr->sample_status, RFPS_ERR_TIMEOUT);
+                    publish_abort_tags<S>(board, G, rank, K);
+                }
+                return false;
+            }
+            if (rank == 0 && n_out && wave == kRWaves - 1)
+                write_out(lane);
+            smax = sh.sx[round & 1u];
+            if (tid == 0)
+                sh.sx[(round + 1u) & 1u] = 0ull;  // last read in the round before
+        } else {
+            if (n_out)
+                rank_out();
 #pragma unroll
-            for (int s2 = 0; s2 < R; ++s2) {
-                gkey[s2] = empty ? 0ull : ((unsigned long long)gi[6 * s2 + 3] << 32) | (~gi[6 * s2 + 4]);
-                if (s2 > 0)
-                    repeat = repeat || (gkey[s2] == gkey[s2 - 1] && gkey[s2] != 0ull);
+            for (int u = 0; u < NU; ++u) {
+                ck[u] = 0ull;
+                if (uin[u]) {
+                    const int e = tid + u * kRBlock;
+                    cd[u] = unpack_cand(sh.rec[e][0], sh.rec[e][1]);
+                    ck[u] = sh.rkey[e];
+                }
             }
-            const unsigned long long sk = wave_max_u64(gbound);
-            const bool anyrep = ballot64(repeat) != 0ull;
-            if (lane == 0) {
-                sh.red[wave] = sk;
-                sh.repw[wave] = anyrep ? 1u : 0u;
-            }
-            if (tid == 0) {
-                sh.mcount = 0;
-                sh.pfront = 0;
-            }
-        }
-        __syncthreads();
-        if (sh.abort) {
-            if (tid == 0) {
-                set_status(&a.hdr->sample_status, RFPS_ERR_TIMEOUT);
-                for (int par = 0; par < 2; ++par)
-                    for (int w = 0; w < W; ++w)
-                        bstore<S>(board + ((size_t)par * G + rank) * kMaxSlotWords + w,
-                                  (unsigned long long)kAbortEpoch << 32);
-            }
-            return false;
+            prepare();
+            smax = sh.gb[round & 1u];
+            solo_out = n_out != 0;
         }
         if (clocks) {
             const unsigned long long t = wall_clock64();
@@ -665,513 +916,503 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, int rank, 
         }
 
         // =============== M: certified merge (whole workgroup) ===============
-        // Candidates are taken in descending order of local key; each one is
-        // certified when its true distance (its local distance lowered by
-        // every earlier pick of the round) still equals its local distance.
-        // Taking the group with the largest bound B_g at every step visits
-        // exactly this order until the largest published bound S* = max_g
-        // k_{R+1} is reached, where it stops.  So the candidates above S* are
-        // listed (at most kList: a longer list is cut at a key boundary, and
-        // the bound rises to the largest key left out), and for every listed
-        // candidate its rank in key order and the set of listed candidates
-        // that would lower it (state value of their distance below its listed
-        // distance) are computed once, by all wavefronts.  Certification is
-        // then a walk over the order in one wavefront: the first candidate
-        // with a member of its set at an earlier position fails.  A failed
-        // candidate is re-listed (below) and the walk resumes; distances
-        // between candidates do not change, so only the re-listed candidate's
-        // own set is computed again, against its new key.
-        {
-            unsigned long long smax = 0;
+        // The candidates above S*, in the order of the units (the same in
+        // every workgroup).  A candidate at distance 0 is never listed: when
+        // nothing is left above distance 0, the loop ends below.  Positions
+        // past kList are counted only.
+        uint32_t L;
+        auto list_above = [&](unsigned long long lim) {
+            uint32_t mine = 0;
+            unsigned long long km[NU];
 #pragma unroll
-            for (int q = 0; q < kWavesPerBlock; ++q)
-                smax = umax64(smax, sh.red[q]);
-            // Keys of different points differ, so only a group's own repeats
-            // can tie: once every point of a group has local distance 0, its
-            // lookahead returns its lowest index again and again, and its
-            // bound equals those candidates.  A group's candidates precede its
-            // own bound, so a candidate equal to S* is taken when S* is the
-            // bound of its own group.  The candidates above S* are compacted
-            // (in any order) from the registers, with what the ranking pass
-            // reads staged for the first kList of them.
-            const unsigned long long below = lane ? (~0ull >> (kWave - lane)) : 0ull;
-            // what the ranking pass reads about listed candidate pos (candidate c, key k)
-            auto stage = [&](uint32_t pos, uint32_t c, unsigned long long k) {
-                sh.lq[pos] = make_float4(__uint_as_float(cword(c, 0)), __uint_as_float(cword(c, 1)),
-                                         __uint_as_float(cword(c, 2)), __uint_as_float((uint32_t)(k >> 32)));
-                sh.lkl[pos] = (uint32_t)k;
-                sh.lset1[pos] = 0ull;
-                sh.lrank[pos] = 0u;
-            };
+            for (int u = 0; u < NU; ++u) {
+                km[u] = ballot64(ck[u] > lim) & ballot64((ck[u] >> 32) != 0ull);
+                mine += (uint32_t)__popcll(km[u]);
+            }
+            if (lane == 0)
+                sh.cnt[wave] = mine;
+            __syncthreads();
+            uint32_t base = 0;
+            L = 0;
 #pragma unroll
-            for (int s2 = 0; s2 < R; ++s2) {
-                const unsigned long long k = gkey[s2];
-                const bool keep = tid < G && (k > smax || (k == smax && gbound == smax));
-                const unsigned long long km = ballot64(keep);
-                uint32_t base = 0;
-                if (lane == 0 && km)
-                    base = atomicAdd(&sh.mcount, (uint32_t)__popcll(km));
-                base = (uint32_t)__shfl((int)base, 0, kWave);
-                if (keep) {
-                    const uint32_t pos = base + (uint32_t)__popcll(km & below);
-                    const uint32_t c = (uint32_t)(tid * R + s2);
-                    skey[pos] = k;
-                    sidx[pos] = c;
-                    if (pos < (uint32_t)kList)
-                        stage(pos, c, k);
+            for (int q = 0; q < kRWaves; ++q) {
+                const uint32_t c = sh.cnt[q];
+                base += q < wave ? c : 0u;
+                L += c;
+            }
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const uint32_t pos = base + (uint32_t)__popcll(km[u] & below);
+                if (((km[u] >> lane) & 1ull) && pos < (uint32_t)kList) {
+                    sh.lq[pos] = make_float4(cd[u].x, cd[u].y, cd[u].z, __uint_as_float(cd[u].u));
+                    sh.lb[pos] = cb[u];
+                    sh.ld[pos] = __uint_as_float(cd[u].d);
+                    sh.lT[pos] = ct[u];
+                    sh.lkey[pos] = ck[u];
                 }
+                base += (uint32_t)__popcll(km[u]);
             }
             __syncthreads();
-            const uint32_t L = sh.mcount;
-            const bool rep = (sh.repw[0] | sh.repw[1] | sh.repw[2] | sh.repw[3]) != 0u;
-            uint32_t *ord = reinterpret_cast<uint32_t *>(obuf);
-            // scur: every listed key is above it (or equals S*, see taken) and
-            // every point left out of the list has its true key at most it
-            unsigned long long scur = smax;
-            uint32_t W = L;  // the list: skey / sidx [0, W)
-            if (L > (uint32_t)kList) {
-                // a histogram of the keys' high halves (distance bits, between
-                // S* and the largest listed key) in 256 buckets
-                unsigned long long hm = 0;
-                for (uint32_t i = tid; i < L; i += kBlock)
-                    hm = umax64(hm, skey[i]);
-                hm = wave_max_u64(hm);
-                if (lane == 0)
-                    sh.red2[wave] = hm;
-                sh.hist[tid] = 0;
-                __syncthreads();
-                unsigned long long hmax = 0;
+        };
+        list_above(smax);
+        if (solo_out && wave == kRWaves - 1)
+            write_out(lane);
+        // scur: every listed key is above it, and every point left out of the
+        // list has its true key at most it
+        unsigned long long scur = smax;
+        if (L == 0) {
+            // The largest key is never a bound unless its distance is 0 (keys
+            // of different points differ, and a candidate's own key falls to
+            // distance 0 once it is applied), so every distance is 0: the
+            // lowest index is selected for good (Sec. 3.1).
+            unsigned long long mk = 0;
 #pragma unroll
-                for (int q = 0; q < kWavesPerBlock; ++q)
-                    hmax = umax64(hmax, sh.red2[q]);
-                const uint32_t hlo = (uint32_t)(smax >> 32);
-                const uint32_t span = (uint32_t)(hmax >> 32) - hlo;
-                const int bits = span ? 32 - __clz((int)span) : 0;
-                const int bshift = bits > 8 ? bits - 8 : 0;
-                for (uint32_t i = tid; i < L; i += kBlock)
-                    atomicAdd(&sh.hist[((uint32_t)(skey[i] >> 32) - hlo) >> bshift], 1u);
+            for (int u = 0; u < NU; ++u)
+                mk = umax64(mk, ck[u]);
+            int at;
+            mk = wave_max_key(mk, at);
+            if (lane == 0)
+                sh.red2[wave] = mk;
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kRWaves; ++q)
+                mk = umax64(mk, sh.red2[q]);
+            if (mk == 0 || (mk >> 32) != 0) {
+                // impossible by construction; a guard so that a violated
+                // invariant ends the call
+                if (tid == 0)
+                    set_status(&a.hdr->sample_status, RFPS_ERR_INTERNAL);
+                return false;
+            }
+            if (rank == 0) {
+                for (int q = j + tid; q < job.m; q += kRBlock) {
+                    job.out_idx[q] = (int32_t)key_orig(mk);
+                    if (job.out_d2)
+                        job.out_d2[q] = 0.0f;
+                }
+            }
+            if (trace && round - 1 < (uint32_t)kTraceCap) {
+                a.trace[2 * (size_t)(round - 1)] = t_pub;
+                a.trace[2 * (size_t)(round - 1) + 1] =
+                    wall_clock64() | ((unsigned long long)min(job.m - j, 0xffff) << 48);
+            }
+            n_out = 0;
+            break;
+        }
+        if (T && clocks)
+            tl.above += L;
+        if (L > (uint32_t)kList) {
+            // Too many for one round: find a key with at most kList (and at
+            // least half as many) candidates above it, by 256-bin histograms
+            // of the keys' range, narrowed to the bin that holds the edge.
+            unsigned long long hm = 0;
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+                hm = umax64(hm, ck[u]);
+            int at;
+            hm = wave_max_key(hm, at);
+            if (lane == 0)
+                sh.red2[wave] = hm;
+            __syncthreads();
+            unsigned long long hi = 0;
+#pragma unroll
+            for (int q = 0; q < kRWaves; ++q)
+                hi = umax64(hi, sh.red2[q]);
+            unsigned long long lo = umax64(smax, 0xffffffffull) + 1ull;  // keys of the range: lo .. hi
+            uint32_t have = 0;                                           // candidates above the range
+            for (;;) {
+                const int bits = 64 - __clzll((long long)((hi - lo) | 1ull));
+                const int shift = bits > 8 ? bits - 8 : 0;
                 __syncthreads();
-                // msel: the highest bucket whose suffix holds kList candidates
+                if (tid < 256)
+                    sh.hist[tid] = 0;
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < NU; ++u)
+                    if (ck[u] >= lo && ck[u] <= hi)
+                        atomicAdd(&sh.hist[(uint32_t)((ck[u] - lo) >> shift)], 1u);
+                __syncthreads();
                 if (wave == 0) {
-                    uint32_t c4 = 0;
+                    // the lowest bin such that it and those above hold at most kList - have
+                    uint32_t c4[4], sum = 0;
 #pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        c4 += sh.hist[4 * lane + b];
-                    uint32_t suf = c4;  // candidates in the buckets of lanes >= this one
-#pragma unroll
-                    for (int off = 1; off < kWave; off <<= 1) {
-                        const uint32_t o = (uint32_t)__shfl_down((int)suf, off, kWave);
-                        suf += lane + off < kWave ? o : 0u;
+                    for (int v = 0; v < 4; ++v) {
+                        c4[v] = sh.hist[4 * lane + v];
+                        sum += c4[v];
                     }
-                    const unsigned long long enough = __ballot(suf >= (uint32_t)kList);
-                    const int lt = 63 - __clzll((long long)enough);
-                    if (lane == lt) {
-                        uint32_t acc = suf - c4;
-                        for (int b = 3; b >= 0; --b) {
-                            acc += sh.hist[4 * lane + b];
-                            if (acc >= (uint32_t)kList) {
-                                sh.msel = (uint32_t)(4 * lane + b);
-                                sh.mtotal = acc;
-                                break;
-                            }
+                    uint32_t suf = sum;
+#pragma unroll
+                    for (int o = 1; o < kWave; o <<= 1) {
+                        const uint32_t v = (uint32_t)__shfl_down((int)suf, o, kWave);
+                        suf += lane + o < kWave ? v : 0u;
+                    }
+                    uint32_t acc = suf - sum, bin = 256, tot = 0;
+#pragma unroll
+                    for (int v = 3; v >= 0; --v) {
+                        acc += c4[v];
+                        if (acc <= (uint32_t)kList - have) {
+                            bin = 4 * lane + v;
+                            tot = acc;
                         }
                     }
-                }
-                __syncthreads();
-                const uint32_t bsel = sh.msel;
-                const uint32_t above = sh.mtotal - sh.hist[bsel];  // fewer than kList
-                // the buckets above msel are listed when they hold anything;
-                // else msel alone holds kList or more (keys that agree in their
-                // high bits), and its candidates are put in order below
-                const uint32_t bfront = above ? bsel + 1 : bsel;
-                const uint32_t nfront = above ? above : sh.mtotal;
-                constexpr int kParts = (kMaxGroups * R + kBlock - 1) / kBlock;  // L <= G * R
-                unsigned long long pk_[kParts];
-                uint32_t pc_[kParts], pp_[kParts];
-#pragma unroll
-                for (int u = 0; u < kParts; ++u) {
-                    const uint32_t i = tid + kBlock * u;
-                    const bool in = i < L;
-                    pk_[u] = in ? skey[i] : 0ull;
-                    pc_[u] = in ? sidx[i] : 0u;
-                    const bool front = in && (((uint32_t)(pk_[u] >> 32) - hlo) >> bshift) >= bfront;
-                    const unsigned long long fm = __ballot(front);
-                    uint32_t fb = 0;
-                    if (lane == 0 && fm)
-                        fb = atomicAdd(&sh.pfront, (uint32_t)__popcll(fm));
-                    fb = (uint32_t)__shfl((int)fb, 0, kWave);
-                    pp_[u] = front ? fb + (uint32_t)__popcll(fm & below) : 0xffffffffu;
-                }
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < kParts; ++u) {
-                    if (pp_[u] != 0xffffffffu) {
-                        skey[pp_[u]] = pk_[u];
-                        sidx[pp_[u]] = pc_[u];
+                    const uint32_t lowest = wave_min_u32(bin);
+                    const unsigned long long own = ballot64(bin == lowest);
+                    if (lane == __ffsll((long long)own) - 1) {
+                        sh.cut_bin = lowest;
+                        sh.cut_have = lowest < 256 ? tot : 0u;
                     }
                 }
                 __syncthreads();
-                // every candidate left out lies in a bucket below bfront
-                const unsigned long long edge = (unsigned long long)(hlo + (bfront << bshift)) << 32;
-                if (edge)
-                    scur = umax64(scur, edge - 1ull);
-                W = nfront;
-                if (!above && nfront > (uint32_t)kList) {
-                    // order the bucket by whole keys (equal keys: list order)
-                    // and keep its first kList, cut between different keys
-                    for (uint32_t i = tid; i < nfront; i += kBlock) {
-                        const unsigned long long ki = skey[i];
-                        uint32_t r = 0;
-                        for (uint32_t q = 0; q < nfront; ++q) {
-                            const unsigned long long kq = skey[q];
-                            r += (kq > ki || (kq == ki && q < i)) ? 1u : 0u;
-                        }
-                        if (r <= (uint32_t)kList)
-                            ord[r] = i;
-                    }
-                    __syncthreads();
-                    W = kList;
-                    while (W > 1 && skey[ord[W - 1]] == skey[ord[W]])
-                        --W;  // equal keys are repeats of one point (at most R)
-                    scur = umax64(scur, skey[ord[W]]);
-                    unsigned long long kk = 0;
-                    uint32_t cc = 0;
-                    if ((uint32_t)tid < W) {
-                        kk = skey[ord[tid]];
-                        cc = sidx[ord[tid]];
-                    }
-                    __syncthreads();
-                    if ((uint32_t)tid < W) {
-                        skey[tid] = kk;
-                        sidx[tid] = cc;
-                    }
-                    __syncthreads();
+                const uint32_t bin = sh.cut_bin;
+                have += sh.cut_have;
+                const unsigned long long edge = lo + ((unsigned long long)bin << shift);
+                if (have >= (uint32_t)kList / 2 || shift == 0 || bin == 0) {
+                    scur = edge - 1ull;
+                    break;
                 }
-                // the list moved: stage it again
-                if ((uint32_t)tid < W)
-                    stage(tid, sidx[tid], skey[tid]);
-                __syncthreads();
-            }
-            const uint32_t pmax = min(W, (uint32_t)(job.m - j));
-            unsigned long long t_sub = 0;
-            if (clocks) {
-                t_sub = wall_clock64();
-                tl.sub[0] += t_sub - t_mark;
-                tl.above += L;
-                tl.listed += W;
-            }
-
-            // Ranks and lowering sets: for every listed candidate i, the set of
-            // listed candidates q with a larger key that would lower it (state
-            // value of their distance below i's listed distance), as two
-            // 64-bit words (q < 64, q >= 64), and its rank in key order
-            // (larger keys, then equal keys listed before it: only repeats of
-            // one point are equal).  For q < 64, lanes take q and the
-            // wavefronts take every fourth i, kRankPerPass at a time (measured
-            // faster than a contiguous quarter of the list each), and one
-            // ballot gives a word; the few q >= 64 are taken the other way
-            // round (lanes take i, wavefronts share the q) so that no pass
-            // runs over a nearly empty chunk of lanes.  Every ballot is of a single
-            // comparison, so its lane mask is used as it is.
-            const bool two = W > (uint32_t)kWave;  // some candidates are q >= 64
-            const unsigned long long v0 = ballot64((uint32_t)lane < W);
-            const unsigned long long v1 = ballot64((uint32_t)lane + kWave < W);
-            const float4 q0 = sh.lq[lane];
-            const float4 q1 = sh.lq[two ? lane + kWave : lane];
-            const unsigned long long k0 = ((unsigned long long)__float_as_uint(q0.w) << 32) | sh.lkl[lane];
-            const unsigned long long k1 =
-                ((unsigned long long)__float_as_uint(q1.w) << 32) | sh.lkl[two ? lane + kWave : lane];
-            {
-                uint32_t r0l = 0, r0h = 0, rrk = 0;
-                int t = 0;
-                constexpr int kP = kRankPerPass;
-                for (uint32_t i = (uint32_t)wave; i < W; i += kP * kWavesPerBlock, t += kP) {
-                    // kP independent candidates per pass (the later ones may
-                    // lie past the list: their results are not kept)
-                    float4 qa[kP];
-                    unsigned long long ka[kP];
-#pragma unroll
-                    for (int u = 0; u < kP; ++u) {
-                        const uint32_t iu = i + u * kWavesPerBlock < W ? i + u * kWavesPerBlock : i;
-                        qa[u] = sh.lq[iu];
-                        ka[u] = ((unsigned long long)__float_as_uint(qa[u].w) << 32) | sh.lkl[iu];
-                    }
-#pragma unroll
-                    for (int u = 0; u < kP; ++u) {
-                        const float da = sqdist(qa[u].x, qa[u].y, qa[u].z, q0.x, q0.y, q0.z);
-                        const unsigned long long ga = ballot64(k0 > ka[u]) & v0;
-                        bool ba = da < qa[u].w;
-                        if (euclid)
-                            ba = ba && sqrt_class_top(da) < qa[u].w;
-                        const unsigned long long ma = ballot64(ba) & ga;
-                        // lane t keeps the results of this wavefront's t-th candidate
-                        const bool sa = lane == t + u;
-                        r0l = sa ? (uint32_t)ma : r0l;
-                        r0h = sa ? (uint32_t)(ma >> 32) : r0h;
-                        rrk = sa ? (uint32_t)__popcll(ga) : rrk;
-                    }
-                }
-                const uint32_t i = (uint32_t)wave + (uint32_t)kWavesPerBlock * (uint32_t)lane;
-                if (i < W) {
-                    sh.lset0[i] = ((unsigned long long)r0h << 32) | r0l;
-                    atomicAdd(&sh.lrank[i], rrk);
-                }
-            }
-            if (two) {
-                // q >= 64: lane l takes candidates l and l + 64, wavefront w
-                // the q = 64 + w, 64 + w + 4, ...
-                unsigned long long s0 = 0, s1 = 0;
-                uint32_t c0 = 0, c1 = 0;
-                for (uint32_t q = (uint32_t)kWave + wave; q < W; q += kWavesPerBlock) {
-                    const float4 qq = sh.lq[q];
-                    const unsigned long long kq = ((unsigned long long)__float_as_uint(qq.w) << 32) | sh.lkl[q];
-                    const unsigned long long bit = 1ull << (q - kWave);
-                    const float d0 = sqdist(q0.x, q0.y, q0.z, qq.x, qq.y, qq.z);
-                    const float d1 = sqdist(q1.x, q1.y, q1.z, qq.x, qq.y, qq.z);
-                    bool b0 = d0 < q0.w, b1 = d1 < q1.w;
-                    if (euclid) {
-                        b0 = b0 && sqrt_class_top(d0) < q0.w;
-                        b1 = b1 && sqrt_class_top(d1) < q1.w;
-                    }
-                    const bool g0 = kq > k0, g1 = kq > k1;
-                    s0 |= (b0 && g0) ? bit : 0ull;
-                    s1 |= (b1 && g1) ? bit : 0ull;
-                    c0 += g0 ? 1u : 0u;
-                    c1 += g1 ? 1u : 0u;
-                }
-                if ((uint32_t)lane < W) {
-                    if (s0)
-                        atomicOr(&sh.lset1[lane], s0);
-                    atomicAdd(&sh.lrank[lane], c0);
-                }
-                if ((uint32_t)lane + kWave < W) {
-                    if (s1)
-                        atomicOr(&sh.lset1[lane + kWave], s1);
-                    atomicAdd(&sh.lrank[lane + kWave], c1);
-                }
-            }
-            if (rep) {
-                // equal keys (repeats of one point): those listed before a
-                // candidate also rank above it
-                for (uint32_t i = (uint32_t)wave; i < W; i += kWavesPerBlock) {
-                    const float4 qi = sh.lq[i];
-                    const unsigned long long ki = ((unsigned long long)__float_as_uint(qi.w) << 32) | sh.lkl[i];
-                    const uint32_t il = i & (kWave - 1);
-                    const unsigned long long before = il ? ~0ull >> (kWave - il) : 0ull;
-                    const unsigned long long e0 = ballot64(k0 == ki) & v0 & (i >= (uint32_t)kWave ? ~0ull : before);
-                    const unsigned long long e1 = ballot64(k1 == ki) & v1 & (i >= (uint32_t)kWave ? before : 0ull);
-                    if (lane == 0 && (e0 | e1))
-                        atomicAdd(&sh.lrank[i], (uint32_t)(__popcll(e0) + __popcll(e1)));
-                }
+                hi = edge - 1ull;  // the bin below holds more than fit: narrow the range to it
+                lo = edge - (1ull << shift);
             }
             __syncthreads();
-            if (clocks) {
-                const unsigned long long t = wall_clock64();
-                tl.sub[1] += t - t_sub;
-                t_sub = t;
-            }
+            list_above(scur);
+        }
+        const int nb = (int)((L + kBlk - 1) / kBlk);
+        unsigned long long t_sub = 0;
+        if (clocks) {
+            t_sub = wall_clock64();
+            tl.sub[0] += t_sub - t_mark;
+            tl.listed += L;
+        }
 
-            // Certification walk (wavefront 0), in registers: lane l holds
-            // listed candidates l and l + 64 (key, set, rank, coordinates).
-            // The list stays in key order, so "earlier" means "larger key":
-            // a live candidate fails when a live member of its set exists
-            // (every live candidate with a larger key is a pick if the walk
-            // reaches it), the first failure is the failing candidate with
-            // the largest key, and the picks before it are the live
-            // candidates with larger keys, which stay live from then on.
-            if (wave == 0) {
-                unsigned long long s00 = sh.lset0[lane], s01 = sh.lset1[lane];
-                unsigned long long s10 = two ? sh.lset0[lane + kWave] : 0ull;
-                unsigned long long s11 = two ? sh.lset1[lane + kWave] : 0ull;
-                const uint32_t rk0 = sh.lrank[lane], rk1 = two ? sh.lrank[lane + kWave] : 0u;
-                const uint32_t cc0 = sidx[lane], cc1 = two ? sidx[lane + kWave] : 0u;
-                unsigned long long kc0 = k0, kc1 = k1;      // current listed keys
-                unsigned long long L0 = v0, L1 = v1;        // live (listed) candidates
-                unsigned long long X0 = 0, X1 = 0;          // re-listed or dropped as a group's later candidate
-                unsigned long long R0 = 0, R1 = 0;          // re-listed
-                uint32_t nfail = 0, P;
-                for (;;) {
-                    const unsigned long long F0 = ballot64(((s00 & L0) | (s01 & L1)) != 0ull) & L0;
-                    const unsigned long long F1 = ballot64(((s10 & L0) | (s11 & L1)) != 0ull) & L1;
-                    if (!(F0 | F1)) {
-                        P = min((uint32_t)(__popcll(L0) + __popcll(L1)), pmax);
-                        break;
-                    }
-                    // the failing candidate with the largest key
-                    const unsigned long long bit = 1ull << lane;
-                    const unsigned long long kf = wave_max_u64(umax64((F0 & bit) ? kc0 : 0ull, (F1 & bit) ? kc1 : 0ull));
-                    const unsigned long long h0 = ballot64(kc0 > kf) & L0, h1 = ballot64(kc1 > kf) & L1;
-                    P = (uint32_t)(__popcll(h0) + __popcll(h1));
-                    if (P >= pmax) {
-                        P = pmax;
-                        break;
-                    }
-                    if (++nfail > kMaxFailures)
-                        break;
-                    const unsigned long long e0 = ballot64(kc0 == kf) & F0;
-                    const uint32_t fi = e0 ? (uint32_t)(__ffsll((long long)e0) - 1)
-                                           : (uint32_t)kWave + (uint32_t)(__ffsll((long long)(ballot64(kc1 == kf) & F1)) - 1);
-                    const bool fh = fi >= (uint32_t)kWave;
-                    const int fl = (int)(fi & (kWave - 1));
-                    const float xf = lane_f32(fh ? q1.x : q0.x, fl), yf = lane_f32(fh ? q1.y : q0.y, fl),
-                                zf = lane_f32(fh ? q1.z : q0.z, fl);
-                    const unsigned long long sfl = fh ? s10 : s00, sfh = fh ? s11 : s01;
-                    const unsigned long long sf0 = ((unsigned long long)lane_u32((uint32_t)(sfl >> 32), fl) << 32) |
-                                                   lane_u32((uint32_t)sfl, fl);
-                    const unsigned long long sf1 = ((unsigned long long)lane_u32((uint32_t)(sfh >> 32), fl) << 32) |
-                                                   lane_u32((uint32_t)sfh, fl);
-                    const uint32_t cf = lane_u32(fh ? cc1 : cc0, fl);
-                    // its true distance: the listed distance lowered by the
-                    // live members of its set (all of them picks)
-                    const float d0 = sqdist(xf, yf, zf, q0.x, q0.y, q0.z), d1 = sqdist(xf, yf, zf, q1.x, q1.y, q1.z);
-                    float tv = INFINITY;
-                    if ((sf0 & L0) & bit)
-                        tv = min_dist(tv, d0, euclid);
-                    if ((sf1 & L1) & bit)
-                        tv = min_dist(tv, d1, euclid);
-                    const float tf = fminf(wave_min_dist(tv), __uint_as_float((uint32_t)(kf >> 32)));
-                    const unsigned long long kt = ((unsigned long long)__float_as_uint(tf) << 32) | (uint32_t)kf;
-                    scur = umax64(scur, ((unsigned long long)cword(cf, 5) << 32) | 0xffffffffull);
-                    const uint32_t gf = cf / R, hf = cf % R;
-                    // the group's later candidates (their local keys assumed
-                    // this one picked) and every key <= the bound leave; the
-                    // picks so far (h0, h1: the live keys above it) stay
-                    const unsigned long long g0 = ballot64(cc0 / R == gf) & ballot64(cc0 % R > hf) & L0 & ~h0;
-                    const unsigned long long g1 = ballot64(cc1 / R == gf) & ballot64(cc1 % R > hf) & L1 & ~h1;
-                    X0 |= g0;
-                    X1 |= g1;
-                    L0 &= ~((g0 | ballot64(kc0 <= scur)) & ~h0);
-                    L1 &= ~((g1 | ballot64(kc1 <= scur)) & ~h1);
-                    // the failed candidate goes back in with key kt if that is
-                    // above the bound; its set is taken again against tf
-                    const bool put = kt > scur;
-                    if (fh) {
-                        const unsigned long long fb = 1ull << fl;
-                        L1 = put ? (L1 | fb) : (L1 & ~fb);
-                        X1 |= fb;
-                        R1 |= fb;
-                        if (lane == fl)
-                            kc1 = kt;
-                    } else {
-                        const unsigned long long fb = 1ull << fl;
-                        L0 = put ? (L0 | fb) : (L0 & ~fb);
-                        X0 |= fb;
-                        R0 |= fb;
-                        if (lane == fl)
-                            kc0 = kt;
-                    }
-                    bool b0 = d0 < tf, b1 = d1 < tf;
-                    if (euclid) {
-                        b0 = b0 && sqrt_class_top(d0) < tf;
-                        b1 = b1 && sqrt_class_top(d1) < tf;
-                    }
-                    const unsigned long long n0 = ballot64(b0) & ballot64(kc0 > kt) & v0;
-                    const unsigned long long n1 = ballot64(b1) & ballot64(kc1 > kt) & v1;
-                    // candidates now above it no longer have it earlier
-                    const unsigned long long above = fh ? ~(1ull << fl) : ~0ull, abovel = fh ? ~0ull : ~(1ull << fl);
-                    if (kc0 > kt) {
-                        s00 &= abovel;
-                        s01 &= above;
-                    }
-                    if (kc1 > kt) {
-                        s10 &= abovel;
-                        s11 &= above;
-                    }
-                    if (lane == fl) {
-                        if (fh) {
-                            s10 = n0;
-                            s11 = n1;
-                        } else {
-                            s00 = n0;
-                            s01 = n1;
-                        }
-                    }
+        // Conflicts: for every listed candidate i, the set of listed
+        // candidates q of no smaller distance that may lower it.  The matrix
+        // cores test 16 x 16 blocks of pairs with a margin that keeps every
+        // true conflict (filter_row); the certification checks the kept ones
+        // it meets exactly, ties of the distance included.  Columns are i: a
+        // lane holds one i and four q per block, so it collects its part of
+        // the row of i without exchange.
+        {
+            // NP wavefronts split the row blocks (QS each, kept in registers)
+            // and the others the columns: what a wavefront reads of LDS is
+            // what bounds this phase (1.4 us for lists of about 150; 2.4 with
+            // the row data read again for every block).  A lane stores the
+            // bits of its row blocks at once.  Row blocks past the list give
+            // bits of positions past it, which no live mask holds.
+            const float *lbf = reinterpret_cast<const float *>(sh.lb);
+            auto conflicts = [&](auto qs_c, auto np_c) {
+                constexpr int QS = decltype(qs_c)::value, NP = decltype(np_c)::value;
+                const int part = wave & (NP - 1);
+                if (part * QS >= nb)
+                    return;
+                float av[QS];
+                float4 dr[QS];
+#pragma unroll
+                for (int v = 0; v < QS; ++v) {
+                    const int rb = part * QS + v;
+                    av[v] = lbf[(rb * kBlk + li) * 4 + lg];
+                    dr[v] = *reinterpret_cast<const float4 *>(&sh.ld[rb * kBlk + 4 * lg]);
                 }
-                // Order of the live candidates by current key.  A candidate
-                // whose key never changed has its list rank less the
-                // re-listed or group-dropped candidates ranked above it
-                // (every other candidate that left the list lies below all
-                // live ones), plus the re-listed live candidates above it; a
-                // re-listed one counts the live keys above its own.
-                uint32_t lr0 = rk0, lr1 = rk1;
-                unsigned long long xs0 = X0, xs1 = X1;
-                while (xs0 | xs1) {
-                    const bool qh = xs0 == 0ull;
-                    const int ql = __ffsll((long long)(qh ? xs1 : xs0)) - 1;
-                    if (qh)
-                        xs1 &= xs1 - 1;
+                for (int cb = wave / NP; cb < nb; cb += kRWaves / NP) {
+                    const int i = cb * kBlk + li;
+                    const float bv = lbf[i * 4 + lg];
+                    const float bv2 = lg == 3 ? 1.0f : -2.0f * bv;
+                    const float ti = sh.lT[i];
+                    // the next value below the distance: q of the same
+                    // distance give a negative difference too
+                    const float di = __uint_as_float(__float_as_uint(sh.ld[i]) - 1u);
+                    f32x4 dd[QS];
+#pragma unroll
+                    for (int v = 0; v < QS; ++v)
+                        dd[v] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[v], bv2, f32x4{ti, ti, ti, ti}, 0, 0, 0);
+                    // a pair is kept when both terms are negative: their
+                    // common sign bit goes into the row
+                    uint32_t acc = 0;
+                    auto put = [&](float x, float dq) {
+                        acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(x) & __float_as_uint(di - dq), 31);
+                    };
+#pragma unroll
+                    for (int v = QS - 1; v >= 0; --v) {
+                        put(dd[v][3], dr[v].w);
+                        put(dd[v][2], dr[v].z);
+                        put(dd[v][1], dr[v].y);
+                        put(dd[v][0], dr[v].x);
+                    }
+                    // a candidate and itself
+                    const int v = cb - part * QS;
+                    if (v >= 0 && v < QS)
+                        acc &= lg == li / 4 ? ~(1u << (4 * v + li % 4)) : ~0u;
+                    if constexpr (QS <= 2)
+                        reinterpret_cast<uint8_t *>(sh.adj)[(i * 4 + lg) * NP + part] = (uint8_t)acc;
                     else
-                        xs0 &= xs0 - 1;
-                    const uint32_t rq = lane_u32(qh ? rk1 : rk0, ql);
-                    const unsigned long long kv = qh ? kc1 : kc0;
-                    const unsigned long long kq =
-                        ((unsigned long long)lane_u32((uint32_t)(kv >> 32), ql) << 32) | lane_u32((uint32_t)kv, ql);
-                    const bool rel_live = ((qh ? R1 & L1 : R0 & L0) >> ql) & 1ull;
-                    lr0 = lr0 - (rq < rk0 ? 1u : 0u) + ((rel_live && kq > kc0) ? 1u : 0u);
-                    lr1 = lr1 - (rq < rk1 ? 1u : 0u) + ((rel_live && kq > kc1) ? 1u : 0u);
+                        reinterpret_cast<uint16_t *>(sh.adj)[(i * 4 + lg) * NP + part] = (uint16_t)acc;
                 }
-                // a re-listed live candidate: the live keys above its own
-                unsigned long long rs0 = R0 & L0, rs1 = R1 & L1;
-                while (rs0 | rs1) {
-                    const bool qh = rs0 == 0ull;
-                    const int ql = __ffsll((long long)(qh ? rs1 : rs0)) - 1;
-                    if (qh)
-                        rs1 &= rs1 - 1;
-                    else
-                        rs0 &= rs0 - 1;
-                    const unsigned long long kv = qh ? kc1 : kc0;
-                    const unsigned long long kq =
-                        ((unsigned long long)lane_u32((uint32_t)(kv >> 32), ql) << 32) | lane_u32((uint32_t)kv, ql);
-                    const uint32_t own =
-                        (uint32_t)(__popcll(ballot64(kc0 > kq) & L0) + __popcll(ballot64(kc1 > kq) & L1));
-                    if (lane == ql) {
-                        if (qh)
-                            lr1 = own;
-                        else
-                            lr0 = own;
-                    }
-                }
-                // the picks: the first P live candidates in that order.  Their
-                // coordinates go to the apply phase; rank 0 writes the
-                // outputs (original index and distance from the listed key)
-                // straight away, long before this wavefront next waits on
-                // device memory (in the next exchange)
-                const bool p0 = ((L0 >> lane) & 1ull) && lr0 < P, p1 = ((L1 >> lane) & 1ull) && lr1 < P;
-                if (p0) {
-                    pkx[lr0] = q0.x;
-                    pky[lr0] = q0.y;
-                    pkz[lr0] = q0.z;
-                    if (rank == 0) {
-                        job.out_idx[j + (int)lr0] = (int32_t)~(uint32_t)kc0;
-                        if (job.out_d2)
-                            job.out_d2[j + (int)lr0] = __uint_as_float((uint32_t)(kc0 >> 32));
-                    }
-                }
-                if (p1) {
-                    pkx[lr1] = q1.x;
-                    pky[lr1] = q1.y;
-                    pkz[lr1] = q1.z;
-                    if (rank == 0) {
-                        job.out_idx[j + (int)lr1] = (int32_t)~(uint32_t)kc1;
-                        if (job.out_d2)
-                            job.out_d2[j + (int)lr1] = __uint_as_float((uint32_t)(kc1 >> 32));
-                    }
-                }
-                if (lane == 0)
-                    sh.npick = P;
-                if (clocks) {
-                    const unsigned long long t = wall_clock64();
-                    tl.sub[2] += t - t_sub;
-                    tl.sub[3] -= t;
-                    tl.fails += nfail;
-                }
-            }
+            };
+            const std::integral_constant<int, 4> c4{};
+            if (nb <= 4)
+                conflicts(std::integral_constant<int, 2>(), std::integral_constant<int, 2>());
+            else if (nb <= 8)
+                conflicts(std::integral_constant<int, 2>(), c4);
+            else if (nb <= 12)
+                conflicts(std::integral_constant<int, 3>(), c4);
+            else
+                conflicts(c4, c4);
         }
         __syncthreads();
-        const int P = (int)sh.npick;
+        if (clocks) {
+            const unsigned long long t = wall_clock64();
+            tl.sub[1] += t - t_sub;
+            t_sub = t;
+        }
+
+        // Certification, in registers, on wavefront 0 for lists of up to 128
+        // and on four wavefronts for longer ones (a pass over four rows per
+        // lane on one wavefront took 3.1 us a round, split over four 1.7;
+        // two rows do not pay for the two barriers).  Lane l holds the listed
+        // candidates at conflict_pos(w, l) with their conflict rows.  A live
+        // candidate with no live one in its row is free: it is a pick if the
+        // round gets that far.  One that a free candidate lowers has failed:
+        // its true key is at most its distance to that candidate, and the
+        // other points of its wavefront are bounded by its runner-up, so the
+        // bound rises to the larger of the two.  Failed candidates and every
+        // key at or below the bound leave, and so on until every live
+        // candidate is free.  (The live candidate with the largest key that is
+        // not free always has a free one in its row, so every pass ends one or
+        // clears a pair that is no conflict; a failed candidate the sequence
+        // would not have reached has its key, and so both of its terms, below
+        // the bound already.)
+        if (wave == 0) {
+            auto walk = [&](auto nw_c) {
+                constexpr int NW = decltype(nw_c)::value;
+                const int qs = nb <= 12 ? 3 : 4;
+                unsigned long long s[NW][NW], key[NW], lv[NW];
+                float4 q[NW];
+#pragma unroll
+                for (int k = 0; k < NW; ++k) {
+                    const int i = conflict_pos<NW>(k, lane, qs);
+                    const bool in = (uint32_t)i < L;
+                    lv[k] = ballot64(in);
+                    const int ii = in ? i : 0;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w)
+                        s[k][w] = sh.adj[ii * NW + w];
+                    q[k] = sh.lq[ii];
+                    key[k] = sh.lkey[ii];
+                }
+                uint32_t nfail = 0;
+                bool ties = false;  // the last pass ended nothing: mutual ties
+                for (;;) {
+                    unsigned long long f[NW], fr[NW], any = 0;
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) {
+                        unsigned long long acc = 0;
+#pragma unroll
+                        for (int w = 0; w < NW; ++w)
+                            acc |= s[k][w] & lv[w];
+                        f[k] = ballot64(acc != 0ull) & lv[k];
+                        any |= f[k];
+                    }
+                    if (!any)
+                        break;
+#pragma unroll
+                    for (int k = 0; k < NW; ++k)
+                        fr[k] = ties ? lv[k] : lv[k] & ~f[k];
+                    unsigned long long b = 0, met = 0;
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) {
+                        // the first free candidate of its row (the list has one
+                        // order in every workgroup, so all find the same bound)
+                        int at = 0, aw = -1;
+                        unsigned long long bit = 0;
+#pragma unroll
+                        for (int w = NW - 1; w >= 0; --w) {
+                            const unsigned long long h = s[k][w] & fr[w];
+                            if (h) {
+                                at = conflict_pos<NW>(w, __ffsll((long long)h) - 1, qs);
+                                bit = h & (0ull - h);
+                                aw = w;
+                            }
+                        }
+                        bool fails = false;
+                        const bool meets = ((f[k] >> lane) & 1ull) && aw >= 0;
+                        if (meets) {
+                            const float4 p = sh.lq[at];
+                            const float d = key_d2(key[k]);
+                            const float t = min_dist(d, sqdist(q[k].x, q[k].y, q[k].z, p.x, p.y, p.z), euclid);
+                            // a pair within the filter's margin, or a tie of
+                            // the distance with the smaller key, is no conflict
+                            const bool real = t < d && sh.lkey[at] > key[k];
+                            fails = real && !ties;
+#pragma unroll
+                            for (int w = 0; w < NW; ++w)
+                                s[k][w] &= (!real && aw == w) ? ~bit : ~0ull;
+                            const unsigned long long kt =
+                                ((unsigned long long)__float_as_uint(t) << 32) | (uint32_t)key[k];
+                            // the runner-up's key is below this one's
+                            const unsigned long long ku =
+                                ((unsigned long long)__float_as_uint(q[k].w) << 32) | 0xffffffffull;
+                            const unsigned long long kb = umax64(kt, ku < key[k] ? ku : key[k] - 1ull);
+                            b = fails ? umax64(b, kb) : b;
+                        }
+                        const unsigned long long om = ballot64(fails);
+                        lv[k] &= ~om;
+                        met |= ballot64(meets);
+                        nfail += (uint32_t)__popcll(om);
+                    }
+                    // no free candidate in any row: only ties of the distance
+                    // hold the largest of them back; clear those next
+                    ties = met == 0ull;
+                    int at;
+                    scur = umax64(scur, wave_max_key(b, at));
+#pragma unroll
+                    for (int k = 0; k < NW; ++k)
+                        lv[k] &= ballot64(key[k] > scur);
+                }
+                // the picks, in any order, for the apply phase and the outputs
+                uint32_t n = 0;
+#pragma unroll
+                for (int k = 0; k < NW; ++k) {
+                    const uint32_t pos = n + (uint32_t)__popcll(lv[k] & below);
+                    if ((lv[k] >> lane) & 1ull) {
+                        sh.pk[pos] = q[k];
+                        sh.pk[kList + pos] = sh.lb[conflict_pos<NW>(k, lane, qs)];
+                        sh.pkey[pos] = key[k];
+                    }
+                    n += (uint32_t)__popcll(lv[k]);
+                }
+                // padding of the last block: columns that pass no filter
+                if (lane < kBlk && n + lane < (n + kBlk - 1) / kBlk * kBlk)
+                    sh.pk[kList + n + lane] = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
+                if (lane == 0)
+                    sh.npick = n;
+                if (clocks)
+                    tl.fails += nfail;
+            };
+            if (L <= kWave)
+                walk(std::integral_constant<int, 1>());
+            else if (L <= 2 * kWave)
+                walk(std::integral_constant<int, 2>());
+        }
+        if (L > 2 * kWave) {
+            // The same for longer lists, on four wavefronts: wavefront w takes
+            // the candidates of word w, and masks and bound meet in LDS.
+            const int qs = nb <= 12 ? 3 : 4;
+            const int w4 = wave & 3;
+            unsigned long long s[4], key[4], lv[4];
+            float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            const int own = conflict_pos<4>(w4, lane, qs);
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const int i = conflict_pos<4>(w, lane, qs);
+                lv[w] = ballot64((uint32_t)i < L);
+                key[w] = sh.lkey[(uint32_t)i < L ? i : 0];
+                s[w] = sh.adj[((uint32_t)own < L ? own : 0) * 4 + w];
+            }
+            q = sh.lq[(uint32_t)own < L ? own : 0];
+            const unsigned long long k0 = w4 == 0 ? key[0] : w4 == 1 ? key[1] : w4 == 2 ? key[2] : key[3];
+            uint32_t nfail = 0;
+            bool ties = false;
+            for (;;) {
+                if (wave < 4) {
+                    const unsigned long long acc = (s[0] & lv[0]) | (s[1] & lv[1]) | (s[2] & lv[2]) | (s[3] & lv[3]);
+                    const unsigned long long f = ballot64(acc != 0ull) &
+                                                 (w4 == 0 ? lv[0] : w4 == 1 ? lv[1] : w4 == 2 ? lv[2] : lv[3]);
+                    if (lane == 0)
+                        sh.wf[wave] = f;
+                    if (tid == 0)
+                        sh.wscur = 0ull;
+                }
+                __syncthreads();
+                unsigned long long f[4], fr[4];
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    f[w] = lane_u64(sh.wf[w], 0);
+                if (!(f[0] | f[1] | f[2] | f[3]))
+                    break;
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    fr[w] = ties ? lv[w] : lv[w] & ~f[w];
+                if (wave < 4) {
+                    int at = 0, aw = -1;
+                    unsigned long long bit = 0;
+#pragma unroll
+                    for (int w = 3; w >= 0; --w) {
+                        const unsigned long long h = s[w] & fr[w];
+                        if (h) {
+                            at = conflict_pos<4>(w, __builtin_ctzll(h), qs);
+                            bit = h & (0ull - h);
+                            aw = w;
+                        }
+                    }
+                    unsigned long long b = 0;
+                    bool fails = false;
+                    const unsigned long long fo = w4 == 0 ? f[0] : w4 == 1 ? f[1] : w4 == 2 ? f[2] : f[3];
+                    const bool meets = ((fo >> lane) & 1ull) && aw >= 0;
+                    if (meets) {
+                        const float4 p = sh.lq[at];
+                        const float d = key_d2(k0);
+                        const float t = min_dist(d, sqdist(q.x, q.y, q.z, p.x, p.y, p.z), euclid);
+                        const bool real = t < d && sh.lkey[at] > k0;
+                        fails = real && !ties;
+#pragma unroll
+                        for (int w = 0; w < 4; ++w)
+                            s[w] &= (!real && aw == w) ? ~bit : ~0ull;
+                        const unsigned long long kt = ((unsigned long long)__float_as_uint(t) << 32) | (uint32_t)k0;
+                        const unsigned long long ku = ((unsigned long long)__float_as_uint(q.w) << 32) | 0xffffffffull;
+                        const unsigned long long kb = umax64(kt, ku < k0 ? ku : k0 - 1ull);
+                        b = fails ? kb : 0ull;
+                    }
+                    const unsigned long long om = ballot64(fails), met = ballot64(meets);
+                    int mat;
+                    b = wave_max_key(b, mat);
+                    if (lane == 0) {
+                        sh.wo[wave] = om;
+                        sh.wmet[wave] = met ? 1u : 0u;
+                        if (b)
+                            atomicMax(&sh.wscur, b);
+                    }
+                }
+                __syncthreads();
+                scur = umax64(scur, sh.wscur);
+                ties = (sh.wmet[0] | sh.wmet[1] | sh.wmet[2] | sh.wmet[3]) == 0u;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const unsigned long long om = lane_u64(sh.wo[w], 0);
+                    nfail += (uint32_t)__popcll(om);
+                    lv[w] &= ~om & ballot64(key[w] > scur);
+                }
+                __syncthreads();
+            }
+            // the picks, in any order, for the apply phase and the outputs
+            uint32_t n = 0, base = 0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                base += w < w4 ? (uint32_t)__popcll(lv[w]) : 0u;
+                n += (uint32_t)__popcll(lv[w]);
+            }
+            if (wave < 4) {
+                const unsigned long long lo = w4 == 0 ? lv[0] : w4 == 1 ? lv[1] : w4 == 2 ? lv[2] : lv[3];
+                const uint32_t pos = base + (uint32_t)__popcll(lo & below);
+                if ((lo >> lane) & 1ull) {
+                    sh.pk[pos] = q;
+                    sh.pk[kList + pos] = sh.lb[own];
+                    sh.pkey[pos] = k0;
+                }
+                if (wave == 0 && lane < kBlk && n + lane < (n + kBlk - 1) / kBlk * kBlk)
+                    sh.pk[kList + n + lane] = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
+                if (tid == 0)
+                    sh.npick = n;
+                if (clocks)
+                    tl.fails += nfail;
+            }
+        }
+        if (clocks)
+            tl.sub[2] += wall_clock64() - t_sub;
+        __syncthreads();
+        const int PN = (int)sh.npick;  // picks certified; the last round may need fewer
+        const int P = min(PN, job.m - j);
         if (P == 0) {
-            // impossible by construction (the largest bound is attained at round
-            // start); kept as a guard so a violated invariant cannot spin forever
+            // impossible by construction (the largest key is always free);
+            // kept as a guard so a violated invariant cannot spin forever
             if (tid == 0)
                 set_status(&a.hdr->sample_status, RFPS_ERR_INTERNAL);
             return false;
@@ -1183,124 +1424,105 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, int rank, 
         if (clocks) {
             const unsigned long long t = wall_clock64();
             tl.ph[2] += t - t_mark;
-            tl.sub[3] += t;  // from the end of the walk (subtracted there)
             t_mark = t;
         }
+        j_out = j;
+        n_out = P;
+        p_out = PN;
         j += P;
         if (j >= job.m)
             break;
 
         // =============== A: apply the round's picks to the true state ===============
-        // Lanes take picks k and k + 64 (the second set only when the round
-        // has more than 64), wavefronts take tiles, kApplyTiles at a time so
-        // that their sphere loads are in flight together.  A tile's test uses
-        // its current threshold (only its own update can lower it); the picks
-        // that survive update the tile's points (the minimum over picks does
-        // not depend on their order).  The sphere array is padded to whole
-        // passes with spheres that never pass, so the tests need no bounds
-        // and a pass branches only when some tile of it is hit: this loop is
-        // bound by the instructions one wavefront issues, not by LDS.
+        // Every wavefront takes its own tiles, so that its next lookahead
+        // needs no barrier.  The matrix cores test blocks of 16 tiles by 16
+        // picks (filter_row of the pruning threshold); a tile some pick
+        // passes is updated with the picks of the block (the minimum over
+        // picks does not depend on their order) and re-keyed.
         {
-            const int ka = lane < P ? lane : 0, kc = lane + kWave < P ? lane + kWave : 0;
-            const float sax = pkx[ka], say = pky[ka], saz = pkz[ka];
-            const float scx = pkx[kc], scy = pky[kc], scz = pkz[kc];
-            const unsigned long long kma = P >= kWave ? ~0ull : ((1ull << P) - 1ull);
-            const unsigned long long kmc =
-                P >= 2 * kWave ? ~0ull : P > kWave ? ((1ull << (P - kWave)) - 1ull) : 0ull;
-            constexpr int kT = kApplyTiles;
-            constexpr int kStep = kT * kWavesPerBlock;
-            auto pass = [&](auto two_c) {
-                constexpr bool TWO = decltype(two_c)::value;
-                for (int lt0 = kT * wave; lt0 < ntl; lt0 += kStep) {
-                    unsigned long long ma[kT], mc[kT];
-                    float4 sp[kT];
-#pragma unroll
-                    for (int v = 0; v < kT; ++v)
-                        sp[v] = tsph[lt0 + v];  // in the padding past the tiles
-                    unsigned long long any = 0;
-#pragma unroll
-                    for (int v = 0; v < kT; ++v) {
-                        const int lt = lt0 + v;
-                        ma[v] = ballot64(!(sqdist(sp[v].x, sp[v].y, sp[v].z, sax, say, saz) >= sp[v].w)) & kma;
-                        mc[v] = TWO ? ballot64(!(sqdist(sp[v].x, sp[v].y, sp[v].z, scx, scy, scz) >= sp[v].w)) & kmc
-                                    : 0ull;
-                        any |= ma[v] | mc[v];
-                        if (tele && lane == 0 && lt < ntl) {
-                            const unsigned long long nh = (unsigned long long)(__popcll(ma[v]) + __popcll(mc[v]));
-                            tl.tests += (unsigned long long)P;
-                            tl.pruned += (unsigned long long)P - nh;
-                            tl.visited += nh * (tmeta[lt] >> 16);
-                        }
-                    }
-                    if (!any)
+            const float osh = lg == 0 ? job.ox : lg == 1 ? job.oy : job.oz;
+            const float *sf = reinterpret_cast<const float *>(tsph);
+            const float *bf = reinterpret_cast<const float *>(sh.pk + kList);
+            const int npb = (P + kBlk - 1) / kBlk;
+            for (int rb = 0; rb < ntw; rb += kBlk) {
+                const float av = sf[(wb + rb + li) * 4 + lg];
+                const float av2 = lg == 3 ? 1.0f : -2.0f * (av - osh);
+                const float4 t4 = *reinterpret_cast<const float4 *>(&trow[wb + rb + 4 * lg]);
+                if (tele && lane == 0)
+                    tl.tests += (unsigned long long)P * (unsigned long long)min(kBlk, ntw - rb);
+                for (int cb = 0; cb < npb; ++cb) {
+                    const float bv = bf[(cb * kBlk + li) * 4 + lg];
+                    const f32x4 dd =
+                        __builtin_amdgcn_mfma_f32_16x16x4f32(av2, bv, f32x4{t4.x, t4.y, t4.z, t4.w}, 0, 0, 0);
+                    unsigned long long mr[4] = {ballot64(!(dd[0] >= 0.0f)), ballot64(!(dd[1] >= 0.0f)),
+                                                ballot64(!(dd[2] >= 0.0f)), ballot64(!(dd[3] >= 0.0f))};
+                    if (tele && lane == 0)
+                        tl.pruned += (unsigned long long)min(kBlk, P - cb * kBlk) * min(kBlk, ntw - rb) -
+                                     (unsigned long long)(__popcll(mr[0]) + __popcll(mr[1]) + __popcll(mr[2]) +
+                                                          __popcll(mr[3]));
+                    if (!(mr[0] | mr[1] | mr[2] | mr[3]))
                         continue;
-                    unsigned long long t_upd = 0;
-                    if (clocks) {
-                        t_upd = wall_clock64();
-                        for (int v = 0; v < kT; ++v)
-                            tl.apairs += (unsigned long long)(__popcll(ma[v]) + __popcll(mc[v]));
-                    }
+                    // (a tile that is never skipped passes the padding too)
+                    const unsigned long long cols = ballot64(cb * kBlk + li < P);
 #pragma unroll
-                    for (int v = 0; v < kT; ++v) {
-                        if (!(ma[v] | mc[v]))
-                            continue;
-                        const int lt = lt0 + v;
-                        const uint32_t meta = tmeta[lt];
-                        const uint32_t ls = meta & 0xffffu, cnt = meta >> 16;
-                        const bool valid = (uint32_t)lane < cnt;
-                        const uint32_t pp = ls + (valid ? lane : 0);
-                        const float x = px[pp], y = py[pp], z = pz[pp];
-                        float d = pd[pp];
-                        bool changed = false;
-                        for (int h = 0; h < (TWO ? 2 : 1); ++h) {
-                            unsigned long long mask = h ? mc[v] : ma[v];
-                            while (mask) {
-                                const int kk = (h ? kWave : 0) + (__ffsll((long long)mask) - 1);
-                                mask &= mask - 1;
-                                const float qx = pkx[kk], qy = pky[kk], qz = pkz[kk];
-                                if (valid) {
-                                    const float dx = x - qx, dy = y - qy, dz = z - qz;
-                                    const float xx = dx * dx, yy = dy * dy, zz = dz * dz;
-                                    const bool skip = use_skip && (xx >= d || yy >= d || zz >= d);
-                                    const float s2 = xx + yy;
-                                    float t = s2 + zz;
-                                    if (euclid && !skip && t < d)
-                                        t = sqrt_class_top(t);
-                                    if (!skip && t < d) {
-                                        d = t;
-                                        changed = true;
-                                    }
-                                    if (tele)
-                                        tl.skipped += skip;
+                    for (int r = 0; r < 4; ++r) {
+                        unsigned long long m = mr[r] & cols;
+                        while (m) {
+                            const int g = __builtin_ctzll(m) >> 4;
+                            uint32_t f = (uint32_t)(m >> (16 * g)) & 0xffffu;
+                            m &= ~(0xffffull << (16 * g));
+                            const int s = wb + rb + 4 * g + r;
+                            const uint32_t meta = uniform_u32(tmeta[s]);
+                            const uint32_t ls = meta & 0xffffu, cnt = meta >> 16;
+                            const bool valid = (uint32_t)lane < cnt;
+                            const uint32_t pp = ls + (valid ? lane : 0);
+                            const float4 q = pq[pp];
+                            float d = pd[pp];
+                            const float d0 = d;
+                            if (clocks)
+                                tl.apairs += (unsigned long long)__popc(f);
+                            if (tele && lane == 0)
+                                tl.visited += (unsigned long long)__popc(f) * cnt;
+                            while (f) {
+                                const int kk = cb * kBlk + __builtin_ctz(f);
+                                f &= f - 1;
+                                const float4 s4 = sh.pk[kk];
+                                if (tele && count_skip && valid) {
+                                    const float dx = q.x - s4.x, dy = q.y - s4.y, dz = q.z - s4.z;
+                                    tl.skipped += (dx * dx >= d || dy * dy >= d || dz * dz >= d) ? 1 : 0;
                                 }
+                                d = min_dist(d, sqdist(q.x, q.y, q.z, s4.x, s4.y, s4.z), euclid);
+                            }
+                            const bool changed = valid && d < d0;
+                            const unsigned long long um = ballot64(changed);
+                            if (tele && lane == 0) {
+                                tl.updated += (unsigned long long)__popcll(um);
+                                tl.resync += um != 0;
+                            }
+                            if (um) {
+                                if (changed)
+                                    pd[pp] = d;
+                                rekey(s, valid, d, __float_as_uint(q.w));
+                                if (clocks)
+                                    ++tl.arekeys;
                             }
                         }
-                        if (changed)
-                            pd[pp] = d;
-                        const unsigned long long um = __ballot(changed);
-                        if (tele && lane == 0) {
-                            tl.updated += (unsigned long long)__popcll(um);
-                            tl.resync += um != 0;
-                        }
-                        if (um)
-                            tile_rekey<4>(lane, lt, ls, cnt, d, po[pp], trad, tkey, tbest, tthr);
-                        if (clocks && um)
-                            ++tl.arekeys;
                     }
-                    if (clocks && t_upd)
-                        tl.sub[10] += wall_clock64() - t_upd;
                 }
-            };
-            if (P > kWave)
-                pass(std::true_type());
-            else
-                pass(std::false_type());
+            }
         }
-        if (clocks)
-            tl.sub[8] += wall_clock64() - t_mark;
+        if (clocks) {
+            const unsigned long long t = wall_clock64();
+            tl.sub[8] += t - t_mark;
+            tl.ph[3] += t - t_mark;
+        }
+    }
+    if (rank == 0 && n_out) {
         __syncthreads();
-        if (clocks)
-            tl.ph[3] += wall_clock64() - t_mark;
+        rank_out();
+        __syncthreads();
+        if (wave == 0)
+            write_out(lane);
     }
     tl.rounds += round;
     __syncthreads();  // LDS is reused by the next cloud
@@ -1344,7 +1566,7 @@ __device__ void flush_telemetry(IndexHeader *hdr, const RoundTele &tl, bool cloc
 // ---------------------------------------------------------------------------
 // Single cloud: one team made of the whole grid, agent-scope exchange.
 // ---------------------------------------------------------------------------
-template <int R, bool E, bool T>
+template <int NU, bool E, bool T>
 __device__ __forceinline__ void rounds_single(const RoundArgs &a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1355,9 +1577,9 @@ __device__ __forceinline__ void rounds_single(const RoundArgs &a)
     if (tid == 0)
         s_status = hdr->build_status | hdr->sample_status;
     __syncthreads();
-    if (s_status)
+    const int G = hdr->team_g, K = hdr->team_k, steps = hdr->team_steps;
+    if (s_status || (int)blockIdx.x >= G)
         return;
-    const bool tele = T && (a.flags & RFPS_F_TELEMETRY) != 0;
     const bool timed = T && (a.flags & (RFPS_F_TELEMETRY | RFPS_F_CLOCKS)) != 0;
     const bool clocks = timed && blockIdx.x == 0 && tid == 0;
     CloudJob job;
@@ -1368,10 +1590,19 @@ __device__ __forceinline__ void rounds_single(const RoundArgs &a)
     job.start = a.start;
     job.out_idx = a.out_idx;
     job.out_d2 = a.out_d2;
+    job.ox = (float)hdr->origin[0];
+    job.oy = (float)hdr->origin[1];
+    job.oz = (float)hdr->origin[2];
     uint32_t epoch = 0;
     RoundTele tl;
-    const bool ok = sample_cloud<R, Scope::Agent, E, T>(a, job, blockIdx.x, a.G, a.board, epoch, smem, sh, tl,
-                                                  (a.flags & RFPS_F_TRACE) != 0 && blockIdx.x == 0, clocks);
+    const bool trace = (a.flags & RFPS_F_TRACE) != 0 && blockIdx.x == 0;
+    bool ok;
+    if (NU == 2 && G * (int)slot_units((uint32_t)K) <= kRBlock)
+        ok = sample_cloud<Scope::Agent, 1, E, T>(a, job, blockIdx.x, G, K, steps, a.board, epoch, smem, sh, tl, trace,
+                                                 clocks);
+    else
+        ok = sample_cloud<Scope::Agent, NU, E, T>(a, job, blockIdx.x, G, K, steps, a.board, epoch, smem, sh, tl, trace,
+                                                  clocks);
     if (timed && ok) {
         flush_telemetry(hdr, tl, clocks);  // the counters stay 0 without RFPS_F_TELEMETRY
         if (blockIdx.x == 0 && tid == 0) {
@@ -1389,20 +1620,20 @@ __device__ __forceinline__ void rounds_single(const RoundArgs &a)
 // RFPS_F_TRACE): the default kernel carries no code of either.  Its machine
 // code is close to the instruction cache's size, and compiling the
 // instrumentation out of it shortens a round measurably.
-#define RFPS_ROUNDS_KERNEL(NAME, BODY, E, T)                                                                 \
-    template <int R>                                                                                          \
-    __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1))) void NAME(RoundArgs a)    \
+#define RFPS_ROUNDS_KERNEL(NAME, ...)                                                                         \
+    __global__ __launch_bounds__(kRBlock)                                                                     \
+        __attribute__((amdgpu_waves_per_eu(kRBlock / 256, kRBlock / 256))) void NAME(RoundArgs a)             \
     {                                                                                                         \
-        BODY<R, E, T>(a);                                                                                     \
-    }                                                                                                         \
-    template __global__ void NAME<2>(RoundArgs);                                                              \
-    template __global__ void NAME<3>(RoundArgs);                                                              \
-    template __global__ void NAME<4>(RoundArgs);                                                              \
-    template __global__ void NAME<8>(RoundArgs);
-RFPS_ROUNDS_KERNEL(k_rfps_rounds, rounds_single, false, false)
-RFPS_ROUNDS_KERNEL(k_rfps_rounds_euclid, rounds_single, true, false)
-RFPS_ROUNDS_KERNEL(k_rfps_rounds_tele, rounds_single, false, true)
-RFPS_ROUNDS_KERNEL(k_rfps_rounds_euclid_tele, rounds_single, true, true)
+        __VA_ARGS__(a);                                                                                       \
+    }
+RFPS_ROUNDS_KERNEL(k_rfps_rounds, rounds_single<2, false, false>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_wide, rounds_single<5, false, false>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_euclid, rounds_single<2, true, false>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_wide_euclid, rounds_single<5, true, false>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_tele, rounds_single<2, false, true>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_wide_tele, rounds_single<5, false, true>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_euclid_tele, rounds_single<2, true, true>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_wide_euclid_tele, rounds_single<5, true, true>)
 
 
 // ---------------------------------------------------------------------------
@@ -1415,7 +1646,7 @@ __device__ __forceinline__ uint32_t xcc_id()
     return __builtin_amdgcn_s_getreg((20) | (0 << 6) | ((16 - 1) << 11)) & 0xffu;
 }
 
-template <int R, bool E, bool I>
+template <bool E, bool I>
 __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1504,7 +1735,11 @@ __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
         job.start = bc.starts ? bc.starts[c] : 0;
         job.out_idx = a.out_idx + bc.out_offsets[c];
         job.out_d2 = a.out_d2 ? a.out_d2 + bc.out_offsets[c] : nullptr;
-        if (!sample_cloud<R, Scope::Xcd, E, I>(a, job, rank, T, board, epoch, smem, sh, tl, false, false))
+        const uint32_t *bb = a.cl_bb + 6 * (size_t)c;
+        job.ox = 0.5f * ord2f(bb[0]) + 0.5f * ord2f(bb[3]);
+        job.oy = 0.5f * ord2f(bb[1]) + 0.5f * ord2f(bb[4]);
+        job.oz = 0.5f * ord2f(bb[2]) + 0.5f * ord2f(bb[5]);
+        if (!sample_cloud<Scope::Xcd, 1, E, I>(a, job, rank, T, a.K, a.steps, board, epoch, smem, sh, tl, false, false))
             return;
     }
     if (tele) {
@@ -1514,10 +1749,10 @@ __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
     }
 }
 
-RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched, rounds_batched, false, false)
-RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched_euclid, rounds_batched, true, false)
-RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched_tele, rounds_batched, false, true)
-RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched_euclid_tele, rounds_batched, true, true)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched, rounds_batched<false, false>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched_euclid, rounds_batched<true, false>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched_tele, rounds_batched<false, true>)
+RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched_euclid_tele, rounds_batched<true, true>)
 #undef RFPS_ROUNDS_KERNEL
 
 // ---------------------------------------------------------------------------
@@ -1615,36 +1850,21 @@ hipError_t launch_exchange_probe(unsigned long long *board, int G, int W, int ro
 // ---------------------------------------------------------------------------
 // Host launchers
 // ---------------------------------------------------------------------------
-static const void *rounds_fn(int R, bool batched, bool euclid, bool tele)
+static const void *rounds_fn(const SampleLaunch &L, bool batched, bool wide_slots)
 {
-#define RFPS_ROUNDS_FN(K)                                                                                    \
-    (R == 2 ? reinterpret_cast<const void *>(K<2>) : R == 3 ? reinterpret_cast<const void *>(K<3>)          \
-     : R == 4                                            ? reinterpret_cast<const void *>(K<4>)            \
-     : R == 8                                            ? reinterpret_cast<const void *>(K<8>)            \
-                                                         : nullptr)
-    if (batched) {
-        if (tele)
-            return euclid ? RFPS_ROUNDS_FN(k_rfps_rounds_batched_euclid_tele)
-                          : RFPS_ROUNDS_FN(k_rfps_rounds_batched_tele);
-        return euclid ? RFPS_ROUNDS_FN(k_rfps_rounds_batched_euclid) : RFPS_ROUNDS_FN(k_rfps_rounds_batched);
-    }
-    if (tele)
-        return euclid ? RFPS_ROUNDS_FN(k_rfps_rounds_euclid_tele) : RFPS_ROUNDS_FN(k_rfps_rounds_tele);
-    return euclid ? RFPS_ROUNDS_FN(k_rfps_rounds_euclid) : RFPS_ROUNDS_FN(k_rfps_rounds);
-#undef RFPS_ROUNDS_FN
-}
-
-size_t rfps_rounds_static_lds(int R)
-{
-    size_t mx = 0;
-    for (int b = 0; b < 8; ++b) {
-        const void *fn = rounds_fn(R, (b & 1) != 0, (b & 2) != 0, (b & 4) != 0);
-        hipFuncAttributes attr;
-        if (!fn || hipFuncGetAttributes(&attr, fn) != hipSuccess)
-            return 0;
-        mx = attr.sharedSizeBytes > mx ? attr.sharedSizeBytes : mx;
-    }
-    return mx;
+    const int e = (L.flags & RFPS_F_SQRT) != 0, t = (L.flags & (RFPS_F_TELEMETRY | RFPS_F_TRACE | RFPS_F_CLOCKS)) != 0;
+#define RFPS_FN(K) reinterpret_cast<const void *>(K)
+    static const void *const one[2][2] = {{RFPS_FN(k_rfps_rounds), RFPS_FN(k_rfps_rounds_tele)},
+                                          {RFPS_FN(k_rfps_rounds_euclid), RFPS_FN(k_rfps_rounds_euclid_tele)}};
+    static const void *const wide[2][2] = {{RFPS_FN(k_rfps_rounds_wide), RFPS_FN(k_rfps_rounds_wide_tele)},
+                                           {RFPS_FN(k_rfps_rounds_wide_euclid), RFPS_FN(k_rfps_rounds_wide_euclid_tele)}};
+    static const void *const many[2][2] = {
+        {RFPS_FN(k_rfps_rounds_batched), RFPS_FN(k_rfps_rounds_batched_tele)},
+        {RFPS_FN(k_rfps_rounds_batched_euclid), RFPS_FN(k_rfps_rounds_batched_euclid_tele)}};
+#undef RFPS_FN
+    if (batched)
+        return many[e][t];
+    return wide_slots ? wide[e][t] : one[e][t];
 }
 
 static RoundArgs round_args(const IndexView &v, int m, int start, const SampleLaunch &L, int32_t *out_idx,
@@ -1670,9 +1890,11 @@ static RoundArgs round_args(const IndexView &v, int m, int start, const SampleLa
     a.n = v.n;
     a.m = m;
     a.start = start;
-    a.G = L.G;
     a.flags = L.flags;
-    a.lds_budget = L.lds_budget;
+    a.lds_budget = 0;
+    a.K = L.K ? L.K : 3;
+    a.steps = L.steps;
+    a.cl_bb = nullptr;
     a.bc = BatchCtl{};
     a.bstate = nullptr;
     a.tile_first = nullptr;
@@ -1683,20 +1905,23 @@ static RoundArgs round_args(const IndexView &v, int m, int start, const SampleLa
 hipError_t launch_rfps_rounds(const IndexView &v, int m, int start, const SampleLaunch &L, int32_t *out_idx,
                               float *out_d2, hipStream_t s)
 {
-    k_rounds_plan<<<(L.G + kBlock - 1) / kBlock, kBlock, 0, s>>>(v.hdr, v.tcnt, L.G, L.R, L.lds_budget);
+    RoundArgs a = round_args(v, m, start, L, out_idx, out_d2);
+    a.lds_budget = rounds_dynamic((uint32_t)L.max_lds);
+    // at most K + 1 units of a slot from every workgroup the launch may use
+    const int most = L.G * (int)slot_units((uint32_t)(L.K ? L.K : 3));
+    if (!a.lds_budget || L.K > kRWaves || most > 5 * kRBlock)
+        return hipErrorInvalidValue;
+    k_rounds_plan<<<1, kPlanBlock, 0, s>>>(v.hdr, v.tcnt, m, L.G, L.Gcap, L.fixed_g ? L.G : 0, L.K, L.R,
+                                           L.lds_budget, a.lds_budget);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || m <= 1)
         return e;
-    const void *fn = rounds_fn(L.R, false, (L.flags & RFPS_F_SQRT) != 0,
-                               (L.flags & (RFPS_F_TELEMETRY | RFPS_F_TRACE | RFPS_F_CLOCKS)) != 0);
-    if (!fn)
-        return hipErrorInvalidValue;
-    RoundArgs a = round_args(v, m, start, L, out_idx, out_d2);
+    const void *fn = rounds_fn(L, false, most > 2 * kRBlock);
     void *args[] = {&a};
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds_budget);
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds_budget);
     if (e != hipSuccess)
         return e;
-    return launch_persistent(fn, L.G, args, L.lds_budget, s);
+    return launch_persistent(fn, L.G, args, a.lds_budget, s, kRBlock);
 }
 
 // Batched: per-cloud capacity check for teams of bc.team_size workgroups,
@@ -1740,20 +1965,21 @@ hipError_t launch_rfps_rounds_batched(const IndexView &v, const SampleLaunch &L,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    const void *fn = rounds_fn(L.R, true, (L.flags & RFPS_F_SQRT) != 0,
-                               (L.flags & (RFPS_F_TELEMETRY | RFPS_F_TRACE | RFPS_F_CLOCKS)) != 0);
-    if (!fn)
-        return hipErrorInvalidValue;
+    const void *fn = rounds_fn(L, true, false);
     RoundArgs a = round_args(v, 0, 0, L, out_idx, out_d2);
     a.bc = v.bc;
     a.bstate = v.bstate;
     a.tile_first = v.tile_first;
     a.order = v.order;
+    a.cl_bb = v.cl_bb;
+    a.lds_budget = rounds_dynamic((uint32_t)L.max_lds);
+    if (!a.lds_budget)
+        return hipErrorInvalidValue;
     void *args[] = {&a};
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.lds_budget);
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds_budget);
     if (e != hipSuccess)
         return e;
-    e = launch_persistent(fn, L.G, args, L.lds_budget, s);
+    e = launch_persistent(fn, L.G, args, a.lds_budget, s, kRBlock);
     if (e != hipSuccess)
         return e;
     return launch_sample_finalize(v.hdr, v.bc.m_total, out_idx, out_d2, s);
