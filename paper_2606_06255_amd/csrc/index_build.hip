@@ -523,9 +523,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_reset(IndexHeader *hdr, BatchC
         for (int t = 0; t < kTeleFields; ++t)
             hdr->tele[t] = 0;
         st->joined = 0;
-        st->next = 0;
         for (int x = 0; x < kMaxXcds; ++x)
-            st->xcd_count[x] = 0;
+            st->next[x] = st->xcd_count[x] = 0;
     }
     for (int c = tid; c < bc.batch; c += nth) {
         for (int a = 0; a < 3; ++a) {
@@ -707,21 +706,6 @@ __global__ __launch_bounds__(kBlock) void k_tile_first(const uint32_t *__restric
     }
 }
 
-// Clouds by decreasing cost N_c * m_c, ties by index: the teams take them in
-// this order, so the longest jobs start first.
-__global__ void k_batch_order(BatchCtl bc, int32_t *order)
-{
-    for (int c = threadIdx.x; c < bc.batch; c += blockDim.x) {
-        const long long cc = (long long)(bc.offsets[c + 1] - bc.offsets[c]) * (long long)bc.m[c];
-        int rank = 0;
-        for (int d = 0; d < bc.batch; ++d) {
-            const long long cd = (long long)(bc.offsets[d + 1] - bc.offsets[d]) * (long long)bc.m[d];
-            rank += (cd > cc) || (cd == cc && d < c);
-        }
-        order[rank] = c;
-    }
-}
-
 hipError_t launch_build_batch(const IndexView &v, const float *xyz, hipStream_t s)
 {
     const int n = v.n, B = v.bc.batch;
@@ -760,7 +744,6 @@ hipError_t launch_build_batch(const IndexView &v, const float *xyz, hipStream_t 
         v.vstart, v.tbase, v.hdr, v.tile, v.xs, v.ys, v.zs, v.tstart, v.tcnt, v.tcx, v.tcy, v.tcz, v.trad);
     k_tile_first<<<std::min(blocks_for(n, kBlock), 1024), kBlock, 0, s>>>(v.tstart, v.orig, v.hdr, v.bc,
                                                                           v.tile_first);
-    k_batch_order<<<1, kBlock, 0, s>>>(v.bc, v.order);
     return hipGetLastError();
 }
 

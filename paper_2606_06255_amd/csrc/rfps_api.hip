@@ -368,7 +368,6 @@ rfps_status rfps_sample(const rfps_index *index, int32_t m, int32_t start, const
     L.Gcap = (!L.fixed_g && !single && index->n < (1 << 16)) ? std::max(1, all / 2) : L.G;
     L.K = (params && params->lookahead) ? params->lookahead : 0;
     L.R = single ? 0 : (L.K ? L.K : kDefaultLookahead);
-    L.steps = 0;
     if (!sampler_budget(*d, L))
         return RFPS_ERR_UNSUPPORTED;
     if (L.G > d->cus)
@@ -592,7 +591,7 @@ rfps_status rfps_sample_batched(const float *xyz, int32_t n, const int32_t *offs
     const int per_xcd = d->cus / kMaxXcds;
     const int T = (params && params->groups) ? params->groups : per_xcd;
     const long long teams = d->cus / std::max(T, 1);
-    if (T < 2 || per_xcd % T != 0 || teams * (2 * T + 1) * kMaxSlotWords > kBoardWords)
+    if ((per_xcd & (per_xcd - 1)) != 0 || T < 2 || per_xcd % T != 0 || teams * (2 * T + 1) * kMaxSlotWords > kBoardWords)
         return RFPS_ERR_UNSUPPORTED;
     SampleLaunch L;
     L.G = d->cus;
@@ -601,13 +600,13 @@ rfps_status rfps_sample_batched(const float *xyz, int32_t n, const int32_t *offs
     L.fixed_g = true;
     L.K = (params && params->lookahead) ? params->lookahead : 0;
     L.R = L.K ? L.K : kDefaultLookahead;
-    L.steps = 2;
     if (!sampler_budget(*d, L))
         return RFPS_ERR_UNSUPPORTED;
 
     IndexView v = make_view_l(ws, BL, n, fixed_n_vox, resolve_tile(params));
     v.bc.batch = batch;
     v.bc.team_size = T;
+    v.bc.fixed_team = params && params->groups;
     v.bc.per_xcd = per_xcd;
     v.bc.fixed_n_vox = fixed_n_vox;
     v.bc.shell_inv = shell_inv_of(params);

@@ -71,7 +71,8 @@ constexpr int kMaxBatch = 4096;  // clouds per batched call
 // Batch description, passed by value to the kernels.
 struct BatchCtl {
     int32_t batch;
-    int32_t team_size;       // T, workgroups sampling one cloud (divides per_xcd)
+    int32_t team_size;       // T, workgroups sampling one cloud, at most (divides per_xcd)
+    int32_t fixed_team;      // whether the caller asked for teams of T
     int32_t per_xcd;         // workgroups the launch places on every XCD
     int32_t fixed_n_vox;     // 0: per-cloud default rule
     double shell_inv;        // 1 / shell spacing, 0 without shells
@@ -84,8 +85,11 @@ struct BatchCtl {
 
 // Per-call device state of a batch (in the workspace, cleared before every call).
 struct BatchState {
-    uint32_t joined, next;
+    uint32_t joined;
+    uint32_t next[8];         // clouds taken of every level
     uint32_t xcd_count[kMaxXcds];
+    uint32_t level_first[8];  // first cloud of every level in the order
+    uint32_t level_k[8];      // candidates a workgroup publishes
 };
 
 // Device pointers into an index workspace (see layout_index in rfps_api.hip).
@@ -434,7 +438,6 @@ struct SampleLaunch {
     uint32_t lds_budget;  // on-chip bytes a workgroup's share may take (the capacity limit)
     int max_lds;          // bytes of LDS a workgroup may use
     int K;                // multi-pick sampler: candidates a workgroup publishes as asked for; 0 = by rule
-    int steps;            // lookahead steps of a wavefront (batched sampler)
 };
 // Static LDS of the one-pick sampler kernel (bytes).
 size_t rfps_sampler_static_lds();

@@ -92,6 +92,29 @@ RFPS_HOST_DEVICE inline TeamShape team_shape(uint32_t tiles, uint32_t m)
     return t;
 }
 
+// Batches: team sizes are per_xcd >> level.  A workgroup has two slots of the
+// largest size side by side on the board; the control words of the levels
+// follow.
+constexpr int kBatchLevels = 6;
+constexpr int kBatchSlotWords = 2 * 64;
+// Candidates a workgroup of a batch publishes, by level and (a whole XCD) by
+// the points a workgroup holds.  Few workgroups must publish many for a round
+// to settle many picks; a large team lists enough of few.  Measured with the
+// device full, ms for 4 | 6 | 8 | 15 candidates: 1,024 points on 32
+// workgroups 0.43 | 0.46 | 0.50 | -, 16,384 on 32 1.50 | 1.45 | 1.51 | -,
+// 50,000 on 32 3.23 | 2.83 | 2.80 | -, 65,536 on 32 - | - | 3.95 | 4.50, 8,192
+// on 2 - | - | 2.40 | 2.05, 16,384 on 4 - | - | 2.30 | 2.03.
+constexpr int kBatchK = 15;  // at most (a slot's words)
+RFPS_HOST_DEVICE inline int batch_k(int level, unsigned long long points_per_group)
+{
+    if (level > 2)
+        return kBatchK;
+    return level > 0 || points_per_group >= 1500u ? 8 : points_per_group >= 400u ? 6 : 4;
+}
+// Lookahead steps of a wavefront in a batch: 4 (2 cost up to 20 % where a
+// workgroup's share is full and gain 1 % where it is small; 8 gain nothing).
+constexpr int kBatchSteps = 4;
+
 // Bytes a workgroup's share may take by that rule: what a compute unit has
 // beside 6,496 bytes.
 constexpr uint32_t kRoundsReserve = 6496;

@@ -75,7 +75,6 @@ struct RoundArgs {
     int32_t n, m, start;
     uint32_t flags;
     uint32_t lds_budget;
-    int32_t K, steps;  // candidates a workgroup publishes per round, lookahead steps of a wavefront
     // batched mode
     BatchCtl bc;
     BatchState *bstate;
@@ -103,18 +102,6 @@ __device__ __forceinline__ uint32_t uniform_u32(uint32_t v)
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// Capacity plan of one team of G workgroups over the tiles [tb, te).
-__device__ __forceinline__ bool team_fits(const uint32_t *tcnt, uint32_t tb, uint32_t te, int G, int R,
-                                          uint32_t budget, int rank)
-{
-    uint32_t tiles = 0, pts = 0;
-    for (uint32_t t = tb + rank; t < te; t += G) {
-        ++tiles;
-        pts += tcnt[t];
-    }
-    return share_granted(tiles, pts, G, R, budget);
-}
 
 // Plan of a single cloud: checks the capacity of the team of Gcap workgroups
 // (R candidates) the caller's parameters stand for, then settles the shape
@@ -213,13 +200,20 @@ __device__ __forceinline__ unsigned long long bload(const unsigned long long *p)
 constexpr uint32_t kAbortTag = 0xffffu;
 __device__ __forceinline__ uint32_t tag_of(uint32_t epoch) { return epoch % 65534u + 1u; }
 
+// A team's slots: rank r's slot of exchange e is at
+// base + (e & 1) * par_words + r * slot_words.
+struct Board {
+    unsigned long long *base;
+    uint32_t slot_words, par_words;
+};
+
 template <Scope S>
-__device__ void publish_abort_tags(unsigned long long *board, int G, int rank, int K)
+__device__ void publish_abort_tags(const Board &bd, int rank, int K)
 {
-    const size_t words = slot_units(K) * kUnit;
-    for (int par = 0; par < 2; ++par)
-        for (size_t w = 0; w < words; ++w)
-            bstore<S>(board + ((size_t)par * G + rank) * words + w, (unsigned long long)kAbortTag << 48);
+    const uint32_t words = slot_units(K) * kUnit;
+    for (uint32_t par = 0; par < 2; ++par)
+        for (uint32_t w = 0; w < words; ++w)
+            bstore<S>(bd.base + par * bd.par_words + rank * bd.slot_words + w, (unsigned long long)kAbortTag << 48);
 }
 
 // Reads one or two units (32 bytes each) past the L1, all loads in flight;
@@ -365,7 +359,7 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v,
 // exchange failed (abort).
 template <Scope S, int NU, bool E, bool T>
 __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int rank, const int G, const int K,
-                             const int steps, unsigned long long *board, uint32_t &epoch, unsigned char *smem,
+                             const int steps, const Board &board, uint32_t &epoch, unsigned char *smem,
                              RoundShared &sh, RoundTele &tl, bool record_trace, bool clocks)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -441,7 +435,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
             set_status(&a.hdr->sample_status, RFPS_ERR_INTERNAL);
             // the rest of the team must not wait for this workgroup
             if (!solo)
-                publish_abort_tags<S>(board, G, rank, K);
+                publish_abort_tags<S>(board, rank, K);
         }
         return false;
     }
@@ -507,9 +501,8 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
         const int g = e / units, s = e - g * units;
         uin[u] = e < total;
         ubound[u] = !solo && s == K;
-        upos[u] = uin[u] ? (uint32_t)(e * kUnit) : 0u;
+        upos[u] = uin[u] ? g * board.slot_words + s * kUnit : 0u;
     }
-    const size_t par_words = (size_t)G * units * kUnit;
     const unsigned long long below = lane ? (~0ull >> (kWave - lane)) : 0ull;
 
     unsigned long long t_mark = 0;
@@ -790,7 +783,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                 const int nr = kRWaves * steps, c0 = wave * steps;
                 const unsigned long long kq = lane < nr ? sh.rkey[lane] : 0ull;
                 const unsigned long long gb = sh.gb[round & 1u];
-                unsigned long long *slot = board + (epoch & 1u) * par_words + (size_t)rank * (units * kUnit);
+                unsigned long long *slot = board.base + (epoch & 1u) * board.par_words + rank * board.slot_words;
                 const unsigned long long tag64 = (unsigned long long)tag << 48;
                 for (int s = 0; s < steps; ++s) {
                     const int c = c0 + s;
@@ -809,7 +802,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
             }
             if (rank == 0 && n_out)
                 rank_out();
-            const unsigned long long *sbase = board + (epoch & 1u) * par_words;
+            const unsigned long long *sbase = board.base + (epoch & 1u) * board.par_words;
             unsigned long long b = 0;
             unsigned long long t_first = 0;
             bool lost = false;
@@ -883,7 +876,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
             if (sh.abort) {
                 if (tid == 0) {
                     set_status(&a.hdr->sample_status, RFPS_ERR_TIMEOUT);
-                    publish_abort_tags<S>(board, G, rank, K);
+                    publish_abort_tags<S>(board, rank, K);
                 }
                 return false;
             }
@@ -1596,12 +1589,14 @@ __device__ __forceinline__ void rounds_single(const RoundArgs &a)
     uint32_t epoch = 0;
     RoundTele tl;
     const bool trace = (a.flags & RFPS_F_TRACE) != 0 && blockIdx.x == 0;
+    const uint32_t words = slot_units((uint32_t)K) * kUnit;
+    const Board board = {a.board, words, (uint32_t)G * words};
     bool ok;
     if (NU == 2 && G * (int)slot_units((uint32_t)K) <= kRBlock)
-        ok = sample_cloud<Scope::Agent, 1, E, T>(a, job, blockIdx.x, G, K, steps, a.board, epoch, smem, sh, tl, trace,
+        ok = sample_cloud<Scope::Agent, 1, E, T>(a, job, blockIdx.x, G, K, steps, board, epoch, smem, sh, tl, trace,
                                                  clocks);
     else
-        ok = sample_cloud<Scope::Agent, NU, E, T>(a, job, blockIdx.x, G, K, steps, a.board, epoch, smem, sh, tl, trace,
+        ok = sample_cloud<Scope::Agent, NU, E, T>(a, job, blockIdx.x, G, K, steps, board, epoch, smem, sh, tl, trace,
                                                   clocks);
     if (timed && ok) {
         flush_telemetry(hdr, tl, clocks);  // the counters stay 0 without RFPS_F_TELEMETRY
@@ -1638,8 +1633,15 @@ RFPS_ROUNDS_KERNEL(k_rfps_rounds_wide_euclid_tele, rounds_single<5, true, true>)
 
 // ---------------------------------------------------------------------------
 // Batches: teams of T workgroups, all on one XCD (found from the hardware
-// XCC id at run time), exchange through that XCD's L2; every team takes the
-// next cloud from a queue ordered by decreasing cost until it is empty.
+// XCC id at run time), exchange through that XCD's L2.  The plan gives every
+// cloud a team size (a power of two, a level) and orders the clouds by
+// decreasing size and cost.  All workgroups of an XCD start as one team of
+// the largest level; a team takes the level's clouds until none is left and
+// then splits in two for the next level, down to single workgroups.  Teams
+// never join again, so a level's control word, once it says "no more", stays.
+// Measured against one team of a whole XCD per cloud: 64 clouds of 512 to
+// 4,096 points 2.18 -> 0.78 ms, 32 clouds of 8k to 120k points 16.1 -> 9.8 ms
+// (then bound by the workgroups' time: the device is full until the end).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t xcc_id()
 {
@@ -1685,34 +1687,42 @@ __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
     __syncthreads();
     if (s_status || !s_ok)
         return;
-    const int T = bc.team_size;
-    const int team = (int)s_xcc * (bc.per_xcd / T) + (int)s_xrank / T;
-    const int rank = (int)s_xrank % T;
-    unsigned long long *board = a.board + (size_t)team * (2 * T + 1) * kMaxSlotWords;
-    unsigned long long *ctl = board + (size_t)2 * T * kMaxSlotWords;  // the team's control slot
+    const int per_xcd = bc.per_xcd, me = (int)s_xcc * per_xcd + (int)s_xrank;
+    unsigned long long *const ctl = a.board + (size_t)kMaxGroups * kBatchSlotWords;
     const bool tele = I && (a.flags & RFPS_F_TELEMETRY) != 0;
     RoundTele tl;
+    unsigned long long led = 0;  // rounds of the clouds this workgroup led
     uint32_t epoch = 0, turn = 0;
-    for (;;) {
-        // The team leader takes the next cloud that needs an exchange and
-        // posts it.  Every posted cloud costs at least one exchange, which the
-        // leader cannot finish before every member has read the post, so a
-        // post is never overwritten unread.
+    int lev = 0;
+    while (lev < kBatchLevels && (per_xcd >> lev) > 0) {
+        const int T = per_xcd >> lev, rank = (int)s_xrank & (T - 1);
+        const uint32_t first = st->level_first[lev], last = st->level_first[lev + 1];
+        if (first == last) {
+            ++lev;
+            continue;
+        }
+        // The team leader takes the level's next cloud that needs an exchange
+        // and posts it.  Every posted cloud costs at least one exchange, which
+        // the leader cannot finish before every member has read the post, and
+        // nothing follows the post that ends the level, so a post is never
+        // overwritten unread.
         ++turn;
         if (tid == 0) {
+            unsigned long long *word = ctl + (size_t)lev * kMaxGroups + (me - rank);
             if (rank == 0) {
                 uint32_t q;
                 do {
-                    q = atomicAdd(&st->next, 1u);
-                } while (q < (uint32_t)bc.batch && bc.m[a.order[q]] < 2);
-                bstore<Scope::Xcd>(ctl, ((unsigned long long)turn << 32) | q);
+                    q = first + atomicAdd(&st->next[lev], 1u);
+                } while (q < last && bc.m[a.order[q]] < 2);
+                if (T > 1)
+                    bstore<Scope::Xcd>(word, ((unsigned long long)turn << 32) | min(q, last));
                 s_cloud = q;
             } else {
                 uint32_t spin = 0;
                 unsigned long long v = 0;
                 for (; spin < kSpinLimit; ++spin) {
                     binvalidate<Scope::Xcd>();
-                    v = bload<Scope::Xcd>(ctl);
+                    v = bload<Scope::Xcd>(word);
                     if ((uint32_t)(v >> 32) == turn)
                         break;
                 }
@@ -1724,8 +1734,12 @@ __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
         __syncthreads();
         const uint32_t q = s_cloud;
         __syncthreads();
-        if (q >= (uint32_t)bc.batch)
-            break;
+        if (q == 0xffffffffu)
+            return;
+        if (q >= last) {
+            ++lev;
+            continue;
+        }
         const int c = a.order[q];
         CloudJob job;
         job.tb = a.tile_first[c];
@@ -1739,13 +1753,22 @@ __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
         job.ox = 0.5f * ord2f(bb[0]) + 0.5f * ord2f(bb[3]);
         job.oy = 0.5f * ord2f(bb[1]) + 0.5f * ord2f(bb[4]);
         job.oz = 0.5f * ord2f(bb[2]) + 0.5f * ord2f(bb[5]);
-        if (!sample_cloud<Scope::Xcd, 1, E, I>(a, job, rank, T, a.K, a.steps, board, epoch, smem, sh, tl, false, false))
+        // a workgroup's two slots lie side by side, so a team's slots are the
+        // slots of the teams it splits into.  K never falls from a level to
+        // the next (k_batch_levels): every word a team reads is rewritten at
+        // every second exchange of its members, whatever team they were in.
+        const Board board = {a.board + (size_t)(me - rank) * kBatchSlotWords, (uint32_t)kBatchSlotWords,
+                             (uint32_t)kMaxSlotWords};
+        const unsigned long long r0 = tl.rounds;
+        if (!sample_cloud<Scope::Xcd, 1, E, I>(a, job, rank, T, (int)st->level_k[lev], kBatchSteps, board, epoch, smem, sh,
+                                               tl, false, false))
             return;
+        led += rank == 0 ? tl.rounds - r0 : 0ull;
     }
     if (tele) {
         flush_telemetry(hdr, tl, false);
-        if (rank == 0 && tid == 0)
-            atomicAdd(&hdr->tele[kTeleExchanges], tl.rounds);
+        if (tid == 0)
+            atomicAdd(&hdr->tele[kTeleExchanges], led);
     }
 }
 
@@ -1892,8 +1915,6 @@ static RoundArgs round_args(const IndexView &v, int m, int start, const SampleLa
     a.start = start;
     a.flags = L.flags;
     a.lds_budget = 0;
-    a.K = L.K ? L.K : 3;
-    a.steps = L.steps;
     a.cl_bb = nullptr;
     a.bc = BatchCtl{};
     a.bstate = nullptr;
@@ -1924,44 +1945,165 @@ hipError_t launch_rfps_rounds(const IndexView &v, int m, int start, const Sample
     return launch_persistent(fn, L.G, args, a.lds_budget, s, kRBlock);
 }
 
-// Batched: per-cloud capacity check for teams of bc.team_size workgroups,
-// then the first output of every cloud (its start, at distance +inf) and the
-// counters the sampler does not keep.
-__global__ __launch_bounds__(kBlock) void k_batch_plan(IndexHeader *hdr, const uint32_t *__restrict__ tcnt,
-                                                       BatchCtl bc, const uint32_t *__restrict__ tile_first, int R,
-                                                       uint32_t budget, int32_t *out_idx, float *out_d2)
+// Batched plan, one workgroup per cloud: checks the cloud's capacity for a
+// team of bc.team_size workgroups, finds the smallest team whose shares fit
+// the sampler's LDS (bc.team_size itself when the caller asked for it), and
+// writes the cloud's first output (its start, at distance +inf).  The counters
+// the sampler does not keep are set by the first workgroup.
+constexpr int kBatchPlanBlock = 256;
+__global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr, const uint32_t *__restrict__ tcnt,
+                                                                BatchCtl bc, const uint32_t *__restrict__ tile_first,
+                                                                int R, uint32_t budget, uint32_t lds, uint32_t *cl_team,
+                                                                int32_t *out_idx, float *out_d2)
 {
+    // tiles and points by tile number modulo the largest team: a smaller
+    // team's shares are sums of them
+    __shared__ uint32_t s_tiles[kMaxGroups], s_pts[kMaxGroups], s_big[kBatchLevels];
     if (hdr->build_status)
         return;
-    const int T = bc.team_size;
-    const int total = bc.batch * T;
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x, nth = gridDim.x * blockDim.x;
-    for (int w = tid; w < total; w += nth) {
-        const int c = w / T, r = w % T;
-        if (!team_fits(tcnt, tile_first[c], tile_first[c + 1], T, R, budget, r))
-            set_status(&hdr->sample_status, RFPS_ERR_CAPACITY);
+    const int tid = threadIdx.x, c = blockIdx.x, X = bc.per_xcd, T = bc.team_size;
+    s_tiles[tid] = s_pts[tid] = 0u;
+    if (tid < kBatchLevels)
+        s_big[tid] = 0u;
+    __syncthreads();
+    const uint32_t tb = tile_first[c], te = tile_first[c + 1];
+    for (uint32_t t = tb + tid; t < te; t += kBatchPlanBlock) {
+        atomicAdd(&s_tiles[(t - tb) % (uint32_t)X], 1u);
+        atomicAdd(&s_pts[(t - tb) % (uint32_t)X], tcnt[t]);
     }
-    for (int c = tid; c < bc.batch; c += nth) {
+    __syncthreads();
+    for (int lev = 0; lev < kBatchLevels && (X >> lev) > 0; ++lev) {
+        const int t = X >> lev;
+        if (tid >= t)
+            continue;
+        uint32_t tiles = 0, pts = 0;
+        for (int r = tid; r < X; r += t) {
+            tiles += s_tiles[r];
+            pts += s_pts[r];
+        }
+        if (t == T && !share_granted(tiles, pts, T, R, budget))
+            set_status(&hdr->sample_status, RFPS_ERR_CAPACITY);
+        if (pts > 65535u || rounds_lds_need(tiles, pts) > lds)
+            s_big[lev] = 1u;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int lev = 0;
+        if (bc.fixed_team)
+            while ((X >> lev) > T)
+                ++lev;
+        else
+            while (lev + 1 < kBatchLevels && (X >> (lev + 1)) > 0 && !s_big[lev + 1])
+                ++lev;
+        cl_team[c] = (uint32_t)lev;
         const uint32_t o = bc.out_offsets[c];
         out_idx[o] = bc.starts ? bc.starts[c] : 0;
         if (out_d2)
             out_d2[o] = INFINITY;
+        if (c == 0)
+            hdr->tele[1] = hdr->n_tiles;
+        if (bc.m[c] > 2)
+            atomicAdd(&hdr->tele[0], (unsigned long long)(bc.m[c] - 2));
+    }
+}
+
+// Team sizes and order of the clouds.  A smaller team spends less of the
+// device on a cloud (a workgroup's lookahead and merge are the same for any
+// share), so with more clouds than the device holds at once every cloud keeps
+// its smallest team; otherwise the teams grow, the costliest clouds' first,
+// until the device is full.  The clouds are then ordered by team, and inside
+// a level by decreasing cost N_c m_c (ties by index).
+// Measured, sampling time per cloud with the device full (room, 16,384 ->
+// 4,096): teams of 4 52 us, 8 65, 16 96, 32 172; and latency of one cloud
+// (4,096 -> 1,024): teams of 2 1.3 ms, 4 0.94, 8 0.76, 16 0.67, 32 0.62.
+constexpr int kBatchOrderBlock = 1024;
+__global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *hdr, BatchCtl bc, BatchState *st,
+                                                                   const uint32_t *__restrict__ cl_team, int K,
+                                                                   int32_t *order)
+{
+    __shared__ unsigned long long s_key[kMaxBatch];
+    __shared__ uint32_t s_sum, s_cnt[kBatchLevels];
+    __shared__ unsigned long long s_pts;  // points of the largest level's clouds
+    if (hdr->build_status)
+        return;
+    const int tid = threadIdx.x, B = bc.batch, X = bc.per_xcd;
+    const uint32_t all = (uint32_t)(X * kMaxXcds);
+    auto cost = [&](int c) {
+        return (unsigned long long)(bc.offsets[c + 1] - bc.offsets[c]) * (unsigned long long)bc.m[c];
+    };
+    // level of a cloud whose smallest team is `least`, teams holding 2^(e / 8)
+    // of cost per workgroup
+    auto level_at = [&](uint32_t least, float f, int e) {
+        int lev = (int)least;
+        while (lev > 0 && (float)(X >> (lev - 1)) * exp2f(0.125f * (float)e) <= f)
+            --lev;
+        return lev;
+    };
+    int e = 8 * 64;
+    if (!bc.fixed_team && B <= (int)all) {
+        // the smallest such cost that leaves a place for every team
+        const uint32_t least = tid < B ? cl_team[tid] : 0u;
+        const float f = tid < B ? (float)cost(tid) : 0.0f;
+        int lo = 0, hi = e;  // hi: every cloud keeps its smallest team
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (tid == 0)
+                s_sum = 0u;
+            __syncthreads();
+            if (tid < B)
+                atomicAdd(&s_sum, (uint32_t)(X >> level_at(least, f, mid)));
+            __syncthreads();
+            if (s_sum <= all)
+                hi = mid;
+            else
+                lo = mid + 1;
+            __syncthreads();
+        }
+        e = hi;
+    }
+    if (tid < kBatchLevels)
+        s_cnt[tid] = 0u;
+    if (tid == 0)
+        s_pts = 0ull;
+    __syncthreads();
+    for (int c = tid; c < B; c += kBatchOrderBlock) {
+        const int lev = level_at(cl_team[c], (float)cost(c), e);
+        s_key[c] = ((unsigned long long)(kBatchLevels - lev) << 56) | cost(c);
+        atomicAdd(&s_cnt[lev], 1u);
+        if (lev == 0)
+            atomicAdd(&s_pts, (unsigned long long)(bc.offsets[c + 1] - bc.offsets[c]));
+    }
+    __syncthreads();
+    for (int c = tid; c < B; c += kBatchOrderBlock) {
+        const unsigned long long k = s_key[c];
+        int rank = 0;
+        for (int d = 0; d < B; ++d)
+            rank += (s_key[d] > k) || (s_key[d] == k && d < c);
+        order[rank] = c;
     }
     if (tid == 0) {
-        unsigned long long it = 0;
-        for (int c = 0; c < bc.batch; ++c)
-            it += bc.m[c] > 2 ? (unsigned long long)(bc.m[c] - 2) : 0ull;
-        hdr->tele[0] = it;
-        hdr->tele[1] = hdr->n_tiles;
+        uint32_t at = 0;
+        for (int lev = 0; lev < kBatchLevels; ++lev) {
+            st->level_first[lev] = at;
+            at += s_cnt[lev];
+            const unsigned long long groups = lev ? 1ull : (unsigned long long)max(s_cnt[0], 1u) * (unsigned)X;
+            st->level_k[lev] = (uint32_t)(K ? K : batch_k(lev, s_pts / groups));
+        }
+        st->level_first[kBatchLevels] = at;
     }
 }
 
 hipError_t launch_rfps_rounds_batched(const IndexView &v, const SampleLaunch &L, int32_t *out_idx,
                                       float *out_d2, hipStream_t s)
 {
-    const int total = v.bc.batch * v.bc.team_size;
-    k_batch_plan<<<std::min((total + kBlock - 1) / kBlock, 1024), kBlock, 0, s>>>(
-        v.hdr, v.tcnt, v.bc, v.tile_first, L.R, L.lds_budget, out_idx, out_d2);
+    // (the trace area is free: batches are not traced)
+    uint32_t *cl_team = reinterpret_cast<uint32_t *>(v.trace);
+    const uint32_t lds = rounds_dynamic((uint32_t)L.max_lds);
+    if (!lds || L.K > kBatchK || v.bc.per_xcd * kMaxXcds > kMaxGroups || v.bc.per_xcd >> (kBatchLevels - 1) > 1)
+        return hipErrorInvalidValue;
+    k_batch_plan<<<v.bc.batch, kBatchPlanBlock, 0, s>>>(v.hdr, v.tcnt, v.bc, v.tile_first, L.R, L.lds_budget, lds,
+                                                        cl_team, out_idx, out_d2);
+    k_batch_levels<<<1, kBatchOrderBlock, 0, s>>>(v.hdr, v.bc, v.bstate, cl_team, L.K, v.order);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -1972,9 +2114,7 @@ hipError_t launch_rfps_rounds_batched(const IndexView &v, const SampleLaunch &L,
     a.tile_first = v.tile_first;
     a.order = v.order;
     a.cl_bb = v.cl_bb;
-    a.lds_budget = rounds_dynamic((uint32_t)L.max_lds);
-    if (!a.lds_budget)
-        return hipErrorInvalidValue;
+    a.lds_budget = lds;
     void *args[] = {&a};
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds_budget);
     if (e != hipSuccess)
