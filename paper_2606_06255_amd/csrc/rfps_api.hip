@@ -66,9 +66,9 @@ const DeviceInfo *device_info()
 // Index workspace layout.  Every segment is 256-byte aligned.  A batched
 // workspace appends the per-cloud arrays to the index of all its points.
 struct IndexLayout {
-    size_t hdr, keyA, keyB, valA, valB, xs, ys, zs, inv, flags, hscan, vstart, tcount, tbase, tstart, tcnt, tcx,
+    size_t hdr, keyA, keyB, valA, valB, xs, ys, zs, inv, flags, hscan, tcount, tbase, tstart, tcnt, tcx,
         tcy, tcz, trad, partials, hist, board, trace, total;
-    size_t cl_pmin, cl_L, cl_bb, cl_nvox, cl_base, cl_out, tile_first, order, bstate;
+    size_t cl_team, cl_bb, cl_nvox, cl_base, cl_out, tile_first, order, bstate;
     int radix_passes, nblk, batch;
 };
 
@@ -110,7 +110,7 @@ IndexLayout layout_common(int n, int passes, int batch)
     L.inv = take(4 * N);
     L.flags = take(4 * N);
     L.hscan = take(4 * N);
-    L.vstart = take(4 * (N + 1));
+    take(4 * (N + 1));  // not used
     L.tcount = take(4 * N);
     L.tbase = take(4 * N);
     L.tstart = take(4 * N);
@@ -124,8 +124,8 @@ IndexLayout layout_common(int n, int passes, int batch)
     L.board = take(8 * (size_t)kBoardWords);
     L.trace = take(8 * (size_t)2 * kTraceCap);
     const size_t B = (size_t)batch;
-    L.cl_pmin = take(24 * B);
-    L.cl_L = take(8 * B);
+    take(24 * B);  // not used; workspace sizes stay as they are
+    L.cl_team = take(8 * B);
     L.cl_bb = take(24 * B);
     L.cl_nvox = take(4 * B);
     L.cl_base = take(4 * (B + 1));
@@ -170,7 +170,6 @@ IndexView make_view_l(void *ws, const IndexLayout &L, int n, int n_vox, int tile
     v.inv = reinterpret_cast<uint32_t *>(b + L.inv);
     v.flags = reinterpret_cast<uint32_t *>(b + L.flags);
     v.hscan = reinterpret_cast<uint32_t *>(b + L.hscan);
-    v.vstart = reinterpret_cast<uint32_t *>(b + L.vstart);
     v.tcount = reinterpret_cast<uint32_t *>(b + L.tcount);
     v.tbase = reinterpret_cast<uint32_t *>(b + L.tbase);
     v.tstart = reinterpret_cast<uint32_t *>(b + L.tstart);
@@ -191,8 +190,7 @@ IndexView make_view_l(void *ws, const IndexLayout &L, int n, int n_vox, int tile
     v.shell_cap = 1;
     v.batch = L.batch;
     v.bc = BatchCtl{};
-    v.cl_pmin = reinterpret_cast<double *>(b + L.cl_pmin);
-    v.cl_L = reinterpret_cast<double *>(b + L.cl_L);
+    v.cl_team = reinterpret_cast<uint32_t *>(b + L.cl_team);
     v.cl_bb = reinterpret_cast<uint32_t *>(b + L.cl_bb);
     v.cl_nvox = reinterpret_cast<uint32_t *>(b + L.cl_nvox);
     v.cl_base = reinterpret_cast<uint32_t *>(b + L.cl_base);

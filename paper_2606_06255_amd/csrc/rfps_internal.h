@@ -99,9 +99,8 @@ struct IndexView {
     uint32_t *skey, *orig;                // sorted voxel ids / original indices (alias A or B)
     float *xs, *ys, *zs;                  // sorted coordinates (structure of arrays)
     uint32_t *inv;                        // inv[orig] = sorted position
-    uint32_t *flags, *hscan;              // voxel head flags and their exclusive scan
-    uint32_t *vstart;                     // [K+1] voxel starts in sorted order
-    uint32_t *tcount, *tbase;             // tiles per voxel and its exclusive scan
+    uint32_t *flags, *hscan;              // scratch, n words each
+    uint32_t *tcount, *tbase;             // tiles and voxels of every block of sorted positions
     uint32_t *tstart, *tcnt;              // tile start (sorted position) and size
     float *tcx, *tcy, *tcz, *trad;        // tile sphere centre and radius (rounded up)
     uint32_t *partials;                   // scan partial sums
@@ -114,7 +113,7 @@ struct IndexView {
     // batched index only (batch > 0)
     int32_t batch;
     BatchCtl bc;
-    double *cl_pmin, *cl_L;               // [batch][3], [batch] grid of every cloud
+    uint32_t *cl_team;                    // [batch] level of the smallest team that fits every cloud
     uint32_t *cl_bb;                      // [batch][6] order-preserving bounding boxes
     uint32_t *cl_nvox, *cl_base;          // [batch] bins per axis, [batch+1] first key of every cloud
     uint32_t *tile_first;                 // [batch+1] first tile of every cloud
@@ -426,8 +425,6 @@ __device__ __forceinline__ void publish_abort(unsigned long long *board, int G, 
 hipError_t launch_build_index(const IndexView &v, const float *xyz, hipStream_t s);
 hipError_t launch_gather_xyz(const float *xyz, int n, const int32_t *idx, int m, float *out, hipStream_t s);
 hipError_t launch_sqrt_out(float *d, int m, hipStream_t s);
-hipError_t launch_scan(const uint32_t *in, uint32_t *out, int n, uint32_t *partials, uint32_t *total,
-                       hipStream_t s);
 
 struct SampleLaunch {
     int G;                // workgroups launched
@@ -533,9 +530,14 @@ __host__ __device__ inline int default_n_vox_rule(int n)
     const int cand[11] = {8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256};
     const double target = sqrt((double)(n > 0 ? n : 1) / 40.0);
     int best = cand[0];
-    for (int q = 0; q < 11; ++q)
-        if (fabs(log((double)cand[q] / target)) < fabs(log((double)best / target)))
+    double least = fabs(log((double)best / target));
+    for (int q = 1; q < 11; ++q) {
+        const double v = fabs(log((double)cand[q] / target));
+        if (v < least) {
+            least = v;
             best = cand[q];
+        }
+    }
     return best;
 }
 

@@ -391,15 +391,19 @@ size_t rfps_sampler_static_lds()
 hipError_t launch_rfps_sample(const IndexView &v, int m, int start, const SampleLaunch &L, int32_t *out_idx,
                               float *out_d2, hipStream_t s)
 {
-    k_sample_reset<<<4, kBlock, 0, s>>>(v.hdr, v.board, L.G, start, out_idx, out_d2, m);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
+    const bool rounds = L.R > 0 && !(L.flags & RFPS_F_UNFUSED);
+    hipError_t e = hipSuccess;
+    if (!rounds) {  // (the multi-pick sampler's plan does this itself)
+        k_sample_reset<<<4, kBlock, 0, s>>>(v.hdr, v.board, L.G, start, out_idx, out_d2, m);
+        e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
     if (L.flags & RFPS_F_UNFUSED) {
         e = launch_rfps_unfused(v, m, start, L.flags, out_idx, out_d2, s);
         if (e != hipSuccess)
             return e;
-    } else if (L.R > 0) {
+    } else if (rounds) {
         e = launch_rfps_rounds(v, m, start, L, out_idx, out_d2, s);
         if (e != hipSuccess)
             return e;

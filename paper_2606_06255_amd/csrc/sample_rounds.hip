@@ -110,14 +110,35 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // sampler's LDS.  K0 as asked for, or 0.  One workgroup.
 constexpr int kPlanBlock = 1024;
 __global__ __launch_bounds__(kPlanBlock) void k_rounds_plan(IndexHeader *hdr, const uint32_t *__restrict__ tcnt,
-                                                            int m, int Gall, int Gcap, int G0, int K0, int R,
-                                                            uint32_t budget, uint32_t lds)
+                                                            unsigned long long *board, int m, int start,
+                                                            int32_t *out_idx, float *out_d2, int Gall, int Gcap,
+                                                            int G0, int K0, int R, uint32_t budget, uint32_t lds)
 {
     __shared__ uint32_t s_tiles[kMaxGroups], s_pts[kMaxGroups];
-    __shared__ uint32_t s_bad, s_big;
-    if (hdr->build_status)
-        return;
+    __shared__ uint32_t s_big, s_refused;
     const int tid = threadIdx.x;
+    if (blockIdx.x) {
+        // the slots a team of Gall workgroups may use
+        const int words = 2 * Gall * kMaxSlotWords;
+        for (int w = (blockIdx.x - 1) * kPlanBlock + tid; w < words; w += (gridDim.x - 1) * kPlanBlock)
+            board[w] = 0ull;
+        return;
+    }
+    if (tid == 0) {
+        s_refused = 0u;
+        hdr->last_m = (uint32_t)m;
+        hdr->trace_n = 0;
+        out_idx[0] = start;
+        if (out_d2)
+            out_d2[0] = INFINITY;
+    }
+    if (tid < kTeleFields)
+        hdr->tele[tid] = 0;
+    if (hdr->build_status) {
+        if (tid == 0)
+            hdr->sample_status = 0;
+        return;
+    }
     const uint32_t NT = hdr->n_tiles;
     TeamShape shape = team_shape(NT, (uint32_t)m);
     // shares of a team of G workgroups (tile t belongs to rank t % G)
@@ -126,7 +147,7 @@ __global__ __launch_bounds__(kPlanBlock) void k_rounds_plan(IndexHeader *hdr, co
         if (tid < kMaxGroups)
             s_tiles[tid] = s_pts[tid] = 0u;
         if (tid == 0)
-            s_bad = s_big = 0u;
+            s_big = 0u;
         __syncthreads();
         for (uint32_t t = tid; t < NT; t += kPlanBlock) {
             const uint32_t r = t % (uint32_t)G;
@@ -137,7 +158,8 @@ __global__ __launch_bounds__(kPlanBlock) void k_rounds_plan(IndexHeader *hdr, co
     };
     shares(Gcap);
     if (tid < Gcap && !share_granted(s_tiles[tid], s_pts[tid], Gcap, R, budget))
-        set_status(&hdr->sample_status, RFPS_ERR_CAPACITY);
+        s_refused = 1u;
+    __syncthreads();
     int G = G0;
     if (!G) {
         G = min(shape.G, Gall);
@@ -160,6 +182,7 @@ __global__ __launch_bounds__(kPlanBlock) void k_rounds_plan(IndexHeader *hdr, co
             --K;
     }
     if (tid == 0) {
+        hdr->sample_status = s_refused ? RFPS_ERR_CAPACITY : 0u;
         hdr->team_g = G;
         hdr->team_k = K;
         hdr->team_steps = shape.steps;
@@ -1932,7 +1955,7 @@ hipError_t launch_rfps_rounds(const IndexView &v, int m, int start, const Sample
     const int most = L.G * (int)slot_units((uint32_t)(L.K ? L.K : 3));
     if (!a.lds_budget || L.K > kRWaves || most > 5 * kRBlock)
         return hipErrorInvalidValue;
-    k_rounds_plan<<<1, kPlanBlock, 0, s>>>(v.hdr, v.tcnt, m, L.G, L.Gcap, L.fixed_g ? L.G : 0, L.K, L.R,
+    k_rounds_plan<<<5, kPlanBlock, 0, s>>>(v.hdr, v.tcnt, v.board, m, start, out_idx, out_d2, L.G, L.Gcap, L.fixed_g ? L.G : 0, L.K, L.R,
                                            L.lds_budget, a.lds_budget);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || m <= 1)
@@ -1945,28 +1968,47 @@ hipError_t launch_rfps_rounds(const IndexView &v, int m, int start, const Sample
     return launch_persistent(fn, L.G, args, a.lds_budget, s, kRBlock);
 }
 
-// Batched plan, one workgroup per cloud: checks the cloud's capacity for a
+// Batched plan, one workgroup per cloud: finds the cloud's tiles, checks the cloud's capacity for a
 // team of bc.team_size workgroups, finds the smallest team whose shares fit
 // the sampler's LDS (bc.team_size itself when the caller asked for it), and
 // writes the cloud's first output (its start, at distance +inf).  The counters
 // the sampler does not keep are set by the first workgroup.
 constexpr int kBatchPlanBlock = 256;
-__global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr, const uint32_t *__restrict__ tcnt,
-                                                                BatchCtl bc, const uint32_t *__restrict__ tile_first,
+__global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr, const uint32_t *__restrict__ tstart,
+                                                                const uint32_t *__restrict__ tcnt, BatchCtl bc,
+                                                                uint32_t *__restrict__ tile_first,
                                                                 int R, uint32_t budget, uint32_t lds, uint32_t *cl_team,
                                                                 int32_t *out_idx, float *out_d2)
 {
     // tiles and points by tile number modulo the largest team: a smaller
     // team's shares are sums of them
-    __shared__ uint32_t s_tiles[kMaxGroups], s_pts[kMaxGroups], s_big[kBatchLevels];
+    __shared__ uint32_t s_tiles[kMaxGroups], s_pts[kMaxGroups], s_big[kBatchLevels], s_tile[2];
     if (hdr->build_status)
         return;
     const int tid = threadIdx.x, c = blockIdx.x, X = bc.per_xcd, T = bc.team_size;
+    if (tid < 2 * kWave) {
+        // The cloud's tiles: the sorted points of a cloud are its range of the
+        // input, so its first tile starts there (64 probes a step).
+        const int lane = tid & (kWave - 1), w = tid / kWave;
+        const uint32_t p = (uint32_t)bc.offsets[c + w];
+        uint32_t lo = 0, hi = hdr->n_tiles;  // the first tile that starts at p or later
+        while (lo < hi) {
+            const uint32_t step = (hi - lo + kWave - 1) / kWave, q = lo + lane * step;
+            const uint32_t f = (uint32_t)__popcll(ballot64(q < hi && tstart[q < hi ? q : lo] < p));
+            const uint32_t nlo = f ? lo + (f - 1) * step + 1 : lo;
+            hi = min(lo + f * step, hi);
+            lo = nlo;
+        }
+        if (lane == 0) {
+            s_tile[w] = lo;
+            tile_first[c + w] = lo;  // (twice, the same)
+        }
+    }
     s_tiles[tid] = s_pts[tid] = 0u;
     if (tid < kBatchLevels)
         s_big[tid] = 0u;
     __syncthreads();
-    const uint32_t tb = tile_first[c], te = tile_first[c + 1];
+    const uint32_t tb = s_tile[0], te = s_tile[1];
     for (uint32_t t = tb + tid; t < te; t += kBatchPlanBlock) {
         atomicAdd(&s_tiles[(t - tb) % (uint32_t)X], 1u);
         atomicAdd(&s_pts[(t - tb) % (uint32_t)X], tcnt[t]);
@@ -2031,35 +2073,46 @@ __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *
     auto cost = [&](int c) {
         return (unsigned long long)(bc.offsets[c + 1] - bc.offsets[c]) * (unsigned long long)bc.m[c];
     };
-    // level of a cloud whose smallest team is `least`, teams holding 2^(e / 8)
-    // of cost per workgroup
+    // level of a cloud whose smallest team is `least` and whose cost has the
+    // logarithm f, teams holding 2^(e / 8) of cost per workgroup
+    const int top = 31 - __builtin_clz((uint32_t)X);  // log2 of the largest team
     auto level_at = [&](uint32_t least, float f, int e) {
-        int lev = (int)least;
-        while (lev > 0 && (float)(X >> (lev - 1)) * exp2f(0.125f * (float)e) <= f)
-            --lev;
-        return lev;
+        return max(0, min((int)least, top - (int)floorf(f - 0.125f * (float)e)));
     };
     int e = 8 * 64;
     if (!bc.fixed_team && B <= (int)all) {
-        // the smallest such cost that leaves a place for every team
-        const uint32_t least = tid < B ? cl_team[tid] : 0u;
-        const float f = tid < B ? (float)cost(tid) : 0.0f;
-        int lo = 0, hi = e;  // hi: every cloud keeps its smallest team
-        while (lo < hi) {
-            const int mid = (lo + hi) / 2;
+        // the smallest such cost that leaves a place for every team, found by
+        // the first wavefront
+        if (tid < kWave) {
+            constexpr int per = kMaxGroups / kWave;
+            uint32_t least[per];
+            float f[per];
+#pragma unroll
+            for (int q = 0; q < per; ++q) {
+                const int c = q * kWave + tid;
+                least[q] = c < B ? cl_team[c] : 0u;
+                f[q] = c < B ? log2f((float)cost(c)) : 0.0f;
+            }
+            int lo = 0, hi = e;  // hi: every cloud keeps its smallest team
+            while (lo < hi) {
+                const int mid = (lo + hi) / 2;
+                uint32_t sum = 0;
+#pragma unroll
+                for (int q = 0; q < per; ++q)
+                    sum += q * kWave + tid < B ? (uint32_t)(X >> level_at(least[q], f[q], mid)) : 0u;
+#pragma unroll
+                for (int o = kWave / 2; o > 0; o >>= 1)
+                    sum += (uint32_t)__shfl_xor((int)sum, o, kWave);
+                if (sum <= all)
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
             if (tid == 0)
-                s_sum = 0u;
-            __syncthreads();
-            if (tid < B)
-                atomicAdd(&s_sum, (uint32_t)(X >> level_at(least, f, mid)));
-            __syncthreads();
-            if (s_sum <= all)
-                hi = mid;
-            else
-                lo = mid + 1;
-            __syncthreads();
+                s_sum = (uint32_t)hi;
         }
-        e = hi;
+        __syncthreads();
+        e = (int)s_sum;
     }
     if (tid < kBatchLevels)
         s_cnt[tid] = 0u;
@@ -2067,8 +2120,9 @@ __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *
         s_pts = 0ull;
     __syncthreads();
     for (int c = tid; c < B; c += kBatchOrderBlock) {
-        const int lev = level_at(cl_team[c], (float)cost(c), e);
-        s_key[c] = ((unsigned long long)(kBatchLevels - lev) << 56) | cost(c);
+        const unsigned long long v = cost(c);
+        const int lev = level_at(cl_team[c], log2f((float)v), e);
+        s_key[c] = ((unsigned long long)(kBatchLevels - lev) << 56) | v;
         atomicAdd(&s_cnt[lev], 1u);
         if (lev == 0)
             atomicAdd(&s_pts, (unsigned long long)(bc.offsets[c + 1] - bc.offsets[c]));
@@ -2096,14 +2150,12 @@ __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *
 hipError_t launch_rfps_rounds_batched(const IndexView &v, const SampleLaunch &L, int32_t *out_idx,
                                       float *out_d2, hipStream_t s)
 {
-    // (the trace area is free: batches are not traced)
-    uint32_t *cl_team = reinterpret_cast<uint32_t *>(v.trace);
     const uint32_t lds = rounds_dynamic((uint32_t)L.max_lds);
     if (!lds || L.K > kBatchK || v.bc.per_xcd * kMaxXcds > kMaxGroups || v.bc.per_xcd >> (kBatchLevels - 1) > 1)
         return hipErrorInvalidValue;
-    k_batch_plan<<<v.bc.batch, kBatchPlanBlock, 0, s>>>(v.hdr, v.tcnt, v.bc, v.tile_first, L.R, L.lds_budget, lds,
-                                                        cl_team, out_idx, out_d2);
-    k_batch_levels<<<1, kBatchOrderBlock, 0, s>>>(v.hdr, v.bc, v.bstate, cl_team, L.K, v.order);
+    k_batch_plan<<<v.bc.batch, kBatchPlanBlock, 0, s>>>(v.hdr, v.tstart, v.tcnt, v.bc, v.tile_first, L.R, L.lds_budget, lds,
+                                                        v.cl_team, out_idx, out_d2);
+    k_batch_levels<<<1, kBatchOrderBlock, 0, s>>>(v.hdr, v.bc, v.bstate, v.cl_team, L.K, v.order);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
