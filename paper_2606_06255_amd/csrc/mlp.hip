@@ -10,10 +10,16 @@
 // network picks, the sampled sequence is the same (every partition is
 // output-neutral); it only changes the speed.
 //
-// The products run on the matrix cores: v_mfma_f32_16x16x4f32, one 16 x 16
-// output tile per wavefront, operands read straight from device memory (the
-// matrices are at most 2048 x 516: the whole training step is a few
-// microseconds of arithmetic and is bound by launch latency, not by HBM).
+// The products run on the matrix cores (v_mfma_f32_16x16x4f32).  A gradient is
+// two launches: k_rows takes 16 rows of the batch through the forward pass,
+// the loss and the backward pass with everything in LDS, and k_wgrad forms the
+// weight gradients, one 16 x 16 tile per workgroup.  The arithmetic is 0.3
+// GFLOP for 2,000 rows; what bounds both is their chains of loads and matrix
+// instructions, so every chain is cut as short as the device allows (a
+// product over the rows is split over eight wavefronts, and no step of the
+// backward pass waits for a launch).  2,000 rows: 1,565 -> 30 us; as 14
+// launches, the three one-workgroup column sums and the loss alone took over
+// a millisecond.
 #include <math.h>
 
 #include <algorithm>
@@ -50,114 +56,360 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float x)
     return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ float load_op(const float *p) { return *p; }
-__device__ __forceinline__ float load_op(const uint16_t *p) { return bf16_to_f32(*p); }
-
-enum Epi : int {
-    kPlain = 0,    // C = acc
-    kBiasRelu = 1, // C = acc + bias[n]; C2 = max(C, 0)
-    kBias = 2,     // C = acc + bias[n]
-    kMask = 3,     // C = acc where mask[m][n] > 0, else 0
-};
-
-// C[m][n] = sum_k A(m, k) B(k, n) with A(m, k) = A[m*sam + k*sak] and
-// B(k, n) = B[k*sbk + n*sbn] (the strides express any transposition).
-// Block = 4 wavefronts = a 32 x 32 tile of C; each wavefront accumulates a
-// 16 x 16 tile over K in steps of 4.  Operand lanes: A element (i, k) in
-// lane i + 16k, B element (k, j) in lane j + 16k; result element (i, j) in
-// lane j + 16 (i / 4), component i % 4.
-template <typename TB, int EPI>
-__global__ __launch_bounds__(256) void k_mm(const float *__restrict__ A, int sam, int sak, const TB *__restrict__ B,
-                                            int sbk, int sbn, float *__restrict__ C, float *__restrict__ C2,
-                                            const float *__restrict__ aux, int M, int N, int K)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = blockIdx.y * 32 + (wave >> 1) * 16, n0 = blockIdx.x * 32 + (wave & 1) * 16;
-    const int li = lane & 15, lk = lane >> 4;
-    const int am = m0 + li, bn = n0 + li;
-    floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int k0 = 0; k0 < K; k0 += 4) {
-        const int k = k0 + lk;
-        const float a = (am < M && k < K) ? A[(size_t)am * sam + (size_t)k * sak] : 0.0f;
-        const float b = (bn < N && k < K) ? load_op(B + (size_t)k * sbk + (size_t)bn * sbn) : 0.0f;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
-    }
-    const int n = n0 + li;
-    if (n >= N)
-        return;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = m0 + 4 * lk + r;
-        if (m >= M)
-            continue;
-        float v = acc[r];
-        const size_t o = (size_t)m * N + n;
-        if constexpr (EPI == kBiasRelu) {
-            v += aux[n];
-            C[o] = v;
-            C2[o] = v > 0.0f ? v : 0.0f;
-        } else if constexpr (EPI == kBias) {
-            C[o] = v + aux[n];
-        } else if constexpr (EPI == kMask) {
-            C[o] = aux[o] > 0.0f ? v : 0.0f;
-        } else {
-            C[o] = v;
-        }
-    }
-}
-
-template <typename TB, int EPI>
-static void mm(const float *A, int sam, int sak, const TB *B, int sbk, int sbn, float *C, float *C2, const float *aux,
-               int M, int N, int K, hipStream_t s)
-{
-    dim3 grid((N + 31) / 32, (M + 31) / 32);
-    k_mm<TB, EPI><<<grid, 256, 0, s>>>(A, sam, sak, B, sbk, sbn, C, C2, aux, M, N, K);
-}
-
-// dY = 2 w (Y - T) / B and the loss sum w (Y - T)^2 / B (one workgroup,
-// fixed reduction order).
-__global__ __launch_bounds__(1024) void k_loss(const float *__restrict__ Y, const float *__restrict__ T,
-                                               const float *__restrict__ Wt, int total, int B,
-                                               float *__restrict__ dY, float *__restrict__ loss)
-{
-    __shared__ double part[1024];
-    double acc = 0.0;
-    const float sc = 2.0f / (float)B;
-    for (int e = threadIdx.x; e < total; e += blockDim.x) {
-        const float w = Wt ? Wt[e] : 1.0f;
-        const float d = Y[e] - T[e];
-        dY[e] = sc * w * d;
-        acc += (double)w * (double)d * (double)d;
-    }
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            part[threadIdx.x] += part[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && loss)
-        *loss = (float)(part[0] / (double)B);
-}
-
-// db[n] = sum_m dZ[m][n], one thread per column.
-__global__ void k_colsum(const float *__restrict__ dZ, int M, int N, float *__restrict__ db)
-{
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N)
-        return;
-    float s = 0.0f;
-    for (int m = 0; m < M; ++m)
-        s += dZ[(size_t)m * N + n];
-    db[n] = s;
-}
-
 // Model state in the caller's memory (rfps_mlp_state_size bytes).
 struct State {
     float *master, *m, *v;
     uint16_t *wbf;   // bf16 copy of master (packed like it; only the weight blocks are read)
     uint32_t *step;  // Adam steps taken
 };
+
+// bf16 pair of a word.
+__device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
+
+__device__ __forceinline__ floatx4 mma(float a, float b, floatx4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Matrix instructions take A element (i, k) in lane i + 16k and B element
+// (k, j) in lane j + 16k; result element (i, j) is in lane j + 16 (i / 4),
+// component i % 4.  Which four k one instruction takes is free as long as both
+// operands agree: over 32 of them, instruction s takes 8 q + s from lanes
+// 16 q .., so that a lane's values are eight neighbours in memory.
+struct Bf8 {
+    uint32_t u[4];
+};
+__device__ __forceinline__ Bf8 load_bf8(const uint16_t *p)  // 8-byte aligned
+{
+    const uint2 a = *reinterpret_cast<const uint2 *>(p), b = *reinterpret_cast<const uint2 *>(p + 4);
+    return {{a.x, a.y, b.x, b.y}};
+}
+// c += A B over 32 k: a is the lane's eight values of A in LDS (16-byte aligned).
+__device__ __forceinline__ floatx4 mma32(const float *a, const Bf8 &b, floatx4 c)
+{
+    const floatx4 x = *reinterpret_cast<const floatx4 *>(a), y = *reinterpret_cast<const floatx4 *>(a + 4);
+    c = mma(x[0], bf_lo(b.u[0]), c);
+    c = mma(x[1], bf_hi(b.u[0]), c);
+    c = mma(x[2], bf_lo(b.u[1]), c);
+    c = mma(x[3], bf_hi(b.u[1]), c);
+    c = mma(y[0], bf_lo(b.u[2]), c);
+    c = mma(y[1], bf_hi(b.u[2]), c);
+    c = mma(y[2], bf_lo(b.u[3]), c);
+    return mma(y[3], bf_hi(b.u[3]), c);
+}
+
+// The same in FP64.  The hidden layers' inputs are summed so: their signs
+// decide which units pass a gradient, and a rounding error that turns one of
+// the 256,000 signs of 2,000 rows changes the gradient by more than all other
+// errors together.  An FP64 instruction takes twice an FP32 one's time; its
+// result element (i, j) is in lane j + 16 (i % 4), component i / 4.
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ doublex4 mma(double a, double b, doublex4 c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <typename T>
+__device__ __forceinline__ doublex4 mma32(const T *a, const Bf8 &b, doublex4 c)
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        c = mma((double)a[2 * q], (double)bf_lo(b.u[q]), c);
+        c = mma((double)a[2 * q + 1], (double)bf_hi(b.u[q]), c);
+    }
+    return c;
+}
+
+// What the backward pass leaves for the weight gradients.
+struct RowArrays {
+    float *a1, *a2, *dy, *dz2, *dz1;
+    double *loss;  // one term per workgroup of k_rows
+};
+
+// 16 rows of the batch: Y = X -> 64 ReLU -> 64 ReLU -> 72 outputs, and with
+// GRAD the loss sum w (Y - T)^2 / B, dY = 2 w (Y - T) / B and the gradients of
+// both hidden layers' inputs.  Eight wavefronts: the first layer's four output
+// tiles, each over two halves of the 516 inputs; one tile per wavefront after
+// that.  All weights a wavefront needs are loaded before the first barrier, so
+// the later layers wait for LDS only.  LDS row strides are 4 mod 64 words (12
+// for dY), which spreads the 16 rows of an operand over all banks.
+constexpr int kRows = 16, kRowsBlock = 512;
+constexpr int kChunks = kIn / 32;                 // whole chunks of 32 inputs
+static_assert(kIn - 32 * kChunks == 4, "one more instruction for the rest");
+template <bool GRAD>
+__global__ __launch_bounds__(kRowsBlock) void k_rows(const float *__restrict__ master,
+                                                     const uint16_t *__restrict__ wbf, const float *__restrict__ x,
+                                                     const float *__restrict__ t, const float *__restrict__ wt, int B,
+                                                     float *__restrict__ yout, RowArrays out)
+{
+    constexpr int sX = kIn, sH = kH + 4, sD = kH + 2, sY = kOut + 4;
+    __shared__ __align__(16) float X[kRows * sX];
+    __shared__ __align__(16) double P[2][kRows * sD], A1[kRows * sD];
+    __shared__ __align__(16) float A2[kRows * sH], DY[kRows * sY], DZ[kRows * sH];
+    __shared__ double s_loss[kRowsBlock / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int m0 = blockIdx.x * kRows;
+    const int rows = min(kRows, B - m0);
+    const int n0 = (wave & 3) * 16, half = wave >> 2;
+
+    // weights: layer 1 (half of the chunks), then by wavefront
+    const uint16_t *w1 = wbf + oW1 + (size_t)(n0 + li) * kIn;
+    Bf8 c1[kChunks / 2];
+#pragma unroll
+    for (int c = 0; c < kChunks / 2; ++c)
+        c1[c] = load_bf8(w1 + (2 * c + half) * 32 + lk * 8);
+    const float rest = half == 0 ? bf16_to_f32(w1[kChunks * 32 + lk]) : 0.0f;
+    Bf8 c2[2], c3[2];
+    float b3w[18], b2w[16];
+    const int o3 = wave * 16 + li;  // output column of the third layer
+    if (wave < 4) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            c2[c] = load_bf8(wbf + oW2 + (size_t)(n0 + li) * kH + c * 32 + lk * 8);
+        if constexpr (GRAD) {
+#pragma unroll
+            for (int q = 0; q < 18; ++q) {
+                const int k = q < 16 ? (q / 8) * 32 + lk * 8 + q % 8 : 64 + 4 * (q - 16) + lk;
+                b3w[q] = bf16_to_f32(wbf[oW3 + (size_t)k * kH + n0 + li]);
+            }
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                b2w[q] = bf16_to_f32(wbf[oW2 + (size_t)((q / 8) * 32 + lk * 8 + q % 8) * kH + n0 + li]);
+        }
+    }
+    if (wave < 5) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            c3[c] = load_bf8(wbf + oW3 + (size_t)min(o3, kOut - 1) * kH + c * 32 + lk * 8);
+    }
+    for (int e = tid; e < kRows * kIn; e += kRowsBlock)
+        X[e] = e < rows * kIn ? x[(size_t)m0 * kIn + e] : 0.0f;
+    __syncthreads();
+
+    // ---- layer 1 ----
+    {
+        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < kChunks / 2; ++c)
+            acc = mma32(&X[li * sX + (2 * c + half) * 32 + lk * 8], c1[c], acc);
+        if (half == 0)
+            acc = mma((double)X[li * sX + kChunks * 32 + lk], (double)rest, acc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            P[half][(4 * r + lk) * sD + n0 + li] = acc[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kRows * kH / kRowsBlock; ++q) {
+        const int e = q * kRowsBlock + tid, m = e / kH, n = e % kH;
+        const double z = P[0][m * sD + n] + P[1][m * sD + n] + (double)master[ob1 + n];
+        const double v = z > 0.0 ? z : 0.0;
+        A1[m * sD + n] = v;
+        if (GRAD && m < rows)
+            out.a1[(size_t)(m0 + m) * kH + n] = (float)v;
+    }
+    __syncthreads();
+    // ---- layer 2 ----
+    if (wave < 4) {
+        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            acc = mma32(&A1[li * sD + c * 32 + lk * 8], c2[c], acc);
+        const double bias = (double)master[ob2 + n0 + li];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double z = acc[r] + bias;
+            const float v = z > 0.0 ? (float)z : 0.0f;
+            const int m = 4 * r + lk;
+            A2[m * sH + n0 + li] = v;
+            if (GRAD && m < rows)
+                out.a2[(size_t)(m0 + m) * kH + n0 + li] = v;
+        }
+    }
+    __syncthreads();
+    // ---- layer 3, loss ----
+    double part = 0.0;
+    if (wave < 5) {
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            acc = mma32(&A2[li * sH + c * 32 + lk * 8], c3[c], acc);
+        if (o3 < kOut) {
+            const float bias = master[ob3 + o3], sc = 2.0f / (float)B;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = 4 * lk + r;
+                const float y = acc[r] + bias;
+                const size_t o = (size_t)(m0 + m) * kOut + o3;
+                if constexpr (GRAD) {
+                    float g = 0.0f;
+                    if (m < rows) {
+                        const float w = wt ? wt[o] : 1.0f;
+                        const float d = y - t[o];
+                        g = sc * w * d;
+                        part += (double)w * (double)d * (double)d;
+                        out.dy[o] = g;
+                    }
+                    DY[m * sY + o3] = g;
+                } else if (m < rows) {
+                    yout[o] = y;
+                }
+            }
+        }
+    }
+    if constexpr (!GRAD)
+        return;
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1)
+        part += __shfl_xor(part, h, 64);
+    if (lane == 0)
+        s_loss[wave] = part;
+    __syncthreads();
+    if (tid == 0) {
+        double v = 0.0;
+        for (int q = 0; q < kRowsBlock / 64; ++q)
+            v += s_loss[q];
+        out.loss[blockIdx.x] = v;
+    }
+    // ---- dZ2 = (dY W3) where A2 > 0 ----
+    if (wave < 4) {
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int q = 0; q < 18; ++q) {
+            const int k = q < 16 ? (q / 8) * 32 + lk * 8 + q % 8 : 64 + 4 * (q - 16) + lk;
+            acc = mma(DY[li * sY + k], b3w[q], acc);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 4 * lk + r;
+            const float v = A2[m * sH + n0 + li] > 0.0f ? acc[r] : 0.0f;
+            DZ[m * sH + n0 + li] = v;
+            if (m < rows)
+                out.dz2[(size_t)(m0 + m) * kH + n0 + li] = v;
+        }
+    }
+    __syncthreads();
+    // ---- dZ1 = (dZ2 W2) where A1 > 0 ----
+    if (wave < 4) {
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            acc = mma(DZ[li * sH + (q / 8) * 32 + lk * 8 + q % 8], b2w[q], acc);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 4 * lk + r;
+            if (m < rows)
+                out.dz1[(size_t)(m0 + m) * kH + n0 + li] = A1[m * sD + n0 + li] > 0.0 ? acc[r] : 0.0f;
+        }
+    }
+}
+
+// Weight and bias gradients of the three layers, dW = dZ^T A and db = the
+// column sums of dZ (dZ^T times a column of ones), one 16 x 16 tile of one dW
+// per workgroup: 33 x 4 tiles of dW1, 4 x 4 of dW2, 4 x 5 of dW3.  The eight
+// wavefronts take every eighth group of four rows, and their sums meet in LDS
+// in a fixed order.  The first workgroup adds up the loss.
+constexpr int kTiles1 = ((kIn + 15) / 16) * (kH / 16), kTiles2 = (kH / 16) * (kH / 16),
+              kTiles3 = (kH / 16) * ((kOut + 15) / 16);
+constexpr int kGradWaves = 8;
+__global__ __launch_bounds__(kGradWaves * 64) void k_wgrad(RowArrays in, const float *__restrict__ x, int B,
+                                                           float *__restrict__ grad, float *__restrict__ loss)
+{
+    __shared__ float s_w[kGradWaves][256], s_b[kGradWaves][16];
+    __shared__ double s_loss[kGradWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const float *dz, *act;
+    int tile = blockIdx.x, M, N, ow, ob;
+    if (tile < kTiles1) {
+        dz = in.dz1;
+        act = x;
+        M = kH;
+        N = kIn;
+        ow = oW1;
+        ob = ob1;
+    } else if (tile < kTiles1 + kTiles2) {
+        tile -= kTiles1;
+        dz = in.dz2;
+        act = in.a1;
+        M = kH;
+        N = kH;
+        ow = oW2;
+        ob = ob2;
+    } else {
+        tile -= kTiles1 + kTiles2;
+        dz = in.dy;
+        act = in.a2;
+        M = kOut;
+        N = kH;
+        ow = oW3;
+        ob = ob3;
+    }
+    const int nt = (N + 15) / 16;
+    const int m0 = tile / nt * 16, n0 = tile % nt * 16;
+    const bool bias = n0 == 0;
+    const int am = min(m0 + li, M - 1), bn = min(n0 + li, N - 1);  // (past the edge: not stored)
+    floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f}, sum = {0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int U = 8;  // groups in flight
+    for (int k0 = wave * 4; k0 < B; k0 += U * kGradWaves * 4) {
+        float a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * kGradWaves * 4 + lk;
+            a[u] = k < B ? dz[(size_t)k * M + am] : 0.0f;
+            b[u] = k < B ? act[(size_t)k * N + bn] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            acc = mma(a[u], b[u], acc);
+        if (bias)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                sum = mma(a[u], 1.0f, sum);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        s_w[wave][(4 * lk + r) * 16 + li] = acc[r];
+        if (li == 0)
+            s_b[wave][4 * lk + r] = sum[r];
+    }
+    double l = 0.0;
+    if (blockIdx.x == 0) {
+        const int parts = (B + kRows - 1) / kRows;
+        for (int q = tid; q < parts; q += kGradWaves * 64)
+            l += in.loss[q];
+#pragma unroll
+        for (int h = 32; h > 0; h >>= 1)
+            l += __shfl_xor(l, h, 64);
+        if (lane == 0)
+            s_loss[wave] = l;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        const int m = m0 + tid / 16, n = n0 + tid % 16;
+        float v = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kGradWaves; ++q)
+            v += s_w[q][tid];
+        if (m < M && n < N)
+            grad[ow + (size_t)m * N + n] = v;
+    } else if (bias && tid < 256 + 16) {
+        const int m = m0 + tid - 256;
+        float v = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kGradWaves; ++q)
+            v += s_b[q][tid - 256];
+        if (m < M)
+            grad[ob + m] = v;
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        double v = 0.0;
+        for (int q = 0; q < kGradWaves; ++q)
+            v += s_loss[q];
+        *loss = (float)(v / (double)B);
+    }
+}
 
 __global__ void k_step_inc(uint32_t *step)
 {
@@ -365,7 +617,7 @@ State state_view(void *p)
 }
 
 struct WsLayout {
-    size_t feat, z1, a1, z2, a2, y, dy, dz2, dz1, grad, loss, total;
+    size_t feat, loss_parts, a1, a2, y, dy, dz2, dz1, grad, loss, total;
 };
 WsLayout ws_layout(int B)
 {
@@ -378,9 +630,9 @@ WsLayout ws_layout(int B)
     };
     const size_t b = (size_t)B;
     L.feat = take(sizeof(FeatScratch));
-    L.z1 = take(4 * b * kH);
+    L.loss_parts = take(4 * b * kH);  // a double per 16 rows; workspace sizes stay as they are
     L.a1 = take(4 * b * kH);
-    L.z2 = take(4 * b * kH);
+    take(4 * b * kH);  // not used
     L.a2 = take(4 * b * kH);
     L.y = take(4 * b * kOut);
     L.dy = take(4 * b * kOut);
@@ -398,36 +650,21 @@ T *at(void *ws, size_t off)
     return reinterpret_cast<T *>(static_cast<unsigned char *>(ws) + off);
 }
 
-// Forward pass of B rows: Z1, A1, Z2, A2 and Y in the workspace.
-void forward(const State &st, const float *x, int B, void *ws, const WsLayout &L, float *y, hipStream_t s)
+// Forward pass of B rows.
+void forward(const State &st, const float *x, int B, float *y, hipStream_t s)
 {
-    float *z1 = at<float>(ws, L.z1), *a1 = at<float>(ws, L.a1), *z2 = at<float>(ws, L.z2),
-          *a2 = at<float>(ws, L.a2);
-    mm<uint16_t, kBiasRelu>(x, kIn, 1, st.wbf + oW1, 1, kIn, z1, a1, st.master + ob1, B, kH, kIn, s);
-    mm<uint16_t, kBiasRelu>(a1, kH, 1, st.wbf + oW2, 1, kH, z2, a2, st.master + ob2, B, kH, kH, s);
-    mm<uint16_t, kBias>(a2, kH, 1, st.wbf + oW3, 1, kH, y, nullptr, st.master + ob3, B, kOut, kH, s);
+    k_rows<false><<<(B + kRows - 1) / kRows, kRowsBlock, 0, s>>>(st.master, st.wbf, x, nullptr, nullptr, B, y,
+                                                                 RowArrays{});
 }
 
 // Gradient of the loss with respect to the packed parameters into `grad`.
 void backward(const State &st, const float *x, const float *t, const float *wt, int B, void *ws, const WsLayout &L,
               float *grad, float *loss, hipStream_t s)
 {
-    float *z1 = at<float>(ws, L.z1), *a1 = at<float>(ws, L.a1), *z2 = at<float>(ws, L.z2),
-          *a2 = at<float>(ws, L.a2), *y = at<float>(ws, L.y), *dy = at<float>(ws, L.dy),
-          *dz2 = at<float>(ws, L.dz2), *dz1 = at<float>(ws, L.dz1);
-    forward(st, x, B, ws, L, y, s);
-    k_loss<<<1, 1024, 0, s>>>(y, t, wt, B * kOut, B, dy, loss);
-    // layer 3
-    mm<float, kPlain>(dy, 1, kOut, a2, kH, 1, grad + oW3, nullptr, nullptr, kOut, kH, B, s);
-    k_colsum<<<1, 128, 0, s>>>(dy, B, kOut, grad + ob3);
-    mm<uint16_t, kMask>(dy, kOut, 1, st.wbf + oW3, kH, 1, dz2, nullptr, z2, B, kH, kOut, s);
-    // layer 2
-    mm<float, kPlain>(dz2, 1, kH, a1, kH, 1, grad + oW2, nullptr, nullptr, kH, kH, B, s);
-    k_colsum<<<1, 128, 0, s>>>(dz2, B, kH, grad + ob2);
-    mm<uint16_t, kMask>(dz2, kH, 1, st.wbf + oW2, kH, 1, dz1, nullptr, z1, B, kH, kH, s);
-    // layer 1
-    mm<float, kPlain>(dz1, 1, kH, x, kIn, 1, grad + oW1, nullptr, nullptr, kH, kIn, B, s);
-    k_colsum<<<1, 128, 0, s>>>(dz1, B, kH, grad + ob1);
+    const RowArrays r = {at<float>(ws, L.a1),  at<float>(ws, L.a2),  at<float>(ws, L.dy),
+                         at<float>(ws, L.dz2), at<float>(ws, L.dz1), at<double>(ws, L.loss_parts)};
+    k_rows<true><<<(B + kRows - 1) / kRows, kRowsBlock, 0, s>>>(st.master, st.wbf, x, t, wt, B, nullptr, r);
+    k_wgrad<<<kTiles1 + kTiles2 + kTiles3, kGradWaves * 64, 0, s>>>(r, x, B, grad, loss);
 }
 
 bool aligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) % kAlign) == 0; }
@@ -542,7 +779,7 @@ rfps_status rfps_mlp_forward(const void *state, size_t state_bytes, const float 
     if (!x || !y)
         return RFPS_ERR_INVALID_ARG;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    forward(state_view(const_cast<void *>(state)), x, batch, ws, ws_layout(batch), y, s);
+    forward(state_view(const_cast<void *>(state)), x, batch, y, s);
     return launched(s);
 }
 
@@ -597,7 +834,7 @@ rfps_status rfps_mlp_choose(const void *state, size_t state_bytes, const float *
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const WsLayout L = ws_layout(1);
     float *out = y ? y : at<float>(ws, L.y);
-    forward(state_view(const_cast<void *>(state)), feat, 1, ws, L, out, s);
+    forward(state_view(const_cast<void *>(state)), feat, 1, out, s);
     k_choose<<<1, 64, 0, s>>>(out, default_cand, margin, choice);
     return launched(s);
 }
