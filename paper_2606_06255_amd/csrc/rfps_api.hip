@@ -370,6 +370,11 @@ rfps_status rfps_sample(const rfps_index *index, int32_t m, int32_t start, const
         return RFPS_ERR_UNSUPPORTED;
     if (L.G > d->cus)
         return RFPS_ERR_UNSUPPORTED;
+    // A small cloud with nothing asked for but the distance: one workgroup.
+    // (128 workgroups hold any share of so few points, so no such call can
+    // exceed the capacity.)
+    L.solo = !L.fixed_g && !L.K && L.R > 0 && index->n <= kSoloSingle && L.Gcap >= 128 &&
+             (L.flags & ~(RFPS_F_SQRT | RFPS_F_NO_POINT_SKIP)) == 0;
     const IndexView v = make_view(index->ws, index->n, index->n_vox, index->tile, index->shells);
     hipError_t e = launch_rfps_sample(v, m, start, L, out_idx, out_d2, static_cast<hipStream_t>(stream));
     if (e == hipSuccess && out_d2 && (L.flags & RFPS_F_SQRT))
@@ -592,6 +597,7 @@ rfps_status rfps_sample_batched(const float *xyz, int32_t n, const int32_t *offs
     if ((per_xcd & (per_xcd - 1)) != 0 || T < 2 || per_xcd % T != 0 || teams * (2 * T + 1) * kMaxSlotWords > kBoardWords)
         return RFPS_ERR_UNSUPPORTED;
     SampleLaunch L;
+    L.solo = false;
     L.G = d->cus;
     L.flags = flags;
     L.Gcap = L.G;

@@ -434,6 +434,7 @@ struct SampleLaunch {
     uint32_t flags;
     uint32_t lds_budget;  // on-chip bytes a workgroup's share may take (the capacity limit)
     int max_lds;          // bytes of LDS a workgroup may use
+    bool solo;            // a small cloud, sampled by one workgroup
     int K;                // multi-pick sampler: candidates a workgroup publishes as asked for; 0 = by rule
 };
 // Static LDS of the one-pick sampler kernel (bytes).
@@ -478,6 +479,11 @@ inline hipError_t launch_persistent(const void *fn, int G, void **args, size_t l
     return hipLaunchKernel(fn, dim3(G), dim3(block), args, lds, s);
 }
 
+// A small cloud by one workgroup (sample_solo.hip): resets, samples and, after
+// a failed build, marks the outputs.
+hipError_t launch_rfps_solo(const IndexView &v, int m, int start, bool euclid, int32_t *out_idx, float *out_d2,
+                            hipStream_t s);
+
 // Batched index build (index_build.hip) and batched sampling (sample_rounds.hip).
 hipError_t launch_build_batch(const IndexView &v, const float *xyz, hipStream_t s);
 hipError_t launch_rfps_rounds_batched(const IndexView &v, const SampleLaunch &L, int32_t *out_idx,
@@ -498,6 +504,9 @@ __host__ __device__ inline uint32_t shell_cap_for(uint32_t n, bool shells)
 // shell s = min(floor(r / spacing), shell_cap - 1), which uses cubes of edge
 // (s + 1) L and ceil(n / (s + 1)) bins per axis from the same corner; its key
 // is s * n^3 + V_id on that coarser grid, so shells never share a voxel.
+// The voxels are numbered in blocks of 4 x 4 x 4, and inside one in Morton
+// order, when the bins per axis allow it: points that follow one another then
+// lie in a compact region, not along a row of voxels.
 // Any partition of the points into voxels leaves the sampling result
 // unchanged (the tile spheres enclose their members whatever the grid).
 __device__ __forceinline__ uint32_t voxel_key(float px, float py, float pz, const double *pmin, double L,
@@ -509,6 +518,7 @@ __device__ __forceinline__ uint32_t voxel_key(float px, float py, float pz, cons
         const double r = floor(sqrt(dx * dx + dy * dy + dz * dz) * shell_inv);
         s = r < (double)(shell_cap - 1) ? (uint32_t)r : shell_cap - 1;
     }
+    // (ns bins: a multiple of 4 for every default grid of one shell)
     const uint32_t ns = (n + s) / (s + 1);
     const double Ls = L * (double)(s + 1);
     const double top = (double)(ns - 1);
@@ -520,6 +530,14 @@ __device__ __forceinline__ uint32_t voxel_key(float px, float py, float pz, cons
         q = q > 0.0 ? q : 0.0;  // also maps NaN to 0
         q = q < top ? q : top;
         v[a] = (uint32_t)q;
+    }
+    if ((ns & 3u) == 0u) {
+        const uint32_t nb = ns / 4;
+        const uint32_t block = ((v[2] >> 2) * nb + (v[1] >> 2)) * nb + (v[0] >> 2);
+        const uint32_t a = v[0] & 3u, b = v[1] & 3u, c = v[2] & 3u;
+        const uint32_t in = (a & 1u) | ((b & 1u) << 1) | ((c & 1u) << 2) | ((a & 2u) << 2) | ((b & 2u) << 3) |
+                            ((c & 2u) << 4);
+        return s * n * n * n + block * 64u + in;
     }
     return s * n * n * n + (v[2] * ns + v[1]) * ns + v[0];
 }

@@ -115,6 +115,18 @@ RFPS_HOST_DEVICE inline int batch_k(int level, unsigned long long points_per_gro
 // workgroup's share is full and gain 1 % where it is small; 8 gain nothing).
 constexpr int kBatchSteps = 4;
 
+// One workgroup for a whole cloud (solo_cloud.h): a ring of keys and the
+// coordinates in LDS, at most 16 points a thread in registers.
+constexpr uint32_t kSoloRingBytes = 1024;
+constexpr int kSoloPoints = 8192;
+RFPS_HOST_DEVICE inline uint32_t solo_lds(uint32_t n) { return kSoloRingBytes + n * 16u; }
+// Largest cloud a single call gives to one workgroup.  Measured, sampling of a
+// quarter of the points by one workgroup and by a team, from call to
+// completion in us: 512 points 43 | 155, 1,024 73 | 213, 2,048 167 | 263, 3,000
+// 270 | 301, 3,500 352 | 374, 4,000 400 | 378.
+constexpr int kSoloSingle = 3584;
+static_assert(kSoloRingBytes + kSoloSingle * 16u <= 65536u, "no opt-in for more LDS");
+
 // Bytes a workgroup's share may take by that rule: what a compute unit has
 // beside 6,496 bytes.
 constexpr uint32_t kRoundsReserve = 6496;

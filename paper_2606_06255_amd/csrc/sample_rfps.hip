@@ -391,6 +391,8 @@ size_t rfps_sampler_static_lds()
 hipError_t launch_rfps_sample(const IndexView &v, int m, int start, const SampleLaunch &L, int32_t *out_idx,
                               float *out_d2, hipStream_t s)
 {
+    if (L.solo)
+        return launch_rfps_solo(v, m, start, (L.flags & RFPS_F_SQRT) != 0, out_idx, out_d2, s);
     const bool rounds = L.R > 0 && !(L.flags & RFPS_F_UNFUSED);
     hipError_t e = hipSuccess;
     if (!rounds) {  // (the multi-pick sampler's plan does this itself)

@@ -59,6 +59,7 @@
 
 #include "rfps_internal.h"
 #include "round_layout.h"
+#include "solo_cloud.h"
 
 namespace rfps {
 
@@ -1663,7 +1664,8 @@ RFPS_ROUNDS_KERNEL(k_rfps_rounds_wide_euclid_tele, rounds_single<5, true, true>)
 // then splits in two for the next level, down to single workgroups.  Teams
 // never join again, so a level's control word, once it says "no more", stays.
 // Measured against one team of a whole XCD per cloud: 64 clouds of 512 to
-// 4,096 points 2.18 -> 0.78 ms, 32 clouds of 8k to 120k points 16.1 -> 9.8 ms
+// 4,096 points 2.18 -> 0.78 ms (0.52 with small clouds in one workgroup and a
+// shorter build), 32 clouds of 8k to 120k points 16.1 -> 9.8 ms
 // (then bound by the workgroups' time: the device is full until the end).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t xcc_id()
@@ -1764,6 +1766,20 @@ __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
             continue;
         }
         const int c = a.order[q];
+        if (!I && T == 1) {
+            const uint32_t p = (uint32_t)bc.offsets[c];  // the cloud's place in the input and among the sorted points
+            const SoloJob solo = {a.xs,
+                                  a.ys,
+                                  a.zs,
+                                  a.inv + p,
+                                  bc.offsets[c + 1] - bc.offsets[c],
+                                  bc.m[c],
+                                  bc.starts ? bc.starts[c] : 0,
+                                  a.out_idx + bc.out_offsets[c],
+                                  a.out_d2 ? a.out_d2 + bc.out_offsets[c] : nullptr};
+            solo_any<E>(solo, smem);
+            continue;
+        }
         CloudJob job;
         job.tb = a.tile_first[c];
         job.te = a.tile_first[c + 1];
@@ -1977,7 +1993,8 @@ constexpr int kBatchPlanBlock = 256;
 __global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr, const uint32_t *__restrict__ tstart,
                                                                 const uint32_t *__restrict__ tcnt, BatchCtl bc,
                                                                 uint32_t *__restrict__ tile_first,
-                                                                int R, uint32_t budget, uint32_t lds, uint32_t *cl_team,
+                                                                int R, uint32_t budget, uint32_t lds, bool solo,
+                                                                uint32_t *cl_team,
                                                                 int32_t *out_idx, float *out_d2)
 {
     // tiles and points by tile number modulo the largest team: a smaller
@@ -2025,7 +2042,7 @@ __global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr
         }
         if (t == T && !share_granted(tiles, pts, T, R, budget))
             set_status(&hdr->sample_status, RFPS_ERR_CAPACITY);
-        if (pts > 65535u || rounds_lds_need(tiles, pts) > lds)
+        if (solo && t == 1 ? pts > (uint32_t)kSoloPoints : pts > 65535u || rounds_lds_need(tiles, pts) > lds)
             s_big[lev] = 1u;
     }
     __syncthreads();
@@ -2035,8 +2052,8 @@ __global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr
             while ((X >> lev) > T)
                 ++lev;
         else
-            while (lev + 1 < kBatchLevels && (X >> (lev + 1)) > 0 && !s_big[lev + 1])
-                ++lev;
+            for (int q = 1; q < kBatchLevels && (X >> q) > 0; ++q)
+                lev = s_big[q] ? lev : q;
         cl_team[c] = (uint32_t)lev;
         const uint32_t o = bc.out_offsets[c];
         out_idx[o] = bc.starts ? bc.starts[c] : 0;
@@ -2055,13 +2072,20 @@ __global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr
 // its smallest team; otherwise the teams grow, the costliest clouds' first,
 // until the device is full.  The clouds are then ordered by team, and inside
 // a level by decreasing cost N_c m_c (ties by index).
+//
+// A cloud of up to kSoloPoints points is sampled by one workgroup in registers
+// (solo_cloud.h).  Up to 4,096 points no team is faster; beyond, teams of two
+// and four are not (8,192 -> 2,048: one workgroup 1.4 ms, teams of 2, 4, 8,
+// 16: 2.0, 1.5, 1.2, 0.95).
+//
 // Measured, sampling time per cloud with the device full (room, 16,384 ->
 // 4,096): teams of 4 52 us, 8 65, 16 96, 32 172; and latency of one cloud
 // (4,096 -> 1,024): teams of 2 1.3 ms, 4 0.94, 8 0.76, 16 0.67, 32 0.62.
+constexpr int kSoloBatch = 4096;
 constexpr int kBatchOrderBlock = 1024;
 __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *hdr, BatchCtl bc, BatchState *st,
                                                                    const uint32_t *__restrict__ cl_team, int K,
-                                                                   int32_t *order)
+                                                                   bool solo, int32_t *order)
 {
     __shared__ unsigned long long s_key[kMaxBatch];
     __shared__ uint32_t s_sum, s_cnt[kBatchLevels];
@@ -2076,9 +2100,11 @@ __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *
     // level of a cloud whose smallest team is `least` and whose cost has the
     // logarithm f, teams holding 2^(e / 8) of cost per workgroup
     const int top = 31 - __builtin_clz((uint32_t)X);  // log2 of the largest team
-    auto level_at = [&](uint32_t least, float f, int e) {
-        return max(0, min((int)least, top - (int)floorf(f - 0.125f * (float)e)));
+    auto level_at = [&](uint32_t least, int n, float f, int e) {
+        const int lev = max(0, min((int)least, top - (int)floorf(f - 0.125f * (float)e)));
+        return solo && (int)least == top && (n <= kSoloBatch || lev > top - 3) ? top : lev;
     };
+    auto points = [&](int c) { return bc.offsets[c + 1] - bc.offsets[c]; };
     int e = 8 * 64;
     if (!bc.fixed_team && B <= (int)all) {
         // the smallest such cost that leaves a place for every team, found by
@@ -2086,11 +2112,13 @@ __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *
         if (tid < kWave) {
             constexpr int per = kMaxGroups / kWave;
             uint32_t least[per];
+            int pts[per];
             float f[per];
 #pragma unroll
             for (int q = 0; q < per; ++q) {
                 const int c = q * kWave + tid;
                 least[q] = c < B ? cl_team[c] : 0u;
+                pts[q] = c < B ? points(c) : 0;
                 f[q] = c < B ? log2f((float)cost(c)) : 0.0f;
             }
             int lo = 0, hi = e;  // hi: every cloud keeps its smallest team
@@ -2099,7 +2127,7 @@ __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *
                 uint32_t sum = 0;
 #pragma unroll
                 for (int q = 0; q < per; ++q)
-                    sum += q * kWave + tid < B ? (uint32_t)(X >> level_at(least[q], f[q], mid)) : 0u;
+                    sum += q * kWave + tid < B ? (uint32_t)(X >> level_at(least[q], pts[q], f[q], mid)) : 0u;
 #pragma unroll
                 for (int o = kWave / 2; o > 0; o >>= 1)
                     sum += (uint32_t)__shfl_xor((int)sum, o, kWave);
@@ -2121,7 +2149,7 @@ __global__ __launch_bounds__(kBatchOrderBlock) void k_batch_levels(IndexHeader *
     __syncthreads();
     for (int c = tid; c < B; c += kBatchOrderBlock) {
         const unsigned long long v = cost(c);
-        const int lev = level_at(cl_team[c], log2f((float)v), e);
+        const int lev = level_at(cl_team[c], points(c), log2f((float)v), e);
         s_key[c] = ((unsigned long long)(kBatchLevels - lev) << 56) | v;
         atomicAdd(&s_cnt[lev], 1u);
         if (lev == 0)
@@ -2153,9 +2181,11 @@ hipError_t launch_rfps_rounds_batched(const IndexView &v, const SampleLaunch &L,
     const uint32_t lds = rounds_dynamic((uint32_t)L.max_lds);
     if (!lds || L.K > kBatchK || v.bc.per_xcd * kMaxXcds > kMaxGroups || v.bc.per_xcd >> (kBatchLevels - 1) > 1)
         return hipErrorInvalidValue;
-    k_batch_plan<<<v.bc.batch, kBatchPlanBlock, 0, s>>>(v.hdr, v.tstart, v.tcnt, v.bc, v.tile_first, L.R, L.lds_budget, lds,
+    // (the counters of the instrumented kernel are the team sampler's)
+    const bool solo = (L.flags & RFPS_F_TELEMETRY) == 0 && solo_lds(kSoloPoints) <= lds;
+    k_batch_plan<<<v.bc.batch, kBatchPlanBlock, 0, s>>>(v.hdr, v.tstart, v.tcnt, v.bc, v.tile_first, L.R, L.lds_budget, lds, solo,
                                                         v.cl_team, out_idx, out_d2);
-    k_batch_levels<<<1, kBatchOrderBlock, 0, s>>>(v.hdr, v.bc, v.bstate, v.cl_team, L.K, v.order);
+    k_batch_levels<<<1, kBatchOrderBlock, 0, s>>>(v.hdr, v.bc, v.bstate, v.cl_team, L.K, solo, v.order);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
