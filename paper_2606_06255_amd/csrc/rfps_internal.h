@@ -45,6 +45,8 @@ constexpr int kTeleTicksWait = 14;
 constexpr int kTeleSub = 16;        // eight finer clocks of the rounds (see rfps_telemetry)
 constexpr int kTeleMergeStats = 24; // listed-above, listed, failures summed over rounds
 
+constexpr int kMaxXcds = 8;      // XCDs of an MI355X; batched teams never span two
+
 // Status words live in the index header.  The build status is sticky for the
 // index; the sample status is cleared at the start of every sampling call.
 struct IndexHeader {
@@ -65,7 +67,6 @@ struct IndexHeader {
     unsigned long long tele[kTeleFields];  // rfps_telemetry, in its field order
 };
 
-constexpr int kMaxXcds = 8;      // XCDs of an MI355X; batched teams never span two
 constexpr int kMaxBatch = 4096;  // clouds per batched call
 
 // Batch description, passed by value to the kernels.
@@ -138,30 +139,11 @@ __device__ __forceinline__ float sqdist(float px, float py, float pz, float sx, 
     return s + zz;
 }
 
-// Correctly rounded FP32 square root of x in [0, +inf] (NaN passes through).
-// The FP64 root rounded to FP32 is within one unit of the answer; it is then
-// checked against the rounding boundaries on either side, the midpoints
-// between r and its FP32 neighbours.  A midpoint has at most 25 significant
-// bits, so its FP64 square is exact and never an FP32 value: the comparisons
-// decide the rounding exactly and a tie cannot occur.
-__device__ __forceinline__ float sqrt_rn(float x)
-{
-    if (!(x > 0.0f) || x == INFINITY)
-        return x;
-    float r = (float)sqrt((double)x);
-    const double xd = (double)x;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const uint32_t rb = __float_as_uint(r);
-        const double up = 0.5 * ((double)r + (double)__uint_as_float(rb + 1u));
-        const double dn = 0.5 * ((double)r + (double)__uint_as_float(rb - 1u));
-        if (xd > up * up)
-            r = __uint_as_float(rb + 1u);
-        else if (xd < dn * dn)
-            r = __uint_as_float(rb - 1u);
-    }
-    return r;
-}
+// Correctly rounded FP32 square root of x in [0, +inf] (NaN passes through):
+// the compiler's expansion of sqrtf, which is correctly rounded unless that is
+// switched off.  (Compared with the FP64 root, rounded and checked against the
+// midpoints to both neighbours, for every FP32 value.)
+__device__ __forceinline__ float sqrt_rn(float x) { return sqrtf(x); }
 
 // Euclidean mode (RFPS_F_SQRT).  Sec. 3.4.3 (eq. point_distance_update)
 // states the distance update with the Euclidean norm; its FP32 value is the rounded root of d2.  The state

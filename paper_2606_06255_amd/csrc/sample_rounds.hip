@@ -671,11 +671,14 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                             if (s + 1 < steps)
                                 load(lane_u32(m1, ho), qn, dn, vn);
                             unsigned long long mine = ballot64(ctile == h);
-                            while (mine) {
-                                const int c = __builtin_ctzll(mine);
-                                mine &= mine - 1;
-                                const Cand l = unpack_cand(sh.rec[rb + c][0], sh.rec[rb + c][1]);
-                                d = min_dist(d, sqdist(q.x, q.y, q.z, l.x, l.y, l.z), euclid);
+                            if (mine) {
+                                float least = INFINITY;
+                                for (; mine; mine &= mine - 1) {
+                                    const int c = __builtin_ctzll(mine);
+                                    const Cand l = unpack_cand(sh.rec[rb + c][0], sh.rec[rb + c][1]);
+                                    least = fminf(least, sqdist(q.x, q.y, q.z, l.x, l.y, l.z));
+                                }
+                                d = min_dist(d, least, euclid);
                             }
                         }
                     }
@@ -1500,16 +1503,21 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                                 tl.apairs += (unsigned long long)__popc(f);
                             if (tele && lane == 0)
                                 tl.visited += (unsigned long long)__popc(f) * cnt;
+                            // (the class top of the smallest distance is the
+                            // smallest class top)
+                            float least = INFINITY;
                             while (f) {
                                 const int kk = cb * kBlk + __builtin_ctz(f);
                                 f &= f - 1;
                                 const float4 s4 = sh.pk[kk];
                                 if (tele && count_skip && valid) {
                                     const float dx = q.x - s4.x, dy = q.y - s4.y, dz = q.z - s4.z;
-                                    tl.skipped += (dx * dx >= d || dy * dy >= d || dz * dz >= d) ? 1 : 0;
+                                    const float dn = fminf(d, least);
+                                    tl.skipped += (dx * dx >= dn || dy * dy >= dn || dz * dz >= dn) ? 1 : 0;
                                 }
-                                d = min_dist(d, sqdist(q.x, q.y, q.z, s4.x, s4.y, s4.z), euclid);
+                                least = fminf(least, sqdist(q.x, q.y, q.z, s4.x, s4.y, s4.z));
                             }
+                            d = min_dist(d, least, euclid);
                             const bool changed = valid && d < d0;
                             const unsigned long long um = ballot64(changed);
                             if (tele && lane == 0) {
