@@ -87,10 +87,13 @@ typedef struct rfps_params {
     int32_t tile;
     /* Workgroups of the persistent sampler, 1..256 and at most the number of
      * compute units (all must be resident at once); 0 = one per compute unit,
-     * or half of them for the multi-pick sampler on clouds below 65,536 points. */
+     * of which the multi-pick sampler uses as many as the cloud's tiles and
+     * samples call for (its capacity is that of one per compute unit, or half
+     * of them on clouds below 65,536 points). */
     int32_t groups;
     /* Lookahead depth of the multi-pick sampler: every workgroup proposes
-     * this many local candidates per exchange round; 2, 3, 4 or 8 (0 = 2).
+     * this many local candidates per exchange round; 2, 3, 4 or 8 (0 = the
+     * library's choice; its capacity is that of 2).
      * Output-neutral, like n_vox, tile and groups. */
     int32_t lookahead;
     /* RFPS_F_* bits. */
@@ -207,8 +210,9 @@ rfps_status rfps_build_index(const float *xyz, int32_t n, const rfps_params *par
  * Sec. 3.4): one persistent kernel runs all m - 1 selections.  By default
  * each exchange between workgroups settles a whole round of selections
  * (certified multi-pick: every workgroup proposes `lookahead` candidates
- * from its own points and all workgroups replay the same exact merge);
- * RFPS_F_SINGLE_PICK exchanges once per selection instead.  Both return the
+ * from its own points and all workgroups replay the same exact merge); a
+ * cloud of a few thousand points with default groups and lookahead is sampled
+ * by one workgroup, without exchanges.  RFPS_F_SINGLE_PICK exchanges once per selection instead.  Both return the
  * plain FPS sequence bit for bit.
  *   index    host, a handle from rfps_build_index() whose work precedes this
  *            call in stream order.
@@ -299,8 +303,8 @@ rfps_status rfps_read_plain_status(const void *ws, size_t ws_bytes, void *stream
  * Sec. 3.1 tie rule) runs independently on every cloud of a batch; one call
  * builds one spherical-voxel index over all clouds (Sec. 3.2, every cloud on
  * its own grid) and samples all of them in one persistent launch.  Teams of
- * `groups` workgroups, each team on one XCD, take the clouds from a queue
- * ordered by decreasing N_c * m_c.  Output-neutral like the single-cloud
+ * workgroups, each team on one XCD, take the clouds from queues ordered by
+ * decreasing N_c * m_c.  Output-neutral like the single-cloud
  * parameters: the selections of every cloud equal plain FPS on that cloud.
  *   xyz       device, float32 [n][3]: the clouds one after the other.
  *   n         total points, 1 <= n <= 2^26.
@@ -315,8 +319,9 @@ rfps_status rfps_read_plain_status(const void *ws, size_t ws_bytes, void *stream
  *   params    host, may be NULL.  n_vox: 0 = per-cloud default bins, else
  *             the same bins for every cloud; tile as for rfps_build_index;
  *             groups: workgroups per cloud (a divisor of the compute units of
- *             one XCD, at least 2; 0 = all of them); lookahead 2, 3, 4 or 8 (0 =
- *             2).  RFPS_F_NO_PRUNE, RFPS_F_SINGLE_PICK and RFPS_F_TRACE are
+ *             one XCD, at least 2; 0 = for every cloud its own number, chosen
+ *             on the device from 1 to all of them; the capacity is that of all
+ *             of them); lookahead 2, 3, 4 or 8 (0 = the library's choice).  RFPS_F_NO_PRUNE, RFPS_F_SINGLE_PICK and RFPS_F_TRACE are
  *             not available here (RFPS_ERR_UNSUPPORTED).
  *   ws        device workspace of rfps_batched_workspace_size() bytes,
  *             256-byte aligned; calls on one workspace must not overlap.

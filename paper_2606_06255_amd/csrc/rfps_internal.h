@@ -461,7 +461,7 @@ inline hipError_t launch_persistent(const void *fn, int G, void **args, size_t l
     return hipLaunchKernel(fn, dim3(G), dim3(block), args, lds, s);
 }
 
-// A small cloud by one workgroup (sample_solo.hip): resets, samples and, after
+// A small cloud by one workgroup (sample_rfps.hip): resets, samples and, after
 // a failed build, marks the outputs.
 hipError_t launch_rfps_solo(const IndexView &v, int m, int start, bool euclid, int32_t *out_idx, float *out_d2,
                             hipStream_t s);
