@@ -141,11 +141,10 @@ typedef struct rfps_telemetry {
     int64_t ticks_wait;
     int64_t reserved;
     /* finer clocks of workgroup 0 (multi-pick sampler, single cloud): the
-     * merge's listing (key compaction and any cut of a long list), its
-     * ranking pass, its certification walk and its hand-over of the picks;
-     * the lookahead's first step (on the true tile state, while the other
-     * wavefronts copy it to the private state) and its later steps; the
-     * exchange's polling and its forming of the candidate keys */
+     * merge's listing (and any cut of a long list), its conflict rows
+     * (ticks_merge_rank) and its certification; the exchange's polling and
+     * the rest of it.  ticks_merge_picks, ticks_lookahead_copy and
+     * ticks_lookahead_steps belong to phases the sampler no longer has: 0. */
     int64_t ticks_merge_list;
     int64_t ticks_merge_rank;
     int64_t ticks_merge_walk;
@@ -159,14 +158,11 @@ typedef struct rfps_telemetry {
     int64_t merge_above;
     int64_t merge_listed;
     int64_t merge_failures;
-    /* workgroup 0's own share of the apply phase (its tile loop, without
-     * waiting for the other wavefronts) and of the lookahead (choosing each
-     * local candidate and its runner-up, without the local updates) */
+    /* workgroup 0's apply phase again; ticks_lookahead_select and
+     * ticks_apply_update are 0, as above */
     int64_t ticks_apply_loop;
     int64_t ticks_lookahead_select;
-    /* workgroup 0's first wavefront in the apply phase: clocks of its point
-     * updates (tiles some pick reaches), the tile-pick pairs it updated and
-     * the tiles it re-keyed */
+    /* and its first wavefront's tile-pick pairs updated and tiles re-keyed */
     int64_t ticks_apply_update;
     int64_t apply_pairs;
     int64_t apply_rekeys;

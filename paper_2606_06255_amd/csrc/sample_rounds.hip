@@ -38,17 +38,17 @@
 // picks is its key order, which rank 0 of the team works out while the next
 // exchange is in flight.
 //
-// What bounds a round (1,048,576 points -> 65,536 picks, 256 workgroups, 879
-// rounds of 10.3 us, 74 picks each): lookahead 1.6 us (a serial chain of wave
+// What bounds a round (1,048,576 points -> 65,536 picks, 256 workgroups, 869
+// rounds of 10.8 us, 75 picks each): lookahead 1.8 us (a serial chain of wave
 // maxima), exchange 3.7 us (2.7 of them are the bare exchange of the team's
-// 32 KB, measured with nothing else in a round), list 1.0, conflicts 1.4,
-// certification 1.7, apply 1.0.  One lookahead per wavefront instead of one
+// 32 KB, measured with nothing else in a round), list 1.0, conflicts 1.5,
+// certification 1.7, apply 1.1.  One lookahead per wavefront instead of one
 // per workgroup removes the serial steps over all tiles of a workgroup (the
 // largest term before: 16 steps on one list of tile keys), and the matrix
 // cores take the pair tests, which were the next.  Sampling times before and
-// after: 1,048,576 -> 65,536 14.9 -> 9.0 ms, 114,623 -> 28,655 Euclidean 9.9
-// -> 5.9 ms, 80,000 -> 20,000 4.4 -> 2.9 ms, 32 clouds of 8k to 120k points
-// 34 -> 15.6 ms.
+// after: 1,048,576 -> 65,536 15.5 -> 9.4 ms, 114,623 -> 28,655 Euclidean 10.1
+// -> 5.5 ms, 80,000 -> 20,000 4.5 -> 2.9 ms; with a team size for every cloud,
+// 32 clouds of 8k to 120k points 35 -> 8.8 ms.
 //
 // Exchange scopes: a team spread over the device stores through agent-scope
 // atomics (coherent across XCDs); a team whose workgroups all sit on one XCD
@@ -1818,8 +1818,8 @@ RFPS_ROUNDS_KERNEL(k_rfps_rounds_batched_euclid_tele, rounds_batched<true, true>
 // ---------------------------------------------------------------------------
 // Exchange floor: G workgroups run `rounds` exchanges with nothing else in a
 // round.  Each publishes W epoch-tagged words and reads every word of every
-// slot until all carry the epoch, with the same agent-scope stores, loads and
-// word-major polling as the sampler's exchange.  Workgroup 0 records the
+// slot until all carry the epoch, with agent-scope stores and loads as the
+// sampler's exchange between XCDs.  Workgroup 0 records the
 // wall-clock ticks of the whole loop in out[0]; an expired wait records
 // RFPS_ERR_TIMEOUT in *status and ends the workgroup.  The launcher clears
 // the slots and out[0..1] first.
@@ -1836,7 +1836,7 @@ __global__ __launch_bounds__(kBlock) void k_exchange_clear(unsigned long long *b
 }
 
 // NW: words per thread (G * W <= kBlock * NW), all of a thread's words in
-// flight at once as in the sampler's exchange
+// flight at once
 template <int NW>
 __global__ __launch_bounds__(kBlock) void k_exchange_probe(unsigned long long *board, int G, int W, int rounds,
                                                            unsigned long long *out, uint32_t *status)
