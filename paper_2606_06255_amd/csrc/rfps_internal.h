@@ -21,9 +21,9 @@ constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxGroups = 256;      // one exchange slot per thread of a workgroup
 constexpr int kSlotWords = 5;        // d2, ~orig, x, y, z, each tagged with the epoch
 constexpr int kMaxSlotWords = 64;    // largest slot of any exchange protocol (words)
-// Exchange board: a single cloud uses 2 * G slots; a batch gives every team
-// of T workgroups 2 * T slots plus a control slot, (256 / T) * (2T + 1) slots
-// in all, at most 576 for T >= 4.
+// Exchange board: a single cloud uses 2 * G slots; a batch gives every
+// workgroup two slots and every level of team sizes a control word per
+// workgroup.
 constexpr int kBoardWords = 640 * kMaxSlotWords;
 constexpr int kMaxNVox = 1024;
 constexpr int kMaxShells = 64;       // range shells of one cloud (the last one is open-ended)
@@ -255,13 +255,6 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
     return ((unsigned long long)mhi << 32) | mlo;
 }
 
-// Minimum of non-negative floats (distances, +inf allowed): their bit
-// patterns order like the values.
-__device__ __forceinline__ float wave_min_dist(float v)
-{
-    return __uint_as_float(wave_min_u32(__float_as_uint(v)));
-}
-
 __device__ __forceinline__ float wave_min_f32(float v)
 {
 #pragma unroll
@@ -276,14 +269,6 @@ __device__ __forceinline__ float wave_max_f32(float v)
         v = fmaxf(v, __shfl_xor(v, off, kWave));
     return v;
 }
-__device__ __forceinline__ double wave_max_f64(double v)
-{
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1)
-        v = fmax(v, __shfl_xor(v, off, kWave));
-    return v;
-}
-
 // Order-preserving map of a finite float to uint32 (for atomic min / max).
 __device__ __forceinline__ uint32_t f2ord(float f)
 {

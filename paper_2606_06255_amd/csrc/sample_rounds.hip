@@ -1988,6 +1988,8 @@ hipError_t launch_rfps_rounds(const IndexView &v, int m, int start, const Sample
 // writes the cloud's first output (its start, at distance +inf).  The counters
 // the sampler does not keep are set by the first workgroup.
 constexpr int kBatchPlanBlock = 256;
+static_assert(kMaxGroups * (kBatchSlotWords + kBatchLevels) <= kBoardWords, "a batch's slots and control words");
+static_assert(kBatchSlotWords == 2 * kMaxSlotWords && (kBatchK + 1) * kUnit <= kMaxSlotWords, "a slot's units");
 __global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr, const uint32_t *__restrict__ tstart,
                                                                 const uint32_t *__restrict__ tcnt, BatchCtl bc,
                                                                 uint32_t *__restrict__ tile_first,
