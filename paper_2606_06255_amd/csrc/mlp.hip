@@ -15,11 +15,11 @@
 // the loss and the backward pass with everything in LDS, and k_wgrad forms the
 // weight gradients, one 16 x 16 tile per workgroup.  The arithmetic is 0.3
 // GFLOP for 2,000 rows; what bounds both is their chains of loads and matrix
-// instructions, so every chain is cut as short as the device allows (a
-// product over the rows is split over eight wavefronts, and no step of the
-// backward pass waits for a launch).  2,000 rows: 1,565 -> 30 us; as 14
-// launches, the three one-workgroup column sums and the loss alone took over
-// a millisecond.
+// instructions, so every chain is cut as short as the device and the order of
+// the sums allow (a product over the rows is split over eight wavefronts, and
+// no step of the backward pass waits for a launch).  2,000 rows: 1,532 -> 34
+// us; as 14 launches, the three one-workgroup column sums and the loss alone
+// took over a millisecond.
 #include <math.h>
 
 #include <algorithm>
@@ -63,10 +63,6 @@ struct State {
     uint32_t *step;  // Adam steps taken
 };
 
-// bf16 pair of a word.
-__device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
-
 __device__ __forceinline__ floatx4 mma(float a, float b, floatx4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -74,51 +70,10 @@ __device__ __forceinline__ floatx4 mma(float a, float b, floatx4 c)
 
 // Matrix instructions take A element (i, k) in lane i + 16k and B element
 // (k, j) in lane j + 16k; result element (i, j) is in lane j + 16 (i / 4),
-// component i % 4.  Which four k one instruction takes is free as long as both
-// operands agree: over 32 of them, instruction s takes 8 q + s from lanes
-// 16 q .., so that a lane's values are eight neighbours in memory.
-struct Bf8 {
-    uint32_t u[4];
-};
-__device__ __forceinline__ Bf8 load_bf8(const uint16_t *p)  // 8-byte aligned
-{
-    const uint2 a = *reinterpret_cast<const uint2 *>(p), b = *reinterpret_cast<const uint2 *>(p + 4);
-    return {{a.x, a.y, b.x, b.y}};
-}
-// c += A B over 32 k: a is the lane's eight values of A in LDS (16-byte aligned).
-__device__ __forceinline__ floatx4 mma32(const float *a, const Bf8 &b, floatx4 c)
-{
-    const floatx4 x = *reinterpret_cast<const floatx4 *>(a), y = *reinterpret_cast<const floatx4 *>(a + 4);
-    c = mma(x[0], bf_lo(b.u[0]), c);
-    c = mma(x[1], bf_hi(b.u[0]), c);
-    c = mma(x[2], bf_lo(b.u[1]), c);
-    c = mma(x[3], bf_hi(b.u[1]), c);
-    c = mma(y[0], bf_lo(b.u[2]), c);
-    c = mma(y[1], bf_hi(b.u[2]), c);
-    c = mma(y[2], bf_lo(b.u[3]), c);
-    return mma(y[3], bf_hi(b.u[3]), c);
-}
-
-// The same in FP64.  The hidden layers' inputs are summed so: their signs
-// decide which units pass a gradient, and a rounding error that turns one of
-// the 256,000 signs of 2,000 rows changes the gradient by more than all other
-// errors together.  An FP64 instruction takes twice an FP32 one's time; its
-// result element (i, j) is in lane j + 16 (i % 4), component i / 4.
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ doublex4 mma(double a, double b, doublex4 c)
-{
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-template <typename T>
-__device__ __forceinline__ doublex4 mma32(const T *a, const Bf8 &b, doublex4 c)
-{
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        c = mma((double)a[2 * q], (double)bf_lo(b.u[q]), c);
-        c = mma((double)a[2 * q + 1], (double)bf_hi(b.u[q]), c);
-    }
-    return c;
-}
+// component i % 4.  A row's products are added in the order of k, four to an
+// instruction: the signs of the hidden layers' inputs decide which units pass
+// a gradient, and another order, or a wider sum, turns a sign now and then,
+// which changes the gradient by far more than rounding does.
 
 // What the backward pass leaves for the weight gradients.
 struct RowArrays {
@@ -128,100 +83,94 @@ struct RowArrays {
 
 // 16 rows of the batch: Y = X -> 64 ReLU -> 64 ReLU -> 72 outputs, and with
 // GRAD the loss sum w (Y - T)^2 / B, dY = 2 w (Y - T) / B and the gradients of
-// both hidden layers' inputs.  Eight wavefronts: the first layer's four output
-// tiles, each over two halves of the 516 inputs; one tile per wavefront after
-// that.  All weights a wavefront needs are loaded before the first barrier, so
-// the later layers wait for LDS only.  LDS row strides are 4 mod 64 words (12
-// for dY), which spreads the 16 rows of an operand over all banks.
+// both hidden layers' inputs.  One 16 x 16 output tile per wavefront; a first
+// layer's tile is one chain of 129 matrix instructions (32 clocks each), which
+// is what bounds the kernel.  The first layer's weights and the inputs are
+// staged in LDS by all eight wavefronts with wide loads, and the other layers'
+// weights are loaded before the first barrier, so the later layers wait for
+// LDS only.  LDS row strides are 4 mod 64 words (12 for dY; 2 for the weights,
+// whose words hold two values), which spreads the 16 rows of an operand over
+// all banks.
 constexpr int kRows = 16, kRowsBlock = 512;
-constexpr int kChunks = kIn / 32;                 // whole chunks of 32 inputs
-static_assert(kIn - 32 * kChunks == 4, "one more instruction for the rest");
+constexpr int kSteps1 = kIn / 4, kSteps2 = kH / 4, kSteps3 = kOut / 4;  // matrix instructions over 516, 64 and 72
+static_assert(kIn % 4 == 0 && kH % 4 == 0 && kOut % 4 == 0, "whole instructions");
 template <bool GRAD>
 __global__ __launch_bounds__(kRowsBlock) void k_rows(const float *__restrict__ master,
                                                      const uint16_t *__restrict__ wbf, const float *__restrict__ x,
                                                      const float *__restrict__ t, const float *__restrict__ wt, int B,
                                                      float *__restrict__ yout, RowArrays out)
 {
-    constexpr int sX = kIn, sH = kH + 4, sD = kH + 2, sY = kOut + 4;
+    constexpr int sX = kIn, sH = kH + 4, sY = kOut + 4;
+    constexpr int kW1Bytes = kH * kIn * 2;
+    static_assert(oW1 == 0 && kW1Bytes % 16 == 0, "copied in pieces of 16 bytes");
+    __shared__ __align__(16) uint16_t W1[kH * kIn];
     __shared__ __align__(16) float X[kRows * sX];
-    __shared__ __align__(16) double P[2][kRows * sD], A1[kRows * sD];
-    __shared__ __align__(16) float A2[kRows * sH], DY[kRows * sY], DZ[kRows * sH];
+    __shared__ __align__(16) float A1[kRows * sH], A2[kRows * sH], DY[kRows * sY], DZ[kRows * sH];
     __shared__ double s_loss[kRowsBlock / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 15, lk = lane >> 4;
     const int m0 = blockIdx.x * kRows;
     const int rows = min(kRows, B - m0);
-    const int n0 = (wave & 3) * 16, half = wave >> 2;
+    const int n0 = (wave & 3) * 16;
 
-    // weights: layer 1 (half of the chunks), then by wavefront
-    const uint16_t *w1 = wbf + oW1 + (size_t)(n0 + li) * kIn;
-    Bf8 c1[kChunks / 2];
-#pragma unroll
-    for (int c = 0; c < kChunks / 2; ++c)
-        c1[c] = load_bf8(w1 + (2 * c + half) * 32 + lk * 8);
-    const float rest = half == 0 ? bf16_to_f32(w1[kChunks * 32 + lk]) : 0.0f;
-    Bf8 c2[2], c3[2];
-    float b3w[18], b2w[16];
+    for (int e = tid; e < kW1Bytes / 16; e += kRowsBlock)
+        reinterpret_cast<uint4 *>(W1)[e] = reinterpret_cast<const uint4 *>(wbf + oW1)[e];
+    for (int e = tid; e < kRows * kIn; e += kRowsBlock)
+        X[e] = e < rows * kIn ? x[(size_t)m0 * kIn + e] : 0.0f;
+    float w2[kSteps2], w3[kSteps2], b3w[kSteps3], b2w[kSteps2];
     const int o3 = wave * 16 + li;  // output column of the third layer
     if (wave < 4) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-            c2[c] = load_bf8(wbf + oW2 + (size_t)(n0 + li) * kH + c * 32 + lk * 8);
+        for (int q = 0; q < kSteps2; ++q)
+            w2[q] = bf16_to_f32(wbf[oW2 + (size_t)(n0 + li) * kH + 4 * q + lk]);
         if constexpr (GRAD) {
 #pragma unroll
-            for (int q = 0; q < 18; ++q) {
-                const int k = q < 16 ? (q / 8) * 32 + lk * 8 + q % 8 : 64 + 4 * (q - 16) + lk;
-                b3w[q] = bf16_to_f32(wbf[oW3 + (size_t)k * kH + n0 + li]);
-            }
+            for (int q = 0; q < kSteps3; ++q)
+                b3w[q] = bf16_to_f32(wbf[oW3 + (size_t)(4 * q + lk) * kH + n0 + li]);
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
-                b2w[q] = bf16_to_f32(wbf[oW2 + (size_t)((q / 8) * 32 + lk * 8 + q % 8) * kH + n0 + li]);
+            for (int q = 0; q < kSteps2; ++q)
+                b2w[q] = bf16_to_f32(wbf[oW2 + (size_t)(4 * q + lk) * kH + n0 + li]);
         }
     }
     if (wave < 5) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-            c3[c] = load_bf8(wbf + oW3 + (size_t)min(o3, kOut - 1) * kH + c * 32 + lk * 8);
+        for (int q = 0; q < kSteps2; ++q)
+            w3[q] = bf16_to_f32(wbf[oW3 + (size_t)min(o3, kOut - 1) * kH + 4 * q + lk]);
     }
-    for (int e = tid; e < kRows * kIn; e += kRowsBlock)
-        X[e] = e < rows * kIn ? x[(size_t)m0 * kIn + e] : 0.0f;
     __syncthreads();
 
     // ---- layer 1 ----
-    {
-        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+    if (wave < 4) {
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        const float *xa = &X[li * sX + lk];
+        const uint16_t *wb = &W1[(n0 + li) * kIn + lk];
+#pragma unroll 16
+        for (int q = 0; q < kSteps1; ++q)
+            acc = mma(xa[4 * q], bf16_to_f32(wb[4 * q]), acc);
+        const float bias = master[ob1 + n0 + li];
 #pragma unroll
-        for (int c = 0; c < kChunks / 2; ++c)
-            acc = mma32(&X[li * sX + (2 * c + half) * 32 + lk * 8], c1[c], acc);
-        if (half == 0)
-            acc = mma((double)X[li * sX + kChunks * 32 + lk], (double)rest, acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            P[half][(4 * r + lk) * sD + n0 + li] = acc[r];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kRows * kH / kRowsBlock; ++q) {
-        const int e = q * kRowsBlock + tid, m = e / kH, n = e % kH;
-        const double z = P[0][m * sD + n] + P[1][m * sD + n] + (double)master[ob1 + n];
-        const double v = z > 0.0 ? z : 0.0;
-        A1[m * sD + n] = v;
-        if (GRAD && m < rows)
-            out.a1[(size_t)(m0 + m) * kH + n] = (float)v;
+        for (int r = 0; r < 4; ++r) {
+            const int m = 4 * lk + r;
+            const float z = acc[r] + bias;
+            const float v = z > 0.0f ? z : 0.0f;
+            A1[m * sH + n0 + li] = v;
+            if (GRAD && m < rows)
+                out.a1[(size_t)(m0 + m) * kH + n0 + li] = v;
+        }
     }
     __syncthreads();
     // ---- layer 2 ----
     if (wave < 4) {
-        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-            acc = mma32(&A1[li * sD + c * 32 + lk * 8], c2[c], acc);
-        const double bias = (double)master[ob2 + n0 + li];
+        for (int q = 0; q < kSteps2; ++q)
+            acc = mma(A1[li * sH + 4 * q + lk], w2[q], acc);
+        const float bias = master[ob2 + n0 + li];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const double z = acc[r] + bias;
-            const float v = z > 0.0 ? (float)z : 0.0f;
-            const int m = 4 * r + lk;
+            const int m = 4 * lk + r;
+            const float z = acc[r] + bias;
+            const float v = z > 0.0f ? z : 0.0f;
             A2[m * sH + n0 + li] = v;
             if (GRAD && m < rows)
                 out.a2[(size_t)(m0 + m) * kH + n0 + li] = v;
@@ -233,8 +182,8 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const float *__restrict__ m
     if (wave < 5) {
         floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
-            acc = mma32(&A2[li * sH + c * 32 + lk * 8], c3[c], acc);
+        for (int q = 0; q < kSteps2; ++q)
+            acc = mma(A2[li * sH + 4 * q + lk], w3[q], acc);
         if (o3 < kOut) {
             const float bias = master[ob3 + o3], sc = 2.0f / (float)B;
 #pragma unroll
@@ -276,10 +225,8 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const float *__restrict__ m
     if (wave < 4) {
         floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int q = 0; q < 18; ++q) {
-            const int k = q < 16 ? (q / 8) * 32 + lk * 8 + q % 8 : 64 + 4 * (q - 16) + lk;
-            acc = mma(DY[li * sY + k], b3w[q], acc);
-        }
+        for (int q = 0; q < kSteps3; ++q)
+            acc = mma(DY[li * sY + 4 * q + lk], b3w[q], acc);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = 4 * lk + r;
@@ -294,13 +241,13 @@ __global__ __launch_bounds__(kRowsBlock) void k_rows(const float *__restrict__ m
     if (wave < 4) {
         floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int q = 0; q < 16; ++q)
-            acc = mma(DZ[li * sH + (q / 8) * 32 + lk * 8 + q % 8], b2w[q], acc);
+        for (int q = 0; q < kSteps2; ++q)
+            acc = mma(DZ[li * sH + 4 * q + lk], b2w[q], acc);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = 4 * lk + r;
             if (m < rows)
-                out.dz1[(size_t)(m0 + m) * kH + n0 + li] = A1[m * sD + n0 + li] > 0.0 ? acc[r] : 0.0f;
+                out.dz1[(size_t)(m0 + m) * kH + n0 + li] = A1[m * sH + n0 + li] > 0.0f ? acc[r] : 0.0f;
         }
     }
 }
