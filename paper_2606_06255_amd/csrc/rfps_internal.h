@@ -22,7 +22,7 @@ constexpr int kMaxGroups = 256;      // one exchange slot per thread of a workgr
 constexpr int kSlotWords = 5;        // d2, ~orig, x, y, z, each tagged with the epoch
 constexpr int kMaxSlotWords = 64;    // largest slot of any exchange protocol (words)
 // Exchange board: a single cloud uses 2 * G slots; a batch gives every
-// workgroup two slots and every level of team sizes a control word per
+// workgroup two slots and every level of team sizes two control words per
 // workgroup.
 constexpr int kBoardWords = 640 * kMaxSlotWords;
 constexpr int kMaxNVox = 1024;

@@ -57,6 +57,7 @@
 // units until the words are there.
 #include <type_traits>
 
+#include "batch_teams.h"
 #include "rfps_internal.h"
 #include "round_layout.h"
 #include "solo_cloud.h"
@@ -1658,10 +1659,7 @@ RFPS_ROUNDS_KERNEL(k_rfps_rounds_wide_euclid_tele, rounds_single<5, true, true>)
 // Batches: teams of T workgroups, all on one XCD (found from the hardware
 // XCC id at run time), exchange through that XCD's L2.  The plan gives every
 // cloud a team size (a power of two, a level) and orders the clouds by
-// decreasing size and cost.  All workgroups of an XCD start as one team of
-// the largest level; a team takes the level's clouds until none is left and
-// then splits in two for the next level, down to single workgroups.  Teams
-// never join again, so a level's control word, once it says "no more", stays.
+// decreasing size and cost; batch_teams.h says how the teams take them.
 // Measured against one team of a whole XCD per cloud: 64 clouds of 512 to
 // 4,096 points 2.18 -> 0.78 ms (0.52 with small clouds in one workgroup and a
 // shorter build), 32 clouds of 8k to 120k points 16.1 -> 9.8 ms
@@ -1672,12 +1670,107 @@ __device__ __forceinline__ uint32_t xcc_id()
     return __builtin_amdgcn_s_getreg((20) | (0 << 6) | ((16 - 1) << 11)) & 0xffu;
 }
 
+// What a workgroup of a batch reaches of the device (see batch_teams.h).
+template <bool E, bool I>
+struct BatchIo {
+    static constexpr uint32_t kSpins = kSpinLimit;
+    const RoundArgs &a;
+    const int me;  // this workgroup among all, by XCD and place in it
+    unsigned char *const smem;
+    RoundShared &sh;
+    uint32_t &s_value;
+    RoundTele &tl;
+    unsigned long long led;  // rounds of the clouds this workgroup led
+    uint32_t epoch;
+
+    // Control words: for every level a post, then for every level a count.  A
+    // team's are those of its first workgroup.
+    __device__ __forceinline__ unsigned long long *control(int word, int T)
+    {
+        return a.board + (size_t)kMaxGroups * kBatchSlotWords + (size_t)word * kMaxGroups + (me & ~(T - 1));
+    }
+    __device__ __forceinline__ uint32_t next(int lev) { return atomicAdd(&a.bstate->next[lev], 1u); }
+    __device__ __forceinline__ bool wanted(uint32_t q) { return a.bc.m[a.order[q]] >= 2; }
+    __device__ __forceinline__ void post(int lev, int T, unsigned long long v)
+    {
+        bstore<Scope::Xcd>(control(lev, T), v);
+    }
+    __device__ __forceinline__ unsigned long long posted(int lev, int T) { return ld_agent(control(lev, T)); }
+    // (nothing is handed over: a workgroup's reads have returned before it
+    // arrives, and what it stores next waits for the count)
+    __device__ __forceinline__ void arrive(int lev, int T)
+    {
+        __hip_atomic_fetch_add(control(kBatchLevels + lev, T), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ unsigned long long arrived(int lev, int T)
+    {
+        return ld_agent(control(kBatchLevels + lev, T));
+    }
+    __device__ __forceinline__ uint32_t first(int lev) { return a.bstate->level_first[lev]; }
+    template <class F>
+    __device__ __forceinline__ uint32_t one(F f)
+    {
+        if (threadIdx.x == 0) {
+            s_value = f();
+            if (s_value == kNoCloud)
+                set_status(&a.hdr->sample_status, RFPS_ERR_TIMEOUT);
+        }
+        __syncthreads();
+        const uint32_t v = s_value;
+        __syncthreads();
+        return v;
+    }
+    __device__ __forceinline__ bool sample(int lev, int T, int rank, uint32_t q)
+    {
+        const BatchCtl &bc = a.bc;
+        const int c = a.order[q];
+        if (!I && T == 1) {
+            const uint32_t p = (uint32_t)bc.offsets[c];  // the cloud's place in the input and among the sorted points
+            const SoloJob solo = {a.xs,
+                                  a.ys,
+                                  a.zs,
+                                  a.inv + p,
+                                  bc.offsets[c + 1] - bc.offsets[c],
+                                  bc.m[c],
+                                  bc.starts ? bc.starts[c] : 0,
+                                  a.out_idx + bc.out_offsets[c],
+                                  a.out_d2 ? a.out_d2 + bc.out_offsets[c] : nullptr};
+            solo_any<E>(solo, smem);
+            return true;
+        }
+        CloudJob job;
+        job.tb = a.tile_first[c];
+        job.te = a.tile_first[c + 1];
+        job.point_base = (uint32_t)bc.offsets[c];
+        job.m = bc.m[c];
+        job.start = bc.starts ? bc.starts[c] : 0;
+        job.out_idx = a.out_idx + bc.out_offsets[c];
+        job.out_d2 = a.out_d2 ? a.out_d2 + bc.out_offsets[c] : nullptr;
+        const uint32_t *bb = a.cl_bb + 6 * (size_t)c;
+        job.ox = 0.5f * ord2f(bb[0]) + 0.5f * ord2f(bb[3]);
+        job.oy = 0.5f * ord2f(bb[1]) + 0.5f * ord2f(bb[4]);
+        job.oz = 0.5f * ord2f(bb[2]) + 0.5f * ord2f(bb[5]);
+        // a workgroup's two slots lie side by side, so a team's slots are the
+        // slots of the teams it splits into.  K never falls from a level to
+        // the next (k_batch_levels): every word a team reads is rewritten at
+        // every second exchange of its members, whatever team they were in.
+        const Board board = {a.board + (size_t)(me - rank) * kBatchSlotWords, (uint32_t)kBatchSlotWords,
+                             (uint32_t)kMaxSlotWords};
+        const unsigned long long r0 = tl.rounds;
+        if (!sample_cloud<Scope::Xcd, 1, E, I>(a, job, rank, T, (int)a.bstate->level_k[lev], kBatchSteps, board, epoch,
+                                               smem, sh, tl, false, false))
+            return false;
+        led += rank == 0 ? tl.rounds - r0 : 0ull;
+        return true;
+    }
+};
+
 template <bool E, bool I>
 __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ RoundShared sh;
-    __shared__ uint32_t s_status, s_xcc, s_xrank, s_cloud, s_ok;
+    __shared__ uint32_t s_status, s_xcc, s_xrank, s_value, s_ok;
     const int tid = threadIdx.x;
     IndexHeader *hdr = a.hdr;
     const BatchCtl &bc = a.bc;
@@ -1711,101 +1804,14 @@ __device__ __forceinline__ void rounds_batched(const RoundArgs &a)
     __syncthreads();
     if (s_status || !s_ok)
         return;
-    const int per_xcd = bc.per_xcd, me = (int)s_xcc * per_xcd + (int)s_xrank;
-    unsigned long long *const ctl = a.board + (size_t)kMaxGroups * kBatchSlotWords;
-    const bool tele = I && (a.flags & RFPS_F_TELEMETRY) != 0;
     RoundTele tl;
-    unsigned long long led = 0;  // rounds of the clouds this workgroup led
-    uint32_t epoch = 0, turn = 0;
-    int lev = 0;
-    while (lev < kBatchLevels && (per_xcd >> lev) > 0) {
-        const int T = per_xcd >> lev, rank = (int)s_xrank & (T - 1);
-        const uint32_t first = st->level_first[lev], last = st->level_first[lev + 1];
-        if (first == last) {
-            ++lev;
-            continue;
-        }
-        // The team leader takes the level's next cloud that needs an exchange
-        // and posts it.  Every posted cloud costs at least one exchange, which
-        // the leader cannot finish before every member has read the post, and
-        // nothing follows the post that ends the level, so a post is never
-        // overwritten unread.
-        ++turn;
-        if (tid == 0) {
-            unsigned long long *word = ctl + (size_t)lev * kMaxGroups + (me - rank);
-            if (rank == 0) {
-                uint32_t q;
-                do {
-                    q = first + atomicAdd(&st->next[lev], 1u);
-                } while (q < last && bc.m[a.order[q]] < 2);
-                if (T > 1)
-                    bstore<Scope::Xcd>(word, ((unsigned long long)turn << 32) | min(q, last));
-                s_cloud = q;
-            } else {
-                uint32_t spin = 0;
-                unsigned long long v = 0;
-                for (; spin < kSpinLimit; ++spin) {
-                    v = ld_agent(word);
-                    if ((uint32_t)(v >> 32) == turn)
-                        break;
-                }
-                s_cloud = spin < kSpinLimit ? (uint32_t)v : 0xffffffffu;
-                if (spin >= kSpinLimit)
-                    set_status(&hdr->sample_status, RFPS_ERR_TIMEOUT);
-            }
-        }
-        __syncthreads();
-        const uint32_t q = s_cloud;
-        __syncthreads();
-        if (q == 0xffffffffu)
-            return;
-        if (q >= last) {
-            ++lev;
-            continue;
-        }
-        const int c = a.order[q];
-        if (!I && T == 1) {
-            const uint32_t p = (uint32_t)bc.offsets[c];  // the cloud's place in the input and among the sorted points
-            const SoloJob solo = {a.xs,
-                                  a.ys,
-                                  a.zs,
-                                  a.inv + p,
-                                  bc.offsets[c + 1] - bc.offsets[c],
-                                  bc.m[c],
-                                  bc.starts ? bc.starts[c] : 0,
-                                  a.out_idx + bc.out_offsets[c],
-                                  a.out_d2 ? a.out_d2 + bc.out_offsets[c] : nullptr};
-            solo_any<E>(solo, smem);
-            continue;
-        }
-        CloudJob job;
-        job.tb = a.tile_first[c];
-        job.te = a.tile_first[c + 1];
-        job.point_base = (uint32_t)bc.offsets[c];
-        job.m = bc.m[c];
-        job.start = bc.starts ? bc.starts[c] : 0;
-        job.out_idx = a.out_idx + bc.out_offsets[c];
-        job.out_d2 = a.out_d2 ? a.out_d2 + bc.out_offsets[c] : nullptr;
-        const uint32_t *bb = a.cl_bb + 6 * (size_t)c;
-        job.ox = 0.5f * ord2f(bb[0]) + 0.5f * ord2f(bb[3]);
-        job.oy = 0.5f * ord2f(bb[1]) + 0.5f * ord2f(bb[4]);
-        job.oz = 0.5f * ord2f(bb[2]) + 0.5f * ord2f(bb[5]);
-        // a workgroup's two slots lie side by side, so a team's slots are the
-        // slots of the teams it splits into.  K never falls from a level to
-        // the next (k_batch_levels): every word a team reads is rewritten at
-        // every second exchange of its members, whatever team they were in.
-        const Board board = {a.board + (size_t)(me - rank) * kBatchSlotWords, (uint32_t)kBatchSlotWords,
-                             (uint32_t)kMaxSlotWords};
-        const unsigned long long r0 = tl.rounds;
-        if (!sample_cloud<Scope::Xcd, 1, E, I>(a, job, rank, T, (int)st->level_k[lev], kBatchSteps, board, epoch, smem, sh,
-                                               tl, false, false))
-            return;
-        led += rank == 0 ? tl.rounds - r0 : 0ull;
-    }
-    if (tele) {
+    BatchIo<E, I> io = {a, (int)s_xcc * bc.per_xcd + (int)s_xrank, smem, sh, s_value, tl, 0ull, 0u};
+    if (!walk_levels(io, bc.per_xcd, (int)s_xrank))
+        return;
+    if (I && (a.flags & RFPS_F_TELEMETRY) != 0) {
         flush_telemetry(hdr, tl, false);
         if (tid == 0)
-            atomicAdd(&hdr->tele[kTeleExchanges], led);
+            atomicAdd(&hdr->tele[kTeleExchanges], io.led);
     }
 }
 
@@ -1988,7 +1994,7 @@ hipError_t launch_rfps_rounds(const IndexView &v, int m, int start, const Sample
 // writes the cloud's first output (its start, at distance +inf).  The counters
 // the sampler does not keep are set by the first workgroup.
 constexpr int kBatchPlanBlock = 256;
-static_assert(kMaxGroups * (kBatchSlotWords + kBatchLevels) <= kBoardWords, "a batch's slots and control words");
+static_assert(kMaxGroups * (kBatchSlotWords + 2 * kBatchLevels) <= kBoardWords, "a batch's slots and control words");
 static_assert(kBatchSlotWords == 2 * kMaxSlotWords && (kBatchK + 1) * kUnit <= kMaxSlotWords, "a slot's units");
 __global__ __launch_bounds__(kBatchPlanBlock) void k_batch_plan(IndexHeader *hdr, const uint32_t *__restrict__ tstart,
                                                                 const uint32_t *__restrict__ tcnt, BatchCtl bc,
