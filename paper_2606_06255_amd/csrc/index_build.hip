@@ -285,9 +285,12 @@ __device__ __forceinline__ void digit_ranks(const uint32_t *key, const bool *val
         const uint32_t at = (uint32_t)__popcll(peers & below);
         const uint32_t so_far = cnt[d];
         rank[r] = so_far + at;
-        // (a wavefront's LDS accesses keep their order)
+        // all lanes have read before one of them stores, and the next item
+        // reads what was stored
+        wave_sync();
         if (valid[r] && at == 0)
             cnt[d] = so_far + (uint32_t)__popcll(peers);
+        wave_sync();
     }
 }
 // Turns the wavefronts' counts into first positions: base of the digit plus

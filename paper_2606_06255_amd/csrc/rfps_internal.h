@@ -218,6 +218,17 @@ constexpr int kDppBcast31 = 0x143;
 // a ballot of a compound condition first turns it into a value per lane.
 __device__ __forceinline__ unsigned long long ballot64(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 
+// Orders the LDS accesses of a wavefront's lanes before and after it: what one
+// lane stored before, another lane reads after.  The hardware keeps a
+// wavefront's LDS accesses in order; this keeps the compiler from moving them
+// (no instruction comes of it).  All lanes must call it.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // (the first operand, kept by lanes without a source, is the identity of the
 // operation: the move then folds into it, one instruction a step)
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)

@@ -572,6 +572,8 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
         // its own candidate holds the lowered key in LDS until the lookahead
         // ends, when the true key is put back.
         {
+            // (lane 0 stored the tile keys of the apply phase)
+            wave_sync();
             const int rb = wave * steps;
             unsigned long long bound = 0;
             // candidate s: lane p of the loaded tile (coordinates q, distance
@@ -664,6 +666,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                                 load(lane_u32(m1, ho), qn, dn, vn);
                             unsigned long long mine = ballot64(ctile == h);
                             if (mine) {
+                                wave_sync();  // the records are other lanes'
                                 float least = INFINITY;
                                 for (; mine; mine &= mine - 1) {
                                     const int c = __builtin_ctzll(mine);
@@ -721,6 +724,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                             curk = bk;
                             load(meta, q, d, valid);
                             unsigned long long mine = ballot64(ctile == bt);
+                            wave_sync();  // the records are other lanes'
                             while (mine) {
                                 const int c = __builtin_ctzll(mine);
                                 mine &= mine - 1;
@@ -749,11 +753,14 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                                 }
                                 ++nsv;
                             }
+                            wave_sync();  // the scan before has read the keys
                             if (lane == 0)
                                 tkey[wb + cur] = nk;
+                            wave_sync();
                             scan();
                         }
                     }
+                    wave_sync();
                     if (lane < nsv)
                         tkey[wb + svt] = svk;
                 }
