@@ -1475,14 +1475,18 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                         __builtin_amdgcn_mfma_f32_16x16x4f32(av2, bv, f32x4{t4.x, t4.y, t4.z, t4.w}, 0, 0, 0);
                     unsigned long long mr[4] = {ballot64(!(dd[0] >= 0.0f)), ballot64(!(dd[1] >= 0.0f)),
                                                 ballot64(!(dd[2] >= 0.0f)), ballot64(!(dd[3] >= 0.0f))};
-                    if (tele && lane == 0)
-                        tl.pruned += (unsigned long long)min(kBlk, P - cb * kBlk) * min(kBlk, ntw - rb) -
-                                     (unsigned long long)(__popcll(mr[0]) + __popcll(mr[1]) + __popcll(mr[2]) +
-                                                          __popcll(mr[3]));
-                    if (!(mr[0] | mr[1] | mr[2] | mr[3]))
-                        continue;
                     // (a tile that is never skipped passes the padding too)
                     const unsigned long long cols = ballot64(cb * kBlk + li < P);
+                    if (tele) {
+                        int kept = 0;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            kept += __popcll(mr[r] & cols & ballot64(rb + 4 * lg + r < ntw));
+                        if (lane == 0)
+                            tl.pruned += (unsigned long long)(min(kBlk, P - cb * kBlk) * min(kBlk, ntw - rb) - kept);
+                    }
+                    if (!(mr[0] | mr[1] | mr[2] | mr[3]))
+                        continue;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         unsigned long long m = mr[r] & cols;
