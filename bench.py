@@ -36,9 +36,8 @@ HBM_PEAK_GBS = 8000.0
 # LDS: 256 compute units x 128 bytes per clock x 2.4 GHz (the per-CU LDS rate
 # of CDNA3, taken as the floor for gfx950)
 LDS_PEAK_GBS = 256 * 128 * 2.4
-PHASES = ("lookahead", "lookahead_copy", "lookahead_select", "exchange", "exchange_poll", "exchange_keys",
-          "wait", "merge", "merge_list", "merge_rank", "merge_walk", "merge_picks", "apply", "apply_loop",
-          "apply_update")
+PHASES = ("lookahead", "lookahead_steps", "exchange", "exchange_poll", "exchange_keys", "wait", "merge", "merge_list",
+          "merge_rank", "merge_walk", "merge_picks", "apply", "apply_update")
 WORKLOADS = {
     "dense_lidar": "dense LiDAR-like cloud, 128 beams x 8192 azimuth, N=1,048,576, M=65,536",
     "room": "indoor room-like cloud, N=80,000, M=20,000",
@@ -217,7 +216,6 @@ def main():
     clk = rf.read_telemetry(idx)
     nr = max(1, clk["exchanges"])
     phases = {k: clk["ticks_" + k] / clk["tick_hz"] / nr * 1e6 for k in PHASES}
-    phases["lookahead_update"] = phases["lookahead"] - phases["lookahead_copy"] - phases["lookahead_select"]
     phases["round"] = sum(phases[k] for k in ("lookahead", "exchange", "merge", "apply"))
     merge_stats = {"above": clk["merge_above"] / nr, "listed": clk["merge_listed"] / nr,
                    "failures": clk["merge_failures"] / nr, "wg0_apply_pairs": clk["apply_pairs"] / nr,

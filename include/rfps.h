@@ -118,7 +118,10 @@ typedef struct rfps_index {
     size_t ws_bytes;
 } rfps_index;
 
-/* Counters accumulated by a sampling call made with RFPS_F_TELEMETRY. */
+/* Counters accumulated by a sampling call made with RFPS_F_TELEMETRY.  They
+ * are the multi-workgroup samplers': a small cloud that an uninstrumented call
+ * gives to one workgroup (see rfps_sample) is sampled by a team here, with the
+ * same outputs. */
 typedef struct rfps_telemetry {
     int64_t iters;          /* update rounds after the initial one (m - 2 when m >= 2) */
     int64_t tiles;          /* tiles in the index */
@@ -136,15 +139,17 @@ typedef struct rfps_telemetry {
     int64_t ticks_merge;
     int64_t ticks_apply;
     int64_t tick_hz;        /* rate of those ticks (filled in by the reader) */
-    /* of ticks_exchange, the part spent re-reading slot words that were not
-     * yet published at the first pass (waiting for the slowest workgroup) */
+    /* of ticks_exchange, the part the first wavefront spent re-reading slot
+     * words that were not yet published at its first pass (waiting for the
+     * slowest workgroup it reads, and for the stores' way) */
     int64_t ticks_wait;
     int64_t reserved;
     /* finer clocks of workgroup 0 (multi-pick sampler, single cloud): the
      * merge's listing (and any cut of a long list), its conflict rows
-     * (ticks_merge_rank) and its certification; the exchange's polling and
-     * the rest of it.  ticks_merge_picks, ticks_lookahead_copy and
-     * ticks_lookahead_steps belong to phases the sampler no longer has: 0. */
+     * (ticks_merge_rank), its certification (ticks_merge_walk) and its
+     * hand-over of the picks; the lookahead's steps after the first; the
+     * exchange's polling and the rest of it.  ticks_lookahead_copy belongs to
+     * a phase the sampler no longer has: 0. */
     int64_t ticks_merge_list;
     int64_t ticks_merge_rank;
     int64_t ticks_merge_walk;
@@ -158,11 +163,13 @@ typedef struct rfps_telemetry {
     int64_t merge_above;
     int64_t merge_listed;
     int64_t merge_failures;
-    /* workgroup 0's apply phase again; ticks_lookahead_select and
-     * ticks_apply_update are 0, as above */
+    /* workgroup 0's apply phase again (it has no wait for other wavefronts);
+     * ticks_lookahead_select is 0, as above */
     int64_t ticks_apply_loop;
     int64_t ticks_lookahead_select;
-    /* and its first wavefront's tile-pick pairs updated and tiles re-keyed */
+    /* its first wavefront in the apply phase: clocks of its point updates
+     * (tiles some pick reaches), the tile-pick pairs it updated and the tiles
+     * it re-keyed */
     int64_t ticks_apply_update;
     int64_t apply_pairs;
     int64_t apply_rekeys;

@@ -327,9 +327,9 @@ __device__ __forceinline__ int conflict_pos(int w, int b, int qs)
 struct RoundTele {
     unsigned long long tests = 0, pruned = 0, visited = 0, skipped = 0, updated = 0, resync = 0;
     unsigned long long ph[5] = {0, 0, 0, 0, 0};  // lookahead, exchange, merge, apply, exchange wait
-    // finer clocks: merge list / conflicts / walk / picks, lookahead first / later
-    // steps, exchange poll / keys, apply, lookahead selects, apply updates
-    unsigned long long sub[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    // finer clocks: merge list / conflicts / certification / picks, lookahead
+    // steps after the first, exchange poll / rest, apply's point updates
+    unsigned long long list = 0, conflicts = 0, walk = 0, picks = 0, later = 0, poll = 0, rest = 0, update = 0;
     unsigned long long apairs = 0, arekeys = 0;  // wavefront 0's apply: tile-pick pairs updated, tiles re-keyed
     unsigned long long above = 0, listed = 0, fails = 0;
     unsigned long long rounds = 0;
@@ -374,7 +374,7 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long v,
 // G (K + 1) units are dealt to kRBlock threads).  Returns false when an
 // exchange failed (abort).
 template <Scope S, int NU, bool E, bool T>
-__device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int rank, const int G, const int K,
+__device__ __forceinline__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int rank, const int G, const int K,
                              const int steps, const Board &board, uint32_t &epoch, unsigned char *smem,
                              RoundShared &sh, RoundTele &tl, bool record_trace, bool clocks)
 {
@@ -574,6 +574,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
         {
             // (lane 0 stored the tile keys of the apply phase)
             wave_sync();
+            unsigned long long t_step = 0;  // when the first step was done
             const int rb = wave * steps;
             unsigned long long bound = 0;
             // candidate s: lane p of the loaded tile (coordinates q, distance
@@ -650,6 +651,8 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                         bound = umax64(nk, oth);
                         if (lane == s)
                             ctile = h;
+                        if (clocks && s == 0)
+                            t_step = wall_clock64();
                         if (++s == steps)
                             break;
                         bk = bound;
@@ -741,6 +744,8 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                         if (lane == s)
                             ctile = bt;
                         bound = umax64(nk, oth);
+                        if (clocks && s == 0)
+                            t_step = wall_clock64();
                         if (++s == steps)
                             break;
                         if (nk >= oth) {
@@ -765,6 +770,8 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                         tkey[wb + svt] = svk;
                 }
             }
+            if (clocks && t_step)
+                tl.later += wall_clock64() - t_step;
             if (lane == 0)
                 atomicMax(&sh.gb[round & 1u], bound);
         }
@@ -830,6 +837,9 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                 rank_out();
             const unsigned long long *sbase = board.base + (epoch & 1u) * board.par_words;
             unsigned long long b = 0;
+            // The passes after the first are waiting.  (Of the whole first
+            // wavefront: thread 0 reads its own workgroup's slot.)
+            const bool timed_wave = T && ballot64(clocks) != 0ull;
             unsigned long long t_first = 0;
             bool lost = false;
             const uint32_t tagw = tag << 16;
@@ -848,8 +858,8 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                 bool p0 = uin[0], p1 = uin[1];
                 ck[0] = ck[1] = 0ull;
                 for (uint32_t spin = 0; p0 || p1; ++spin) {
-                    if (clocks && spin == 1 && !t_first)
-                        t_first = wall_clock64();  // the passes after the first are waiting
+                    if (timed_wave && spin == 1 && !t_first)
+                        t_first = wall_clock64();
                     u32x4 x0, y0, x1, y1;
                     load_unit2(sbase + upos[0], sbase + upos[1], x0, y0, x1, y1);
                     if (p0 && fresh(x0, y0)) {
@@ -871,7 +881,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                     ck[u] = 0ull;
                     bool p0 = uin[u];
                     for (uint32_t spin = 0; p0; ++spin) {
-                        if (clocks && spin == 1 && !t_first)
+                        if (timed_wave && spin == 1 && !t_first)
                             t_first = wall_clock64();
                         u32x4 x0, y0;
                         load_unit(sbase + upos[u], x0, y0);
@@ -887,6 +897,14 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
             }
             if (lost)
                 sh.abort = 1;
+            if (timed_wave && ballot64(t_first != 0ull)) {
+                int first;
+                const unsigned long long t0 = ~wave_max_key(t_first ? ~t_first : 0ull, first);
+                if (clocks)
+                    tl.ph[4] += wall_clock64() - t0;
+            }
+            if (clocks)
+                tl.poll += wall_clock64() - t_mark;
             // what the list needs of this thread's candidates, while the
             // wavefront's bound is reduced
             prepare();
@@ -894,10 +912,6 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
             b = wave_max_key(b, at);
             if (lane == 0 && b)
                 atomicMax(&sh.sx[round & 1u], b);
-            if (clocks && t_first)
-                tl.ph[4] += wall_clock64() - t_first;
-            if (clocks)
-                tl.sub[6] += wall_clock64() - t_mark;
             __syncthreads();
             if (sh.abort) {
                 if (tid == 0) {
@@ -930,7 +944,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
         if (clocks) {
             const unsigned long long t = wall_clock64();
             tl.ph[1] += t - t_mark;
-            tl.sub[7] += t - t_mark;  // the poll's share is taken off below
+            tl.rest += t - t_mark;  // the poll's share is taken off below
             t_mark = t;
         }
 
@@ -1099,7 +1113,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
         unsigned long long t_sub = 0;
         if (clocks) {
             t_sub = wall_clock64();
-            tl.sub[0] += t_sub - t_mark;
+            tl.list += t_sub - t_mark;
             tl.listed += L;
         }
 
@@ -1179,7 +1193,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
         __syncthreads();
         if (clocks) {
             const unsigned long long t = wall_clock64();
-            tl.sub[1] += t - t_sub;
+            tl.conflicts += t - t_sub;
             t_sub = t;
         }
 
@@ -1285,6 +1299,11 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
 #pragma unroll
                     for (int k = 0; k < NW; ++k)
                         lv[k] &= ballot64(key[k] > scur);
+                }
+                if (clocks) {
+                    const unsigned long long t = wall_clock64();
+                    tl.walk += t - t_sub;
+                    t_sub = t;
                 }
                 // the picks, in any order, for the apply phase and the outputs
                 uint32_t n = 0;
@@ -1401,6 +1420,11 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                 }
                 __syncthreads();
             }
+            if (clocks) {
+                const unsigned long long t = wall_clock64();
+                tl.walk += t - t_sub;
+                t_sub = t;
+            }
             // the picks, in any order, for the apply phase and the outputs
             uint32_t n = 0, base = 0;
 #pragma unroll
@@ -1425,7 +1449,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
             }
         }
         if (clocks)
-            tl.sub[2] += wall_clock64() - t_sub;
+            tl.picks += wall_clock64() - t_sub;
         __syncthreads();
         const int PN = (int)sh.npick;  // picks certified; the last round may need fewer
         const int P = min(PN, job.m - j);
@@ -1502,6 +1526,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                             const float4 q = pq[pp];
                             float d = pd[pp];
                             const float d0 = d;
+                            const unsigned long long t_upd = clocks ? wall_clock64() : 0ull;
                             if (clocks)
                                 tl.apairs += (unsigned long long)__popc(f);
                             if (tele && lane == 0)
@@ -1534,6 +1559,8 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
                                 if (clocks)
                                     ++tl.arekeys;
                             }
+                            if (clocks)
+                                tl.update += wall_clock64() - t_upd;
                         }
                     }
                 }
@@ -1541,7 +1568,6 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
         }
         if (clocks) {
             const unsigned long long t = wall_clock64();
-            tl.sub[8] += t - t_mark;
             tl.ph[3] += t - t_mark;
         }
     }
@@ -1558,7 +1584,7 @@ __device__ bool sample_cloud(const RoundArgs &a, const CloudJob &job, const int 
 }
 
 // Adds the per-thread telemetry of a workgroup to the header counters.
-__device__ void flush_telemetry(IndexHeader *hdr, const RoundTele &tl, bool clocks)
+__device__ __forceinline__ void flush_telemetry(IndexHeader *hdr, const RoundTele &tl, bool clocks)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const unsigned long long v[6] = {tl.tests, tl.pruned, tl.visited, tl.skipped, tl.updated, tl.resync};
@@ -1572,20 +1598,21 @@ __device__ void flush_telemetry(IndexHeader *hdr, const RoundTele &tl, bool cloc
             atomicAdd(&hdr->tele[2 + q], s);
     }
     if (clocks) {
+#pragma unroll
         for (int q = 0; q < 4; ++q)
             atomicAdd(&hdr->tele[kTeleTicksLookahead + q], tl.ph[q]);
         atomicAdd(&hdr->tele[kTeleTicksWait], tl.ph[4]);
-        // the exchange's key forming is its phase minus its polling
-        const unsigned long long sub[8] = {tl.sub[0], tl.sub[1], tl.sub[2], tl.sub[3],
-                                           tl.sub[4], tl.sub[5], tl.sub[6], tl.sub[7] - tl.sub[6]};
-        for (int q = 0; q < 8; ++q)
-            atomicAdd(&hdr->tele[kTeleSub + q], sub[q]);
+        // (the fields between, of phases the sampler no longer has, stay 0)
+        const int at[7] = {0, 1, 2, 3, 5, 6, 7};
+        const unsigned long long fine[7] = {tl.list, tl.conflicts, tl.walk, tl.picks, tl.later, tl.poll, tl.rest - tl.poll};
+#pragma unroll
+        for (int q = 0; q < 7; ++q)
+            atomicAdd(&hdr->tele[kTeleSub + at[q]], fine[q]);
         atomicAdd(&hdr->tele[kTeleMergeStats + 0], tl.above);
         atomicAdd(&hdr->tele[kTeleMergeStats + 1], tl.listed);
         atomicAdd(&hdr->tele[kTeleMergeStats + 2], tl.fails);
-        atomicAdd(&hdr->tele[kTeleMergeStats + 3], tl.sub[8]);
-        atomicAdd(&hdr->tele[kTeleMergeStats + 4], tl.sub[9]);
-        atomicAdd(&hdr->tele[kTeleMergeStats + 5], tl.sub[10]);
+        atomicAdd(&hdr->tele[kTeleMergeStats + 3], tl.ph[3]);
+        atomicAdd(&hdr->tele[kTeleMergeStats + 5], tl.update);
         atomicAdd(&hdr->tele[kTeleMergeStats + 6], tl.apairs);
         atomicAdd(&hdr->tele[kTeleMergeStats + 7], tl.arekeys);
     }

@@ -40,3 +40,21 @@ def test_pruned_tests_are_counted_without_padding(rf, scale, n, groups):
     # one point a tile: a kept test visits exactly one point
     t = _telemetry(rf, P, n // 2, groups=groups, tile=1)
     assert t["points_visited"] == t["tile_tests"] - t["tiles_pruned"]
+
+
+@pytest.mark.parametrize("m,groups", [(6000, 0), (6000, 256), (1500, 64)])
+def test_clocks_cover_the_phases(rf, m, groups):
+    """The parts of a phase are clocked, and inside it.  The first workgroup
+    waits for another one in some rounds at least, a tick (10 ns) a round on
+    average (its own clocks make it a late one)."""
+    P = np.random.default_rng(3).random((24000, 3)).astype(np.float32)
+    t = _telemetry(rf, P, m, flags=rf.F_CLOCKS, groups=groups)
+    rounds = t["exchanges"]
+    assert rounds > 10
+    assert rounds <= t["ticks_wait"] <= t["ticks_exchange_poll"] <= t["ticks_exchange"]
+    assert 0 < t["ticks_lookahead_steps"] < t["ticks_lookahead"]
+    parts = [t["ticks_merge_" + k] for k in ("list", "rank", "walk", "picks")]
+    assert all(0 < v < t["ticks_merge"] for v in parts) and sum(parts) <= t["ticks_merge"]
+    assert 0 < t["ticks_apply_update"] < t["ticks_apply"] == t["ticks_apply_loop"]
+    assert t["apply_pairs"] >= t["apply_rekeys"] > 0
+    assert t["merge_above"] >= t["merge_listed"] > t["merge_failures"] >= 0
