@@ -422,9 +422,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_blocks(const uint32_t *in, uint
         partials[blockIdx.x] = total;
 }
 
-// One workgroup scans the per-block totals (nb <= kBlock * 64) and writes the
-// grand total to *total_out when it is not NULL.
-__global__ __launch_bounds__(kBlock) void k_scan_partials(uint32_t *partials, int nb, uint32_t *total_out)
+// One workgroup scans the per-block totals (nb <= kBlock * 64).
+__global__ __launch_bounds__(kBlock) void k_scan_partials(uint32_t *partials, int nb)
 {
     __shared__ uint32_t wsum[kWavesPerBlock];
     const int per = (nb + kBlock - 1) / kBlock;
@@ -442,8 +441,6 @@ __global__ __launch_bounds__(kBlock) void k_scan_partials(uint32_t *partials, in
             run += v;
         }
     }
-    if (threadIdx.x == 0 && total_out)
-        *total_out = total;
 }
 
 __global__ __launch_bounds__(kBlock) void k_scan_add(uint32_t *out, int n, const uint32_t *__restrict__ partials)
@@ -854,14 +851,13 @@ hipError_t launch_sqrt_out(float *d, int m, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const uint32_t *in, uint32_t *out, int n, uint32_t *partials, uint32_t *total,
-                       hipStream_t s)
+static hipError_t launch_scan(const uint32_t *in, uint32_t *out, int n, uint32_t *partials, hipStream_t s)
 {
     const int nb = blocks_for(n, kScanChunk);
     if (nb > kBlock * 64)
         return hipErrorInvalidValue;
     k_scan_blocks<<<nb, kBlock, 0, s>>>(in, out, n, partials);
-    k_scan_partials<<<1, kBlock, 0, s>>>(partials, nb, total);
+    k_scan_partials<<<1, kBlock, 0, s>>>(partials, nb);
     k_scan_add<<<blocks_for(n, kBlock), kBlock, 0, s>>>(out, n, partials);
     return hipGetLastError();
 }
@@ -881,7 +877,7 @@ static hipError_t launch_sort_and_tiles(const IndexView &v, const float *xyz, co
         if (pass)
             k_radix_hist<<<nblk, kSortBlock, 0, s>>>(kin, n, shift, v.hist, nblk, rows, range, skip);
         if (!rows) {
-            const hipError_t e = launch_scan(v.hist, v.hist, 256 * nblk, v.partials, nullptr, s);
+            const hipError_t e = launch_scan(v.hist, v.hist, 256 * nblk, v.partials, s);
             if (e != hipSuccess)
                 return e;
         }

@@ -15,6 +15,7 @@ constexpr int kRWaves = kRBlock / kRLanes;
 // Lookahead steps of a wavefront, and so candidates of a workgroup, at most.
 constexpr int kMaxSteps = 8;
 constexpr int kMaxRec = kRWaves * kMaxSteps;
+constexpr int kMinSteps = 2;
 // Candidates one merge lists, and so the selections one round may settle
 // (the merge stops there; a shorter round is always valid).
 constexpr int kList = 256;
@@ -114,6 +115,9 @@ RFPS_HOST_DEVICE inline int batch_k(int level, unsigned long long points_per_gro
 // Lookahead steps of a wavefront in a batch: 4 (2 cost up to 20 % where a
 // workgroup's share is full and gain 1 % where it is small; 8 gain nothing).
 constexpr int kBatchSteps = 4;
+// A workgroup publishes fewer candidates than it has (so its next one bounds
+// the rest): K is at most kBatchK here, and at most 8 otherwise.
+static_assert(kBatchK < kRWaves * kMinSteps && kMinSteps <= kBatchSteps, "candidates of a workgroup");
 
 // One workgroup for a whole cloud (solo_cloud.h): a ring of keys and the
 // coordinates in LDS, at most 16 points a thread in registers.

@@ -827,8 +827,8 @@ __device__ __forceinline__ bool sample_cloud(const RoundArgs &a, const CloudJob 
                     const int r = __popcll(ballot64(kq > kc) | (ballot64(kq == kc) & ((1ull << c) - 1ull)));
                     if (r < K && lane < kUnit)
                         bstore<S>(slot + r * kUnit + lane, tag64 | w);
-                    if ((r == K || (nr == K && c == 0)) && lane < kUnit) {
-                        const unsigned long long b = umax64(gb, r == K ? kc : 0ull);
+                    if (r == K && lane < kUnit) {  // (there are at least 16 candidates, more than K)
+                        const unsigned long long b = umax64(gb, kc);
                         bstore<S>(slot + K * kUnit + lane, tag64 | (lane == 0 ? b >> 32 : b & 0xffffffffull));
                     }
                 }
