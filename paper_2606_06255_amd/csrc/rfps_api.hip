@@ -373,7 +373,7 @@ rfps_status rfps_sample(const rfps_index *index, int32_t m, int32_t start, const
     // A small cloud with nothing asked for but the distance: one workgroup.
     // (128 workgroups hold any share of so few points, so no such call can
     // exceed the capacity.)
-    L.solo = !L.fixed_g && !L.K && L.R > 0 && index->n <= kSoloSingle && L.Gcap >= 128 &&
+    L.solo = !L.fixed_g && !L.K && L.R > 0 && solo_single(index->n, m) && L.Gcap >= 128 &&
              (L.flags & ~(RFPS_F_SQRT | RFPS_F_NO_POINT_SKIP)) == 0;
     const IndexView v = make_view(index->ws, index->n, index->n_vox, index->tile, index->shells);
     hipError_t e = launch_rfps_sample(v, m, start, L, out_idx, out_d2, static_cast<hipStream_t>(stream));

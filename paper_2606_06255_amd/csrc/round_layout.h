@@ -124,11 +124,19 @@ static_assert(kBatchK < kRWaves * kMinSteps && kMinSteps <= kBatchSteps, "candid
 constexpr uint32_t kSoloRingBytes = 1024;
 constexpr int kSoloPoints = 8192;
 RFPS_HOST_DEVICE inline uint32_t solo_lds(uint32_t n) { return kSoloRingBytes + n * 16u; }
-// Largest cloud a single call gives to one workgroup.  Measured, sampling of a
-// quarter of the points by one workgroup and by a team, from call to
-// completion in us: 512 points 43 | 155, 1,024 73 | 213, 2,048 167 | 263, 3,000
-// 270 | 301, 3,500 352 | 374, 4,000 400 | 378.
-constexpr int kSoloSingle = 3584;
+// Whether a single call gives a cloud to one workgroup.  Measured, sampling
+// from call to completion in us, by one workgroup and by a team.  A quarter of
+// the points: 512 points 43 | 155, 1,024 73 | 213, 2,048 167 | 263, 3,000
+// 270 | 301, 3,500 352 | 374, 4,000 400 | 378.  A selection costs one workgroup
+// the same throughout and a team less and less, so with eight points a lane
+// (above 3,072) most of a cloud is a team's: 3,584 points of a room, half of
+// them 701 | 709, three quarters 1,042 | 982, all 1,386 | 1,283; of a cube, all
+// 1,385 | 985.
+constexpr int kSoloSingle = 3584, kSoloSingleAll = 3072;
+RFPS_HOST_DEVICE inline bool solo_single(int n, int m)
+{
+    return n <= kSoloSingleAll || (n <= kSoloSingle && m <= n / 2);
+}
 static_assert(kSoloRingBytes + kSoloSingle * 16u <= 65536u, "no opt-in for more LDS");
 
 // Bytes a workgroup's share may take by that rule: what a compute unit has
