@@ -115,4 +115,16 @@ RFPS_HOST_DEVICE inline float filter_row(float limit, float n2)
     return t + 1e-36f;
 }
 
+// Whether the filter's margin around a candidate at squared distance n2 from
+// the origin spans a good part of what j selections at squared distances near
+// d cover, so that pairs of listed candidates (100 or so, spread over the
+// cloud) are kept without being near: the margin is 2^-16 n2, on a surface j
+// selections cover an area of about j d, and a list of 128 then keeps one
+// false pair a row from 2^-9 n2 = j d on.  (Unlikely clouds: one that fills
+// its box has n2 below j d.  NaN and overflow count as too far.)
+RFPS_HOST_DEVICE inline bool filter_blurred(float n2, float d, int j)
+{
+    return !(n2 * 0x1p-9f <= (float)j * d);
+}
+
 }  // namespace rfps
