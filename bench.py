@@ -644,19 +644,6 @@ def run_batch(args, rf, dev, stream):
     tune_s = time.perf_counter() - t0
     log("autotuner: %s, %.2f ms per batch (%.1f s)" % (chosen, tuned_ms, tune_s))
     kw = dict(groups=chosen["groups"], lookahead=chosen["lookahead"], tile=chosen["tile"])
-    # the default call picks a team size for every cloud; the autotuner's
-    # shapes are uniform: the faster of the two is timed
-    a, b = ev(), ev()
-    for r in range(4):
-        if r == 1:
-            a.record(stream)
-        rf.sample_batched(x, off_d, m_d, m_total=MT, ws=ws, out_idx=out_i, out_d2=out_d, check=False)
-    b.record(stream)
-    torch.cuda.synchronize()
-    default_first_ms = a.elapsed_time(b) / 3
-    log("default call: %.2f ms per batch" % default_first_ms)
-    if default_first_ms < tuned_ms:
-        kw = dict(groups=0, lookahead=0, tile=0)
 
     def call(flags=0, **over):
         p = dict(kw)

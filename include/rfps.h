@@ -384,7 +384,9 @@ rfps_status rfps_batched_read_telemetry(const void *ws, size_t ws_bytes, void *s
  * (2, 3, 4, 8) and tile (32, 64) that `base` leaves at 0 (non-zero fields of
  * base are kept), `reps` timed runs each after one untimed run, and returns
  * the fastest by median in *best (host) and its median in *best_ms (host,
- * may be NULL).  Shapes the device cannot hold (RFPS_ERR_CAPACITY,
+ * may be NULL).  When base leaves groups and lookahead at 0, the call without
+ * a uniform shape (both 0: for every cloud its own) is timed too, and returned
+ * when the fastest uniform one takes more than a tenth longer.  Shapes the device cannot hold (RFPS_ERR_CAPACITY,
  * RFPS_ERR_UNSUPPORTED) are skipped; every other candidate must reproduce
  * the first one's selections exactly (else RFPS_ERR_INTERNAL).  On return
  * the outputs hold the result of the chosen configuration.  Synchronous:
