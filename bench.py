@@ -208,7 +208,6 @@ def main():
               out_idx=out_i, out_d2=out_d)
     tel = rf.read_telemetry(idx)
     tr, hz = rf.read_trace(idx)
-    lookahead = args.lookahead or 3   # candidates per workgroup (the library's choice on broad clouds)
     # phase clocks of workgroup 0 without the counters (instrumented kernel)
     idx = rf.build_index(x, n_vox=n_vox, reuse=idx)
     rf.sample(idx, M, 0, groups=args.groups, lookahead=args.lookahead, flags=rf.F_CLOCKS | fdist, out_idx=out_i,
@@ -221,10 +220,11 @@ def main():
                    "failures": clk["merge_failures"] / nr, "wg0_apply_pairs": clk["apply_pairs"] / nr,
                    "wg0_apply_rekeys": clk["apply_rekeys"] / nr}
     # latency floor of one exchange round: bare exchanges of the sampler's
-    # slot size among the same workgroups (nothing else in the round)
-    G_used = args.groups or 0
-    ex_floor_us = rf.probe_exchange(idx, words=4 * lookahead + 4, rounds=2000, groups=G_used)
-    ex_floor_1w_us = rf.probe_exchange(idx, words=1, rounds=2000, groups=G_used)
+    # slot size among as many workgroups (nothing else in the round)
+    team = {"groups": clk["team"] & 0xffff, "candidates": clk["team"] >> 16}
+    slot_words = 4 * (team["candidates"] + 1)
+    ex_floor_us = rf.probe_exchange(idx, words=slot_words, rounds=2000, groups=team["groups"])
+    ex_floor_1w_us = rf.probe_exchange(idx, words=1, rounds=2000, groups=team["groups"])
     # per exchange round: (publish time, outcome time | picks << 48)
     picks_per_round = (tr[:, 1] >> np.uint64(48)).astype(np.int64)
     t_done = (tr[:, 1] & np.uint64((1 << 48) - 1)).astype(np.int64)
@@ -285,7 +285,7 @@ def main():
                         "note": "publish to merged outcome of workgroup 0, per exchange round"},
         "round_phases_us": phases,
         "merge_per_round": merge_stats,
-        "exchange_floor_us": {"slot_words": 4 * lookahead + 4, "per_round": ex_floor_us,
+        "exchange_floor_us": {"slot_words": slot_words, "team": team, "per_round": ex_floor_us,
                               "one_word_per_round": ex_floor_1w_us,
                               "note": "bare exchange rounds (publish, read every slot) among the same workgroups"},
         "latency_floor_ms": lat_floor_ms,

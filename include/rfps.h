@@ -143,7 +143,9 @@ typedef struct rfps_telemetry {
      * words that were not yet published at its first pass (waiting for the
      * slowest workgroup it reads, and for the stores' way) */
     int64_t ticks_wait;
-    int64_t reserved;
+    /* the multi-pick sampler's team, single cloud: workgroups + 65536 *
+     * candidates each published per exchange */
+    int64_t team;
     /* finer clocks of workgroup 0 (multi-pick sampler, single cloud): the
      * merge's listing (and any cut of a long list), its conflict rows
      * (ticks_merge_rank), its certification (ticks_merge_walk) and its

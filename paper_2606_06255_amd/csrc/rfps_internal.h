@@ -42,6 +42,7 @@ constexpr int kTeleTicksMerge = 11;
 constexpr int kTeleTicksApply = 12;
 constexpr int kTeleTickHz = 13;
 constexpr int kTeleTicksWait = 14;
+constexpr int kTeleTeam = 15;
 constexpr int kTeleSub = 16;        // eight finer clocks of the rounds (see rfps_telemetry)
 constexpr int kTeleMergeStats = 24; // listed-above, listed, failures summed over rounds
 

@@ -1707,6 +1707,7 @@ __device__ __forceinline__ void rounds_single(const RoundArgs &a)
             atomicAdd(&hdr->tele[0], (unsigned long long)(a.m > 1 ? a.m - 2 : 0));
             atomicAdd(&hdr->tele[1], (unsigned long long)hdr->n_tiles);
             atomicAdd(&hdr->tele[kTeleExchanges], tl.rounds);
+            hdr->tele[kTeleTeam] = (unsigned long long)G | ((unsigned long long)K << 16);
         }
     }
     if (blockIdx.x == 0 && tid == 0)

@@ -58,3 +58,13 @@ def test_clocks_cover_the_phases(rf, m, groups):
     assert 0 < t["ticks_apply_update"] < t["ticks_apply"] == t["ticks_apply_loop"]
     assert t["apply_pairs"] >= t["apply_rekeys"] > 0
     assert t["merge_above"] >= t["merge_listed"] > t["merge_failures"] >= 0
+
+
+def test_team_is_reported(rf):
+    P = np.random.default_rng(5).random((9000, 3)).astype(np.float32)
+    for flags in (rf.F_CLOCKS, rf.F_TELEMETRY):
+        for groups, lookahead in ((7, 8), (4, 2), (64, 3)):
+            t = _telemetry(rf, P, 900, flags=flags, groups=groups, lookahead=lookahead)
+            assert t["team"] == groups + 65536 * lookahead
+        t = _telemetry(rf, P, 900, flags=flags)
+        assert 1 <= t["team"] % 65536 <= 256 and 2 <= t["team"] // 65536 <= 8
