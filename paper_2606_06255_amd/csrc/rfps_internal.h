@@ -142,8 +142,8 @@ __device__ __forceinline__ float sqdist(float px, float py, float pz, float sx, 
 
 // Correctly rounded FP32 square root of x in [0, +inf] (NaN passes through):
 // the compiler's expansion of sqrtf, which is correctly rounded unless that is
-// switched off.  (Compared with the FP64 root, rounded and checked against the
-// midpoints to both neighbours, for every FP32 value.)
+// switched off (the tests compare it next to the midpoints of two roots, where
+// a wrong rounding shows first; it was compared for every FP32 value once).
 __device__ __forceinline__ float sqrt_rn(float x) { return sqrtf(x); }
 
 // Euclidean mode (RFPS_F_SQRT).  Sec. 3.4.3 (eq. point_distance_update)
