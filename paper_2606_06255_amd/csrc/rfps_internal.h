@@ -467,7 +467,8 @@ hipError_t launch_rfps_solo(const IndexView &v, int m, int start, bool euclid, i
 hipError_t launch_build_batch(const IndexView &v, const float *xyz, hipStream_t s);
 hipError_t launch_rfps_rounds_batched(const IndexView &v, const SampleLaunch &L, int32_t *out_idx,
                                       float *out_d2, hipStream_t s);
-// Shells a grid of n bins per axis may use: keys s * n^3 + V_id stay below 2^32.
+// Shells a grid of n bins per axis may use: keys, s * n^3 plus the voxel's
+// number, stay below 2^32.
 __host__ __device__ inline uint32_t shell_cap_for(uint32_t n, bool shells)
 {
     if (!shells)
@@ -477,15 +478,17 @@ __host__ __device__ inline uint32_t shell_cap_for(uint32_t n, bool shells)
     return (uint32_t)(cap < (unsigned long long)kMaxShells ? cap : (unsigned long long)kMaxShells);
 }
 
-// Voxel key of a point (Sec. 3.2): V_id = v_z n^2 + v_y n + v_x with
+// Voxel key of a point: a number for its voxel (v_x, v_y, v_z), with
 // v_a = clamp(floor((p_a - pmin_a) / L), 0, n - 1), the quotient in FP64.
+// Sec. 3.2 numbers voxels by rows, V_id = v_z n^2 + v_y n + v_x; here they are
+// numbered in blocks of 4 x 4 x 4, and inside one in Morton order, when the
+// bins per axis allow it (by rows otherwise): points that follow one another
+// then lie in a compact region, not along a row of voxels.
 // With range shells (shell_inv > 0), a point at distance r from `o` lies in
 // shell s = min(floor(r / spacing), shell_cap - 1), which uses cubes of edge
 // (s + 1) L and ceil(n / (s + 1)) bins per axis from the same corner; its key
-// is s * n^3 + V_id on that coarser grid, so shells never share a voxel.
-// The voxels are numbered in blocks of 4 x 4 x 4, and inside one in Morton
-// order, when the bins per axis allow it: points that follow one another then
-// lie in a compact region, not along a row of voxels.
+// is s * n^3 plus its number on that coarser grid, so shells never share a
+// voxel.
 // Any partition of the points into voxels leaves the sampling result
 // unchanged (the tile spheres enclose their members whatever the grid).
 __device__ __forceinline__ uint32_t voxel_key(float px, float py, float pz, const double *pmin, double L,
