@@ -1,6 +1,6 @@
 // Spherical-voxel index builder (Sec. 3.2; the GPU steps of Algorithm 2):
-// bounding box, voxel size L (eq. voxel_size), a key for every point's voxel
-// (voxel_key in rfps_internal.h), stable LSD radix sort of (key, original
+// bounding box, voxel size L (eq. voxel_size), clamped voxel id
+// V_id = v_z n^2 + v_y n + v_x, stable LSD radix sort of (V_id, original
 // index), gather to structure-of-arrays coordinates, split of the active
 // voxels into tiles of at most T points and an enclosing sphere per tile.
 //
@@ -914,7 +914,7 @@ hipError_t launch_build_index(const IndexView &v, const float *xyz, hipStream_t 
 
 // ---------------------------------------------------------------------------
 // Batched index: the clouds of a batch share one sorted index.  A point of
-// cloud c gets base_c plus its voxel key on the cloud's own grid, so
+// cloud c gets the key base_c + V_id (V_id on the cloud's own grid), so
 // voxels and tiles never mix clouds and the tiles of every cloud are one
 // contiguous range.
 // ---------------------------------------------------------------------------
