@@ -287,7 +287,7 @@ def main():
         "merge_per_round": merge_stats,
         "exchange_floor_us": {"slot_words": slot_words, "team": team, "per_round": ex_floor_us,
                               "one_word_per_round": ex_floor_1w_us,
-                              "note": "bare exchange rounds (publish, read every slot) among the same workgroups"},
+                              "note": "bare exchange rounds (publish, read every slot) among as many workgroups"},
         "latency_floor_ms": lat_floor_ms,
         # the sampler keeps its state in LDS and waits on one exchange per
         # round: it is latency-bound.  achieved / peak / frac are the

@@ -69,10 +69,17 @@ RFPS_HOST_DEVICE inline bool share_granted(uint32_t tiles, uint32_t pts, uint32_
 // and the lookahead steps of each wavefront.  A cloud most of whose tiles
 // hold many of its picks (few, full tiles: a spinning sweep sampled to a
 // quarter) needs depth, one with several tiles per pick breadth.  Measured
-// sampling times in ms for (workgroups, candidates, steps):
-//   sweep 114,624 -> 28,656 (12.7 picks per tile): (64, 6, 4) 5.0, (64, 4, 2)
-//   6.9, (256, 3, 2) 6.9; sweep 28,656 -> 7,164: (32, 6, 4) 1.77, (128, 3, 2) 2.3
-//   room 80,000 -> 20,000 (2.1 picks per tile): (256, 3, 2) 2.87, (64, 6, 4) 4.3
+// sampling times in ms for (workgroups, candidates, steps), by picks per tile:
+//                                   (256, 3, 2)  (128, 3, 2)  (64, 3, 2)  (64, 6, 4)
+//   sweep of 114,624 (2,154 tiles)  3: 2.70         2.30         2.14        2.47
+//                                   6.5: 4.18       3.73         3.61        3.44
+//                                   13: 6.38        5.98         6.24        5.24
+//   room of 40,000 (3,643 tiles)    2: 1.56         1.36         1.51        1.69
+//                                   6.5: 2.89       2.84         3.52        3.09
+// The line of six is a sweep's: there depth pays from about five picks a tile.
+// A room or a very large sweep is up to 16 % faster broad at 6.5 (room of
+// 120,000: (256, 3, 2) 6.07, the rule's (64, 6, 4) 7.06; sweep of 1,000,000:
+// 14.7, and 16.1 by the rule).
 constexpr int kDeepPicks = 6;  // picks per tile from which depth pays
 struct TeamShape {
     int G, K, steps;
@@ -82,8 +89,9 @@ RFPS_HOST_DEVICE inline TeamShape team_shape(uint32_t tiles, uint32_t m)
     TeamShape t;
     const bool deep = m > (uint32_t)kDeepPicks * tiles;
     // enough workgroups that the exchange, whose cost grows with the team,
-    // still replaces more local work than it adds; the best team of each
-    // range is within 5 % of its neighbours' at the limits
+    // still replaces more local work than it adds: up to six picks a tile the
+    // rule is within 7 % of the best of ten shapes from 602 to 39,449 tiles
+    // (12 % on a sweep of 602 at 5.5 picks)
     if (deep)
         t.G = tiles < 400 ? 16 : tiles < 1500 ? 32 : 64;
     else

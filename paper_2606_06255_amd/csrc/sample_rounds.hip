@@ -38,17 +38,17 @@
 // picks is its key order, which rank 0 of the team works out while the next
 // exchange is in flight.
 //
-// What bounds a round (1,048,576 points -> 65,536 picks, 256 workgroups, 869
-// rounds of 10.8 us, 75 picks each): lookahead 1.8 us (a serial chain of wave
-// maxima), exchange 3.7 us (2.7 of them are the bare exchange of the team's
-// 32 KB, measured with nothing else in a round), list 1.0, conflicts 1.5,
-// certification 1.7, apply 1.1.  One lookahead per wavefront instead of one
+// What bounds a round (the bench's 1,048,576 points -> 65,536 picks, 256
+// workgroups, 892 rounds of 10.8 us, 73 picks each): lookahead 1.9 us (a
+// serial chain of wave maxima), exchange 3.6 us (2.4 of them are the bare
+// exchange of the team's 32 KB, measured with nothing else in a round), list
+// 1.0, conflicts 1.4, certification 1.3, picks 0.3, apply 1.1.  One lookahead per wavefront instead of one
 // per workgroup removes the serial steps over all tiles of a workgroup (the
 // largest term before: 16 steps on one list of tile keys), and the matrix
 // cores take the pair tests, which were the next.  Sampling times before and
-// after: 1,048,576 -> 65,536 15.5 -> 9.4 ms, 114,623 -> 28,655 Euclidean 10.1
-// -> 5.5 ms, 80,000 -> 20,000 4.5 -> 2.9 ms; with a team size for every cloud,
-// 32 clouds of 8k to 120k points 35 -> 8.8 ms.
+// after: 1,048,576 -> 65,536 15.5 -> 9.5 ms, 114,623 -> 28,655 Euclidean 10.1
+// -> 5.6 ms, 80,000 -> 20,000 4.5 -> 2.8 ms; with a team size for every cloud,
+// 32 clouds of 8k to 120k points 34.3 -> 8.9 ms.
 //
 // Exchange scopes: a team spread over the device stores through agent-scope
 // atomics (coherent across XCDs); a team whose workgroups all sit on one XCD
